@@ -6,11 +6,13 @@
 // Gaussian index).  Instead of radix-sorting K 64-bit keys (about 6 passes over
 // K entries), the path
 //   1. sorts the N Gaussians by depth bits with a stable LSD radix sort that
-//      starts from index order, which yields (depth bits, index) order;
+//      starts from index order, which yields (depth bits, index) order (small
+//      sets: by counting, for each Gaussian, those before it);
 //   2. places every (tile, Gaussian) entry directly at its final position,
 //      counting for each tile the earlier depth ranks that cover it (the
 //      direct emission below, in two levels: 8 x 8-tile super tiles, then
-//      tiles); or, for frames of more tiles than that handles,
+//      tiles; small frames: each tile walks the ranks); or, for frames of more
+//      super tiles than its tables hold,
 //   2'. emits every Gaussian's tiles in rank order at the exclusive prefix
 //      sum of its tile counts and stably sorts the K entries by tile id
 //      (ceil(log2 T) bits, 1-2 passes).
@@ -21,7 +23,13 @@
 namespace gs {
 
 constexpr int kRsThreads = 256;
-constexpr int kOsItemsN = 8;    // depth sort of N keys (onesweep): 4096 keys per workgroup of 8 waves
+// Depth sort of N keys (onesweep): 4096 keys per workgroup of 8 waves, or 2048
+// up to kOsSmallN keys, where half the keys to rank per workgroup save more
+// than the longer look-back costs (14.1 against 15.0 us a pass at 200k
+// keys, 15.6 against 15.2 at 500k).
+constexpr int kOsItemsN = 8;
+constexpr int kOsItemsSmall = 4;
+constexpr int64_t kOsSmallN = int64_t(1) << 18;
 constexpr int kOsThreads = 512;
 constexpr int kRsItemsK = 16;   // tile sort of K entries: 4096 keys per block
 constexpr int kScanItems = 16;
@@ -124,58 +132,29 @@ __global__ __launch_bounds__(256) void k_scan_sums(const uint32_t* __restrict__ 
   if (threadIdx.x == 0) sums[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// Chunk bounds of the direct emission, derived from the scanned counts (see
-// k_scan_apply<true>): with K the total, chunk size E = max(min_entries,
-// ceil(K / target)) and count C = min(ceil(K / E), cmax), bounds[c] is the
-// first rank whose exclusive offset is >= c E for c < C, and n for
-// C <= c <= cmax.  k_dev != NULL: K and the depth sort's look-back flag
-// (total[1]) are also copied to k_dev[0], k_dev[1].
-struct ChunkArgs {
-  uint32_t* bounds;
-  int cmax;
-  unsigned long long min_entries, target;
-  unsigned long long* k_dev;
-};
-
 // Per chunk: its offset is the sum of the sums of all earlier chunks, which
 // every block adds up itself (a few thousand values at most, read from L2) --
 // no separate top-level scan launch.  The last block also writes the 64-bit
 // total.  Thread t owns items [16 t, 16 t + 16) of the chunk; whole, 16-byte
 // aligned runs move as four 16-byte accesses.
-// BOUNDS: instead of the offsets, write the chunk bounds of ChunkArgs.  Every
-// block also sums all chunk sums (K); item i, whose offsets span (offs[i],
-// offs[i] + cnt[i]], holds the bound of every chunk c >= 1 with c E in that
-// span: bounds[c] = i + 1 (the lower bound of c E among the offsets).
-template <bool BOUNDS>
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__ in, int64_t n,
                                                     const uint32_t* __restrict__ sums, uint32_t* __restrict__ out,
-                                                    unsigned long long* __restrict__ total, ChunkArgs ca) {
+                                                    unsigned long long* __restrict__ total) {
   __shared__ uint32_t lds[256];
-  __shared__ unsigned long long red[2][4];
+  __shared__ unsigned long long red[4];
   const int b = blockIdx.x;
-  unsigned long long pre = 0, all = 0;
-  const int upto = BOUNDS ? static_cast<int>(gridDim.x) : b;
-  for (int i = threadIdx.x; i < upto; i += 256) {
-    const uint32_t x = sums[i];
-    if (i < b) pre += x;
-    all += x;
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    pre += __shfl_xor(pre, o, 64);
-    if (BOUNDS) all += __shfl_xor(all, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = pre;
-    red[1][threadIdx.x >> 6] = all;
-  }
+  unsigned long long pre = 0;
+  for (int i = threadIdx.x; i < b; i += 256) pre += sums[i];
+  for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = pre;
   __syncthreads();
-  const unsigned long long offset = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  const unsigned long long offset = red[0] + red[1] + red[2] + red[3];
   const int64_t base = static_cast<int64_t>(b) * kScanChunk;
   uint32_t v[kScanItems];
   uint32_t s = 0;
   const int64_t my = base + static_cast<int64_t>(threadIdx.x) * kScanItems;
-  const bool vec = my + kScanItems <= n && ((reinterpret_cast<uintptr_t>(in + my) |
-                                              (BOUNDS ? 0u : reinterpret_cast<uintptr_t>(out + my))) & 15u) == 0;
+  const bool vec = my + kScanItems <= n &&
+                   ((reinterpret_cast<uintptr_t>(in + my) | reinterpret_cast<uintptr_t>(out + my)) & 15u) == 0;
   if (vec) {
 #pragma unroll
     for (int q = 0; q < kScanItems / 4; ++q) {
@@ -190,40 +169,21 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__
   for (int j = 0; j < kScanItems; ++j) s += v[j];
   uint32_t tot;
   const uint32_t local = block_exclusive_scan(s, lds, tot);
-  if constexpr (BOUNDS) {
-    const unsigned long long K = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-    const unsigned long long E = max(ca.min_entries, (K + ca.target - 1) / ca.target);
-    const unsigned long long C = min((K + E - 1) / E, static_cast<unsigned long long>(ca.cmax));
-    unsigned long long o = offset + local;
+  uint32_t o[kScanItems];
+  uint32_t run = local + static_cast<uint32_t>(offset);
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-      const unsigned long long hi = o + v[j];
-      for (unsigned long long c = o / E + 1; c < C && c * E <= hi; ++c) ca.bounds[c] = static_cast<uint32_t>(my + j + 1);
-      o = hi;
-    }
-    if (b == 0) {
-      for (int c = threadIdx.x; c <= ca.cmax; c += 256)
-        if (static_cast<unsigned long long>(c) >= C) ca.bounds[c] = static_cast<uint32_t>(n);
-        else if (c == 0) ca.bounds[0] = 0u;
-      if (ca.k_dev && threadIdx.x == 0) { ca.k_dev[0] = K; ca.k_dev[1] = total[1]; }
-    }
+  for (int j = 0; j < kScanItems; ++j) {
+    o[j] = run;
+    run += v[j];
+  }
+  if (vec) {
+#pragma unroll
+    for (int q = 0; q < kScanItems / 4; ++q)
+      reinterpret_cast<uint4*>(out + my)[q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
   } else {
-    uint32_t o[kScanItems];
-    uint32_t run = local + static_cast<uint32_t>(offset);
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-      o[j] = run;
-      run += v[j];
-    }
-    if (vec) {
-#pragma unroll
-      for (int q = 0; q < kScanItems / 4; ++q)
-        reinterpret_cast<uint4*>(out + my)[q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kScanItems; ++j)
-        if (my + j < n) out[my + j] = o[j];
-    }
+    for (int j = 0; j < kScanItems; ++j)
+      if (my + j < n) out[my + j] = o[j];
   }
   if (total && b == static_cast<int>(gridDim.x) - 1 && threadIdx.x == 0) *total = offset + tot;
 }
@@ -238,16 +198,8 @@ static size_t scan_ws_words(int64_t n) { return static_cast<size_t>(ceil_div(n >
 static gs_status device_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, ScanWs ws, hipStream_t s) {
   const int nb = static_cast<int>(ceil_div(n > 0 ? n : 1, kScanChunk));
   { TimedLaunch gs_tl("k_scan_sums", s); k_scan_sums<<<nb, 256, 0, s>>>(in, n, ws.sums); }
-  { TimedLaunch gs_tl("k_scan_apply<false>", s); k_scan_apply<false><<<nb, 256, 0, s>>>(in, n, ws.sums, out, ws.total, ChunkArgs{}); }
+  { TimedLaunch gs_tl("k_scan_apply", s); k_scan_apply<<<nb, 256, 0, s>>>(in, n, ws.sums, out, ws.total); }
   return check_launch("device_exclusive_scan");
-}
-
-// The scan's total and the direct emission's chunk bounds (no offsets).
-static gs_status device_chunk_bounds(const uint32_t* in, int64_t n, ScanWs ws, ChunkArgs ca, hipStream_t s) {
-  const int nb = static_cast<int>(ceil_div(n > 0 ? n : 1, kScanChunk));
-  { TimedLaunch gs_tl("k_scan_sums", s); k_scan_sums<<<nb, 256, 0, s>>>(in, n, ws.sums); }
-  { TimedLaunch gs_tl("k_scan_apply<true>", s); k_scan_apply<true><<<nb, 256, 0, s>>>(in, n, ws.sums, nullptr, ws.total, ca); }
-  return check_launch("device_chunk_bounds");
 }
 
 size_t scan_sums_words(int64_t n) { return scan_ws_words(n); }
@@ -490,7 +442,7 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
 // is the same for every key keeps the order.  The last pass that changes it
 // (from the digit counts of every pass, ghist) is the terminal one: it writes
 // the values in their final order to vals_final, with each value's rectangle
-// and tile count when rect != NULL, and no keys; the passes after it return
+// when rect != NULL (and its tile count when cnt_out != NULL), and no keys; the passes after it return
 // at once.  (All passes trivial: pass 0 is terminal and copies.)
 template <int ITEMS, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_os_scatter(const uint32_t* __restrict__ keys_in,
@@ -504,7 +456,7 @@ __global__ __launch_bounds__(THREADS) void k_os_scatter(const uint32_t* __restri
                                                            uint32_t* __restrict__ vals_final,
                                                            const uint2* __restrict__ rect,
                                                            uint2* __restrict__ rect_out,
-                                                           uint32_t* __restrict__ cnt_out, int cshift) {
+                                                           uint32_t* __restrict__ cnt_out) {
   constexpr int CHUNK = THREADS * ITEMS;
   constexpr int WAVES = THREADS / 64;
   constexpr int PER_WAVE = CHUNK / WAVES;
@@ -566,7 +518,7 @@ __global__ __launch_bounds__(THREADS) void k_os_scatter(const uint32_t* __restri
       if (rect) {
         const uint2 rc = rect[val];
         rect_out[g] = rc;
-        cnt_out[g] = rect_count(rect_at(rc, cshift));
+        if (cnt_out) cnt_out[g] = rect_count(rc);
       }
     } else {
       keys_out[g] = key;
@@ -690,7 +642,7 @@ __global__ __launch_bounds__(THREADS) void k_os_scatter(const uint32_t* __restri
       if (tid + j * THREADS < nvalid) {
         vals_final[g[j]] = val[j];
         rect_out[g[j]] = rc[j];
-        cnt_out[g[j]] = rect_count(rect_at(rc[j], cshift));
+        if (cnt_out) cnt_out[g[j]] = rect_count(rc[j]);
       }
     }
     return;
@@ -717,14 +669,13 @@ static size_t os_state_words(int64_t count, int chunk, int passes) {
 // Sorts `count` pairs over key bits [0, total_bits).  Input in (ka, va),
 // which the passes use as ping-pong buffers with (kb, vb); the values in
 // sorted order end in vals_final (with rect: each value's rectangle in
-// rect_out and in cnt_out the count of the blocks of 2^cshift x 2^cshift
-// tiles it touches -- its tile count for cshift 0).
+// rect_out and, if given, its tile count in cnt_out).
 // w.ghist must be zero on entry (k_depth_keys clears both sorts' counts).
 template <int ITEMS, int THREADS>
 static gs_status onesweep_sort_pairs(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, int64_t count,
                                      int total_bits, OsWs w, hipStream_t s, uint32_t* vals_final,
                                      const uint2* rect = nullptr, uint2* rect_out = nullptr,
-                                     uint32_t* cnt_out = nullptr, int cshift = 0) {
+                                     uint32_t* cnt_out = nullptr) {
   constexpr int CHUNK = THREADS * ITEMS;
   const int passes = (total_bits + 7) / 8;
   if (count <= 0) return GS_OK;
@@ -737,8 +688,7 @@ static gs_status onesweep_sort_pairs(uint32_t* ka, uint32_t* va, uint32_t* kb, u
   for (int p = 0; p < passes; ++p) {
     { TimedLaunch gs_tl("k_os_scatter", s); k_os_scatter<ITEMS, THREADS><<<nblocks, THREADS, 0, s>>>(ka, va, kb, vb, count, p, total_bits, w.ghist,
                                                        w.state + static_cast<size_t>(p) * nblocks * 256,
-                                                       w.counters + p, w.err, vals_final, rect, rect_out, cnt_out,
-                                                       cshift); }
+                                                       w.counters + p, w.err, vals_final, rect, rect_out, cnt_out); }
     if ((st = check_launch("k_os_scatter")) != GS_OK) return st;
     uint32_t* t = ka; ka = kb; kb = t;
     t = va; va = vb; vb = t;
@@ -750,11 +700,20 @@ static int sort_passes(int bits) { return (bits + 7) / 8; }
 
 // ------------------------------------------------------------- bin kernels
 
-// Depth keys, and each Gaussian's tile rectangle packed into 8 bytes
-// (x0 | x_end << 16, y0 | y_end << 16, ends exclusive; all zero when empty) so
-// that the later rank-order passes read one small word per Gaussian instead
-// of its record and radius.  Also clears `zero_words` words at `zero` (the
-// depth sort's digit counts, K and the look-back error flag).
+// A Gaussian's tile rectangle packed into 8 bytes (x0 | x_end << 16,
+// y0 | y_end << 16, ends exclusive; all zero when empty).
+__device__ __forceinline__ uint2 packed_rect(float u, float v, int radius, int tiles_x, int tiles_y) {
+  int x0, x1, y0, y1;
+  const int c = tile_rect(u, v, radius, tiles_x, tiles_y, x0, x1, y0, y1);
+  return c > 0 ? make_uint2(static_cast<uint32_t>(x0) | (static_cast<uint32_t>(x1 + 1) << 16),
+                            static_cast<uint32_t>(y0) | (static_cast<uint32_t>(y1 + 1) << 16))
+               : make_uint2(0u, 0u);
+}
+
+// Depth keys, and each Gaussian's packed tile rectangle, so that the later
+// rank-order passes read one small word per Gaussian instead of its record
+// and radius.  Also clears `zero_words` words at `zero` (the depth sort's
+// digit counts, K and the look-back error flag).
 __global__ __launch_bounds__(256) void k_depth_keys(int n, const float* __restrict__ depth,
                                                     const float4* __restrict__ records,
                                                     const int* __restrict__ radius, int tiles_x, int tiles_y,
@@ -767,11 +726,130 @@ __global__ __launch_bounds__(256) void k_depth_keys(int n, const float* __restri
   keys[i] = __float_as_uint(depth[i]);
   vals[i] = static_cast<uint32_t>(i);
   const float4 r0 = records[3 * static_cast<int64_t>(i)];
-  int x0, x1, y0, y1;
-  const int c = tile_rect(r0.x, r0.y, radius[i], tiles_x, tiles_y, x0, x1, y0, y1);
-  rect[i] = c > 0 ? make_uint2(static_cast<uint32_t>(x0) | (static_cast<uint32_t>(x1 + 1) << 16),
-                               static_cast<uint32_t>(y0) | (static_cast<uint32_t>(y1 + 1) << 16))
-                  : make_uint2(0u, 0u);
+  rect[i] = packed_rect(r0.x, r0.y, radius[i], tiles_x, tiles_y);
+}
+
+// ------------------------------------------------------------- small frames
+// Sets of at most kSmallN Gaussians skip the radix sort: the rank of Gaussian
+// i is the number of Gaussians j with (key_j, j) < (key_i, i), counted over
+// all j.  A workgroup ranks 64 Gaussians, one per lane; its 16 waves share
+// the j range in blocks of 64 whose keys are wave-uniform (two VALU
+// instructions per j).  Writes order and rect_rank as the terminal sort pass
+// does, and clears the same words as k_depth_keys.  Bound by launches and
+// latency: the six launches it replaces (keys, histogram, four passes) took
+// 51 us against 11.7 here at 4,096 Gaussians (event timings, about 4 us of
+// each launch the events' own).  kSmallN: the count
+// is quadratic (13 us of VALU work at 16,384), the sort is not.
+constexpr int kSmallN = 16384;
+constexpr int kSmallRankThreads = 1024;
+
+__global__ __launch_bounds__(kSmallRankThreads) void k_small_rank(int n, const float* __restrict__ depth,
+                                                                  const float4* __restrict__ records,
+                                                                  const int* __restrict__ radius, int tiles_x,
+                                                                  int tiles_y, uint32_t* __restrict__ order,
+                                                                  uint2* __restrict__ rect_rank,
+                                                                  uint32_t* __restrict__ zero, int zero_words) {
+  constexpr int WAVES = kSmallRankThreads / 64;
+  __shared__ uint32_t s_cnt[WAVES][64];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  if (blockIdx.x == 0)
+    for (int z = threadIdx.x; z < zero_words; z += kSmallRankThreads) zero[z] = 0u;
+  const uint32_t* const keys = reinterpret_cast<const uint32_t*>(depth);
+  const int own = blockIdx.x;                  // this workgroup's block of 64
+  const int i = own * 64 + lane;
+  const uint32_t ki = i < n ? keys[i] : 0u;
+  const int whole = n / 64;                    // blocks of 64 keys that are full
+  uint32_t cnt = 0u;
+  for (int b = wave; b < whole; b += WAVES) {
+    const uint32_t* const kb = keys + 64 * b;
+    if (b == own) {
+#pragma unroll 16
+      for (int j = 0; j < 64; ++j) cnt += (kb[j] < ki || (kb[j] == ki && j < lane)) ? 1u : 0u;
+    } else if (b < own) {
+#pragma unroll 16
+      for (int j = 0; j < 64; ++j) cnt += kb[j] <= ki ? 1u : 0u;
+    } else {
+#pragma unroll 16
+      for (int j = 0; j < 64; ++j) cnt += kb[j] < ki ? 1u : 0u;
+    }
+  }
+  if (wave == whole % WAVES)                   // the last, partial block
+    for (int j = 64 * whole; j < n; ++j) cnt += (keys[j] < ki || (keys[j] == ki && j < i)) ? 1u : 0u;
+  s_cnt[wave][lane] = cnt;
+  __syncthreads();
+  if (wave != 0 || i >= n) return;
+  uint32_t rank = 0u;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) rank += s_cnt[w][lane];
+  const float4 r0 = records[3 * static_cast<int64_t>(i)];
+  order[rank] = static_cast<uint32_t>(i);
+  rect_rank[rank] = packed_rect(r0.x, r0.y, radius[i], tiles_x, tiles_y);
+}
+
+// Small frames place their entries tile by tile: a workgroup walks all ranks
+// for one tile, its four waves a quarter each (qcnt[tile][4]: their counts,
+// total[tile]: the sum), and after k_tile_starts walks them again to write
+// the tile's list.  Each rank costs a tile about ten instructions per 64, so
+// the work grows with n x tiles; up to kSmallWork of it the two launches
+// cost less than the chunked emission's eight.
+constexpr int64_t kSmallWork = int64_t(1) << 25;
+static bool small_frame(int64_t n, int64_t ntiles) { return n <= kSmallN && n * ntiles <= kSmallWork; }
+
+__device__ __forceinline__ bool covers(uint2 rc, uint32_t tx, uint32_t ty) {
+  return (rc.x & 0xFFFFu) <= tx && tx < (rc.x >> 16) && (rc.y & 0xFFFFu) <= ty && ty < (rc.y >> 16);
+}
+
+constexpr int kSmallUnroll = 8;
+__global__ __launch_bounds__(256) void k_small_count(int n, const uint2* __restrict__ rect_rank, int tiles_x,
+                                                     uint32_t* __restrict__ qcnt, uint32_t* __restrict__ total) {
+  __shared__ uint32_t s_q[4];
+  const uint32_t tile = blockIdx.x, tx = tile % static_cast<uint32_t>(tiles_x), ty = tile / static_cast<uint32_t>(tiles_x);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int per = (n + 255) / 256 * 64, r0 = wave * per, r1 = min(n, r0 + per);
+  uint32_t c = 0u;
+  for (int r = r0; r < r1; r += 64 * kSmallUnroll) {
+    uint2 rc[kSmallUnroll];
+#pragma unroll
+    for (int u = 0; u < kSmallUnroll; ++u)
+      rc[u] = r + 64 * u + lane < r1 ? rect_rank[r + 64 * u + lane] : make_uint2(0u, 0u);
+#pragma unroll
+    for (int u = 0; u < kSmallUnroll; ++u) c += static_cast<uint32_t>(__popcll(__ballot(covers(rc[u], tx, ty))));
+  }
+  if (lane == 0) {
+    s_q[wave] = c;
+    qcnt[4 * tile + wave] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) total[tile] = (s_q[0] + s_q[1]) + (s_q[2] + s_q[3]);
+}
+
+__global__ __launch_bounds__(256) void k_small_emit(int n, const uint32_t* __restrict__ order,
+                                                    const uint2* __restrict__ rect_rank, int tiles_x,
+                                                    const uint32_t* __restrict__ qcnt,
+                                                    const uint32_t* __restrict__ start,
+                                                    const uint32_t* __restrict__ fits,
+                                                    uint32_t* __restrict__ point_list) {
+  if (*fits == 0u) return;
+  const uint32_t tile = blockIdx.x, tx = tile % static_cast<uint32_t>(tiles_x), ty = tile / static_cast<uint32_t>(tiles_x);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int per = (n + 255) / 256 * 64, r0 = wave * per, r1 = min(n, r0 + per);
+  uint32_t pos = start[tile];
+#pragma unroll
+  for (int w = 0; w < 3; ++w) pos += w < wave ? qcnt[4 * tile + w] : 0u;
+  const uint64_t below = lanemask_lt();
+  for (int r = r0; r < r1; r += 64 * kSmallUnroll) {
+    uint2 rc[kSmallUnroll];
+#pragma unroll
+    for (int u = 0; u < kSmallUnroll; ++u)
+      rc[u] = r + 64 * u + lane < r1 ? rect_rank[r + 64 * u + lane] : make_uint2(0u, 0u);
+#pragma unroll
+    for (int u = 0; u < kSmallUnroll; ++u) {
+      const bool in = covers(rc[u], tx, ty);
+      const uint64_t m = __ballot(in);
+      if (in) point_list[pos + static_cast<uint32_t>(__popcll(m & below))] = order[r + 64 * u + lane];
+      pos += static_cast<uint32_t>(__popcll(m));
+    }
+  }
 }
 
 // Emit: a wave takes 64 consecutive depth ranks and writes all of their
@@ -856,9 +934,12 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 // The tile sort without sorting.  After the depth sort the entries of tile t
 // are, in order, the depth ranks whose rectangle contains t.  Two levels,
 // with super tiles of 8 x 8 tiles.
-// Coarse: the ranks are cut into C chunks of about E coarse entries each
-// (chunk c = ranks [R_c, R_c+1); a rank has one coarse entry per super tile
-// its rectangle touches).
+// Coarse: the ranks are cut into up to 1024 chunks of equally many consecutive
+// ranks (a rank has one coarse entry per super tile its rectangle touches).
+// More chunks than the chip holds at once even out their different entry
+// counts; cutting at equal entry counts needs a scan of the counts first (two
+// launches) and gave fewer, longer chunks: 35.5 -> 10.9 us for the coarse
+// emission at 200k Gaussians, 40.2 -> 30.8 at 1M, besides the scan's 17-19.
 //  1. k_chunk_count: per chunk, the coarse entries of every super tile, from
 //     a 2D difference array of the chunk's super-tile rectangles in LDS (four
 //     LDS atomics per Gaussian, then prefix sums along rows and columns) --
@@ -866,7 +947,7 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 //  2. k_chunk_colscan: per super tile, the exclusive prefix over chunks (in
 //     place) and the total; k_coarse_parts: the super tiles' starts in the
 //     coarse list and the cut of each super tile's run into parts of at most
-//     kPart entries (numbered over the super tiles in turn).
+//     1024 (small sets: 256) entries (numbered over the super tiles in turn).
 //  3. k_emit_coarse: one workgroup per chunk walks its ranks 256 at a time.
 //     Rank 64 w + l of a group comes before rank 64 w' + l' on a super tile
 //     that both rectangles contain iff (w, l) < (w', l'); with per-wave 64-bit
@@ -891,20 +972,24 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 // the tiles land as four-byte pieces scattered over the whole list, and lines
 // leave L2 partly written, several times over.
 // Same result as a stable sort by tile of the rank-ordered emission, i.e. the
-// order (tile, depth bits, index).  Used for frames of at most
-// kDirectMaxTiles tiles.
+// order (tile, depth bits, index).  Used for every frame whose super tiles'
+// tables fit in LDS (direct_ok: about 8,000 super tiles, 500,000 tiles).
 constexpr int kSuperShift = 3;            // super tiles of 8 x 8 tiles
 constexpr int kSuper = 1 << kSuperShift;
-constexpr int kDirectChunks = 512;        // chunks at most
-constexpr int64_t kDirectMinEntries = 4096;
+constexpr int kDirectChunks = 1024;       // chunks at most
 constexpr size_t kLdsBudget = 65536;      // bytes of LDS per workgroup
 constexpr size_t kEmitStaticLds = 11776;  // k_emit_coarse's fixed arrays, rounded up
-constexpr int kPart = 1024;               // coarse entries per part of the fine passes
+// Coarse entries per part of the fine passes: sets of up to kSmallPartN
+// Gaussians cut their (shorter) coarse list finer, so that its parts still
+// fill the chip (fine emission 14.2 against 21.0 us at 200k
+// Gaussians; at 1M the finer cut only lengthens the scan over the parts).
+constexpr int kPart = 1024;
+constexpr int kPartSmall = 256;
+constexpr int64_t kSmallPartN = int64_t(1) << 18;
+static int part_entries(int64_t n) { return n <= kSmallPartN ? kPartSmall : kPart; }
 constexpr int kFineThreads = 256;
 constexpr int kFineWaves = kFineThreads / 64;
-constexpr int kPartSteps = kPart / kFineThreads;
 constexpr int kFineGrid = 2048;           // workgroups of the fine passes at most (each loops over parts)
-constexpr int kDirectMaxTiles = 16384;    // tiles at most (one workgroup writes the tile starts)
 
 static int super_dim(int tiles) { return (tiles + kSuper - 1) >> kSuperShift; }
 
@@ -916,15 +1001,16 @@ static size_t emit_dyn_lds(int sx, int sy) {
 }
 static bool direct_ok(int tiles_x, int tiles_y) {
   const int sx = super_dim(tiles_x), sy = super_dim(tiles_y);
-  return static_cast<size_t>(tiles_x) * tiles_y <= static_cast<size_t>(kDirectMaxTiles) &&
-         4 * static_cast<size_t>(sx + 1) * (sy + 1) <= kLdsBudget &&
+  return 4 * static_cast<size_t>(sx + 1) * (sy + 1) <= kLdsBudget &&
          emit_dyn_lds(sx, sy) + kEmitStaticLds <= kLdsBudget;
 }
-static int64_t direct_max_chunks(int64_t cap) {
-  return std::max<int64_t>(1, std::min<int64_t>(kDirectChunks, ceil_div(std::max<int64_t>(cap, 1), kDirectMinEntries)));
-}
+// Ranks per chunk: a whole number of waves, at most kDirectChunks chunks.
+static int direct_ranks(int64_t n) { return static_cast<int>(ceil_div(std::max<int64_t>(n, 1), 64 * kDirectChunks) * 64); }
+static int direct_chunks(int64_t n) { return static_cast<int>(ceil_div(std::max<int64_t>(n, 1), direct_ranks(n))); }
 // parts at most: every super tile's run of at most `cap` coarse entries in total
-static int64_t direct_max_parts(int64_t cap, int ns) { return ceil_div(std::max<int64_t>(cap, 1), kPart) + ns; }
+static int64_t direct_max_parts(int64_t n, int64_t cap, int ns) {
+  return ceil_div(std::max<int64_t>(cap, 1), part_entries(n)) + ns;
+}
 
 // In-place inclusive prefix sums of `len` ints at p[0], p[stride], ... by one wave.
 __device__ __forceinline__ void wave_prefix_lds(int* p, int len, int stride, int lane) {
@@ -940,21 +1026,24 @@ __device__ __forceinline__ void wave_prefix_lds(int* p, int len, int stride, int
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectWaves = kDirectThreads / 64;
 
-// Per chunk: table[c][s] over the sx x sy super tiles, and the chunk's tile
-// counts added to *kfine.
-__global__ __launch_bounds__(kDirectThreads) void k_chunk_count(const uint32_t* __restrict__ bounds,
-                                                                const uint2* __restrict__ rect_rank, int sx, int sy,
-                                                                uint32_t* __restrict__ table,
-                                                                unsigned long long* __restrict__ kfine) {
+// Per chunk: table[c][s] over the sx x sy super tiles, and the sum of the
+// chunk's tile counts in kfine[c] (added up by k_tile_starts: a thousand
+// atomics on one word queue for longer than the kernel runs, 21 us against
+// 15 at 1M Gaussians).
+constexpr int kCountThreads = 256;
+constexpr int kCountWaves = kCountThreads / 64;
+__global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks, const uint2* __restrict__ rect_rank,
+                                                               int sx, int sy, uint32_t* __restrict__ table,
+                                                               unsigned long long* __restrict__ kfine) {
   extern __shared__ int s_diff[];   // (sy + 1) rows of (sx + 1)
-  __shared__ unsigned long long s_k[kDirectWaves];
+  __shared__ unsigned long long s_k[kCountWaves];
   const int c = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int pitch = sx + 1, cells = pitch * (sy + 1);
-  for (int i = tid; i < cells; i += kDirectThreads) s_diff[i] = 0;
+  for (int i = tid; i < cells; i += kCountThreads) s_diff[i] = 0;
   __syncthreads();
-  const uint32_t r1 = bounds[c + 1];
+  const int r0 = c * ranks, r1 = min(n, r0 + ranks);
   unsigned long long fine = 0;
-  for (uint32_t r = bounds[c] + tid; r < r1; r += kDirectThreads) {
+  for (int r = r0 + tid; r < r1; r += kCountThreads) {
     const uint2 rc = rect_rank[r];
     fine += rect_count(rc);
     const uint2 sr = rect_at(rc, kSuperShift);
@@ -971,48 +1060,52 @@ __global__ __launch_bounds__(kDirectThreads) void k_chunk_count(const uint32_t* 
   __syncthreads();
   if (tid == 0) {
     unsigned long long k = 0;
-    for (int w = 0; w < kDirectWaves; ++w) k += s_k[w];
-    if (k) atomicAdd(kfine, k);
+    for (int w = 0; w < kCountWaves; ++w) k += s_k[w];
+    kfine[c] = k;
   }
-  for (int y = wave; y < sy; y += kDirectWaves) wave_prefix_lds(s_diff + y * pitch, sx, 1, lane);
+  for (int y = wave; y < sy; y += kCountWaves) wave_prefix_lds(s_diff + y * pitch, sx, 1, lane);
   __syncthreads();
-  for (int x = wave; x < sx; x += kDirectWaves) wave_prefix_lds(s_diff + x, sy, pitch, lane);
+  for (int x = wave; x < sx; x += kCountWaves) wave_prefix_lds(s_diff + x, sy, pitch, lane);
   __syncthreads();
   uint32_t* const out = table + static_cast<size_t>(c) * sx * sy;
-  for (int y = wave; y < sy; y += kDirectWaves)
+  for (int y = wave; y < sy; y += kCountWaves)
     for (int x = lane; x < sx; x += 64) out[y * sx + x] = static_cast<uint32_t>(s_diff[y * pitch + x]);
 }
 
-// One workgroup (16 waves) per 64 columns (tiles or super tiles); wave w owns
-// a contiguous range of at most kDirectChunks / 16 chunks, whose counts it
-// holds in registers (one read of the table, all loads in flight at once).
-// table[c][t] becomes the entries of t in chunks before c; total[t] is t's
-// count.
-constexpr int kColPer = kDirectChunks / 16;
+// One workgroup per 16 super tiles: thread (g, x) = (tid / 16, tid % 16) owns
+// a contiguous 64th of the chunks of super tile x, whose counts it holds in
+// registers (one read of the table, all loads in flight at once); the 64
+// sums of a super tile are then scanned by one wave.  table[c][t] becomes the
+// entries of t in chunks before c; total[t] is t's count.  Bound by one round
+// trip to memory: a few hundred super tiles make only a handful of
+// workgroups, and 16 columns to each (64 bytes of a table row) take
+// 7.3 us for 977 chunks at 1M Gaussians, 64 columns 28.7 us.
+constexpr int kColPer = kDirectChunks / 64;
 __global__ __launch_bounds__(1024) void k_chunk_colscan(int C, int ntiles, uint32_t* __restrict__ table,
                                                         uint32_t* __restrict__ total) {
-  __shared__ uint32_t s_part[16][64];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 64 + lane;
-  const int per = (C + 15) / 16;   // at most kColPer (C <= kDirectChunks)
-  const int c0 = min(C, wave * per), c1 = min(C, c0 + per);
+  __shared__ uint32_t s_part[64][17];
+  const int g = threadIdx.x >> 4, x = threadIdx.x & 15;
+  const int t = blockIdx.x * 16 + x;
+  const int per = (C + 63) / 64;   // at most kColPer (C <= kDirectChunks)
+  const int c0 = min(C, g * per), c1 = min(C, c0 + per);
   uint32_t v[kColPer];
   uint32_t sum = 0;
 #pragma unroll
-  for (int k = 0; k < kColPer; ++k) {
-    v[k] = (t < ntiles && c0 + k < c1) ? table[static_cast<size_t>(c0 + k) * ntiles + t] : 0u;
-    sum += v[k];
-  }
-  s_part[wave][lane] = sum;
+  for (int k = 0; k < kColPer; ++k) v[k] = (t < ntiles && c0 + k < c1) ? table[static_cast<size_t>(c0 + k) * ntiles + t] : 0u;
+#pragma unroll
+  for (int k = 0; k < kColPer; ++k) sum += v[k];
+  s_part[g][x] = sum;
   __syncthreads();
-  uint32_t run = 0, all = 0;
-  for (int w = 0; w < 16; ++w) {
-    const uint32_t x = s_part[w][lane];
-    run += (w < wave) ? x : 0u;
-    all += x;
+  {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;   // wave w scans column w
+    const uint32_t p = s_part[lane][wave];
+    const uint32_t incl = static_cast<uint32_t>(wave_incl_scan(static_cast<int>(p)));
+    s_part[lane][wave] = incl - p;
+    if (lane == 63 && blockIdx.x * 16 + wave < ntiles) total[blockIdx.x * 16 + wave] = incl;
   }
+  __syncthreads();
   if (t >= ntiles) return;
-  if (wave == 0) total[t] = all;
+  uint32_t run = s_part[g][x];
 #pragma unroll
   for (int k = 0; k < kColPer; ++k) {
     if (c0 + k < c1) table[static_cast<size_t>(c0 + k) * ntiles + t] = run;
@@ -1047,82 +1140,85 @@ __device__ __forceinline__ unsigned long long block_exclusive_u64(unsigned long 
 }
 
 // start[t] = exclusive prefix of total over the tiles, ranges[t] = (start,
-// start + total), by one workgroup.  K = *kfine (the sum of the tile counts)
-// goes to rb[0] and, if given, k_dev[0]; *fits = whether the entries fit.  If
-// they do not fit in `capacity`, every range is written empty instead, so
-// that work queued on these lists before the caller learns of the overflow
-// (the no-wait call) reads nothing past the buffers.
+// start + total).  A workgroup takes 1024 tiles and adds up the totals before
+// them itself (read from L2, all loads in flight; 130 KB at most for a 4K
+// frame), so one launch serves any number of tiles.  K, the sum of kfine[0,
+// chunks) (the chunks' tile counts) or without chunks of the totals, goes to rb[0] and, if given,
+// k_dev[0] (and rb[1], the look-back flag, to k_dev[1]); *fits = whether the
+// entries fit.  If they do not fit in `capacity`, every range is written
+// empty instead, so that work queued on these lists before the caller learns
+// of the overflow (the no-wait call) reads nothing past the buffers.
 struct StartArgs {
   int ntiles;
   uint32_t* start;
   uint2* ranges;
   unsigned long long capacity;
+  int chunks;
   const unsigned long long* kfine;
   unsigned long long* rb;
   unsigned long long* k_dev;
   uint32_t* fits;
 };
-constexpr int kStartRegs = kDirectMaxTiles / 1024;   // a thread's totals, all loads in flight at once
 __global__ __launch_bounds__(1024) void k_tile_starts(const uint32_t* __restrict__ total, StartArgs a) {
   __shared__ unsigned long long s_w[16];
-  // the tile totals, then the tile starts: read and written tile by tile
-  // across the lanes (coalesced), scanned in runs of consecutive tiles
-  __shared__ uint32_t s_t[kDirectMaxTiles];
-  const int tid = threadIdx.x;
-  for (int t = tid; t < a.ntiles; t += 1024) s_t[t] = total[t];
-  __syncthreads();
-  const int per = (a.ntiles + 1023) / 1024;   // at most kStartRegs: direct_ok bounds the tiles
-  const int t0 = min(a.ntiles, tid * per), t1 = min(a.ntiles, t0 + per);
-  uint32_t v[kStartRegs];
-  unsigned long long sum = 0;
-#pragma unroll
-  for (int k = 0; k < kStartRegs; ++k) {
-    v[k] = t0 + k < t1 ? s_t[t0 + k] : 0u;
-    sum += v[k];
+  __shared__ unsigned long long s_pre[16], s_all[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int first = blockIdx.x * 1024, t = first + tid;
+  const uint32_t v = t < a.ntiles ? total[t] : 0u;
+  unsigned long long pre = 0, sum = 0;
+  for (int i = tid; i < a.chunks; i += 1024) sum += a.kfine[i];
+  const int upto = a.chunks ? first : a.ntiles;
+#pragma unroll 4
+  for (int i = tid; i < upto; i += 1024) {
+    const uint32_t x = total[i];
+    pre += i < first ? x : 0u;
+    sum += a.chunks ? 0u : x;
   }
+  for (int o = 32; o > 0; o >>= 1) {
+    pre += __shfl_xor(pre, o, 64);
+    sum += __shfl_xor(sum, o, 64);
+  }
+  if (lane == 0) { s_pre[wave] = pre; s_all[wave] = sum; }
   unsigned long long all;
-  unsigned long long run = block_exclusive_u64<1024>(sum, s_w, all);
-  const unsigned long long K = *a.kfine;
+  unsigned long long run = block_exclusive_u64<1024>(v, s_w, all);   // its barriers publish s_pre and s_all
+  unsigned long long K = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    run += s_pre[w];
+    K += s_all[w];
+  }
   // positions are 32-bit: a total beyond that does not fit either
   const bool fits = K <= min(a.capacity, 0xFFFFFFFFull);
-  if (tid == 0) {
+  if (blockIdx.x == 0 && tid == 0) {
     a.rb[0] = K;
-    if (a.k_dev) a.k_dev[0] = K;
+    if (a.k_dev) { a.k_dev[0] = K; a.k_dev[1] = a.rb[1]; }
     *a.fits = fits ? 1u : 0u;
   }
-  __syncthreads();   // every thread has read its totals
-#pragma unroll
-  for (int k = 0; k < kStartRegs; ++k) {
-    if (t0 + k < t1) s_t[t0 + k] = static_cast<uint32_t>(run);
-    run += v[k];
-  }
-  __syncthreads();
-  // tile t ends where tile t + 1 starts (the last one at the total)
-  for (int t = tid; t < a.ntiles; t += 1024) {
-    const uint32_t st = s_t[t];
-    const uint32_t en = t + 1 < a.ntiles ? s_t[t + 1] : static_cast<uint32_t>(all);
+  if (t < a.ntiles) {
+    const uint32_t st = static_cast<uint32_t>(run);
     a.start[t] = st;
-    a.ranges[t] = fits ? make_uint2(st, en) : make_uint2(0u, 0u);
+    a.ranges[t] = fits ? make_uint2(st, st + v) : make_uint2(0u, 0u);
   }
 }
 
 // Super tile s's run of the coarse list starts at start[s] (exclusive prefix
-// of the totals) and is cut into parts of kPart entries, numbered over the
+// of the totals) and is cut into parts of `part` entries, numbered over the
 // super tiles in turn: parts pbase[s] .. pbase[s+1]-1 (pbase[ns]: all parts).
 // A coarse list longer than its buffer (capacity) gives no parts: K is at
 // least as large, so the frame is reported as not fitting.
-__global__ __launch_bounds__(1024) void k_coarse_parts(int ns, const uint32_t* __restrict__ ctotal,
+__global__ __launch_bounds__(1024) void k_coarse_parts(int ns, int part, const uint32_t* __restrict__ ctotal,
                                                        uint32_t* __restrict__ cstart, unsigned long long capacity,
                                                        uint32_t* __restrict__ pbase) {
   __shared__ unsigned long long s_w[16];
   const int tid = threadIdx.x;
   const int per = (ns + 1023) / 1024;
   const int t0 = min(ns, tid * per), t1 = min(ns, t0 + per);
+  const uint32_t upart = static_cast<uint32_t>(part);
   unsigned long long sum = 0, psum = 0;
   for (int t = t0; t < t1; ++t) {
     const uint32_t v = ctotal[t];
     sum += v;
-    psum += (v + kPart - 1) / kPart;
+    psum += (v + upart - 1) / upart;
   }
   unsigned long long all, pall;
   unsigned long long run = block_exclusive_u64<1024>(sum, s_w, all);
@@ -1133,7 +1229,7 @@ __global__ __launch_bounds__(1024) void k_coarse_parts(int ns, const uint32_t* _
     cstart[t] = static_cast<uint32_t>(run);
     pbase[t] = fits ? static_cast<uint32_t>(prun) : 0u;
     run += v;
-    prun += (v + kPart - 1) / kPart;
+    prun += (v + upart - 1) / upart;
   }
   if (tid == 0) pbase[ns] = fits ? static_cast<uint32_t>(pall) : 0u;
 }
@@ -1261,7 +1357,7 @@ __device__ __forceinline__ void lds_barrier() {
 // writes the group's count into delta[t], which one pass over the super
 // tiles adds to the positions once every entry of the group is placed.
 // two workgroups per CU (8 waves per SIMD): at most 64 VGPRs
-__global__ __launch_bounds__(kDirectThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_emit_coarse(const uint32_t* __restrict__ bounds,
+__global__ __launch_bounds__(kDirectThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_emit_coarse(int n, int ranks,
                                                                 const uint32_t* __restrict__ order,
                                                                 const uint2* __restrict__ rect_rank,
                                                                 const uint32_t* __restrict__ table,
@@ -1282,8 +1378,8 @@ __global__ __launch_bounds__(kDirectThreads) __attribute__((amdgpu_waves_per_eu(
   uint16_t* const s_delta = reinterpret_cast<uint16_t*>(s_pos + ntiles);
   const int c = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const uint32_t R0 = bounds[c], R1 = bounds[c + 1];
-  if (R0 >= R1) return;
+  const uint32_t R0 = static_cast<uint32_t>(c) * static_cast<uint32_t>(ranks);
+  const uint32_t R1 = min(static_cast<uint32_t>(n), R0 + static_cast<uint32_t>(ranks));
   const uint32_t* const tab = table + static_cast<size_t>(c) * ntiles;
   for (int t = tid; t < ntiles; t += kDirectThreads) {
     s_pos[t] = start[t] + tab[t];
@@ -1419,6 +1515,7 @@ __device__ __forceinline__ uint64_t fine_tile_mask(const FineMasks& m, int lane)
 struct Part {
   uint32_t s, lo, hi;
 };
+template <int PART>
 __device__ __forceinline__ Part find_part(const uint32_t* __restrict__ s_pb, int ns, uint32_t p,
                                           const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ ctotal) {
   int a = 0, b = ns - 1;
@@ -1427,16 +1524,17 @@ __device__ __forceinline__ Part find_part(const uint32_t* __restrict__ s_pb, int
     if (s_pb[mid] <= p) a = mid; else b = mid - 1;
   }
   const uint32_t s = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(a));
-  const uint32_t base = cstart[s], lo = base + (p - s_pb[s]) * static_cast<uint32_t>(kPart);
-  return Part{s, lo, min(lo + static_cast<uint32_t>(kPart), base + ctotal[s])};
+  const uint32_t base = cstart[s], lo = base + (p - s_pb[s]) * static_cast<uint32_t>(PART);
+  return Part{s, lo, min(lo + static_cast<uint32_t>(PART), base + ctotal[s])};
 }
 
-// A part's coarse entries, kPartSteps per thread: step j of wave w holds
+// A part's coarse entries, STEPS per thread: step j of wave w holds
 // entries lo + 256 j + 64 w + lane (0 past hi), all loads in flight at once.
+template <int STEPS>
 __device__ __forceinline__ void load_part(const unsigned long long* __restrict__ coarse, const Part& pt, int wave,
-                                          int lane, unsigned long long (&v)[kPartSteps]) {
+                                          int lane, unsigned long long (&v)[STEPS]) {
 #pragma unroll
-  for (int j = 0; j < kPartSteps; ++j) {
+  for (int j = 0; j < STEPS; ++j) {
     const uint32_t e = pt.lo + static_cast<uint32_t>(j * kFineThreads + wave * 64 + lane);
     v[j] = e < pt.hi ? coarse[e] : 0ull;
   }
@@ -1444,11 +1542,13 @@ __device__ __forceinline__ void load_part(const unsigned long long* __restrict__
 
 // Per part p: ftab[p][t] = the entries of its super tile's tile t in the
 // part.  The workgroups loop over the parts.
+template <int PART>
 __global__ __launch_bounds__(kFineThreads) void k_fine_count(const uint32_t* __restrict__ pbase, int ns,
                                                              const uint32_t* __restrict__ cstart,
                                                              const uint32_t* __restrict__ ctotal,
                                                              const unsigned long long* __restrict__ coarse,
                                                              uint32_t* __restrict__ ftab) {
+  constexpr int kPartSteps = PART / kFineThreads;
   extern __shared__ uint32_t s_pb[];   // pbase[0..ns]
   __shared__ uint32_t s_sum[kFineWaves][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1456,7 +1556,7 @@ __global__ __launch_bounds__(kFineThreads) void k_fine_count(const uint32_t* __r
   __syncthreads();
   const uint32_t np = s_pb[ns];
   for (uint32_t p = blockIdx.x; p < np; p += gridDim.x) {
-    const Part pt = find_part(s_pb, ns, p, cstart, ctotal);
+    const Part pt = find_part<PART>(s_pb, ns, p, cstart, ctotal);
     unsigned long long v[kPartSteps];
     load_part(coarse, pt, wave, lane, v);
     uint32_t acc = 0;
@@ -1480,16 +1580,19 @@ __global__ __launch_bounds__(kFineThreads) void k_fine_count(const uint32_t* __r
 
 // Per super tile s (one workgroup): the counts ftab[p][t] of its parts become
 // exclusive prefixes over the parts, and each tile's total goes to total[]
-// (lanes of tiles outside the frame write nothing).  Wave w takes a quarter
+// (lanes of tiles outside the frame write nothing).  Wave w takes a sixteenth
 // of the parts, lane t the tile; the rows are read kScanBatch at a time, all
-// loads in flight together.
+// loads in flight together.  (A small frame's few super tiles hold all the
+// parts: 8.9 us against 17.5 with four waves at 500k Gaussians on 13 x 9
+// tiles.)
 constexpr int kScanBatch = 8;
-__global__ __launch_bounds__(256) void k_fine_scan(const uint32_t* __restrict__ pbase, uint32_t* __restrict__ ftab,
+constexpr int kScanWaves = 16;
+__global__ __launch_bounds__(64 * kScanWaves) void k_fine_scan(const uint32_t* __restrict__ pbase, uint32_t* __restrict__ ftab,
                                                    int sx, int tiles_x, int tiles_y, uint32_t* __restrict__ total) {
-  __shared__ uint32_t s_sum[4][64];
+  __shared__ uint32_t s_sum[kScanWaves][64];
   const int s = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t p0 = pbase[s], p1 = pbase[s + 1];
-  const uint32_t per = (p1 - p0 + 3u) / 4u;
+  const uint32_t per = (p1 - p0 + kScanWaves - 1u) / kScanWaves;
   const uint32_t a = min(p1, p0 + static_cast<uint32_t>(wave) * per), b = min(p1, a + per);
   uint32_t* const col = ftab + lane;
   uint32_t sum = 0;
@@ -1504,7 +1607,7 @@ __global__ __launch_bounds__(256) void k_fine_scan(const uint32_t* __restrict__ 
   __syncthreads();
   uint32_t run = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < kScanWaves; ++w) {
     const uint32_t x = s_sum[w][lane];
     run += (w < wave) ? x : 0u;
     all += x;
@@ -1531,6 +1634,7 @@ __global__ __launch_bounds__(256) void k_fine_scan(const uint32_t* __restrict__ 
 // offsets, and then the 64 tiles go out in turn, one store each (exec = the
 // tile's mask).  Nothing is written unless every entry fits (*fits, from
 // k_tile_starts): then every position is below K <= capacity.
+template <int PART>
 __global__ __launch_bounds__(kFineThreads) void k_fine_emit(const uint32_t* __restrict__ pbase, int ns,
                                                             const uint32_t* __restrict__ cstart,
                                                             const uint32_t* __restrict__ ctotal,
@@ -1539,6 +1643,7 @@ __global__ __launch_bounds__(kFineThreads) void k_fine_emit(const uint32_t* __re
                                                             const uint32_t* __restrict__ start, int sx, int tiles_x,
                                                             int tiles_y, const uint32_t* __restrict__ fits,
                                                             uint32_t* __restrict__ point_list) {
+  constexpr int kPartSteps = PART / kFineThreads;
   extern __shared__ uint32_t s_pb[];   // pbase[0..ns]
   __shared__ uint32_t s_cnt[2][kFineWaves][64];   // two steps in flight: one barrier per step
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1548,7 +1653,7 @@ __global__ __launch_bounds__(kFineThreads) void k_fine_emit(const uint32_t* __re
   const uint32_t np = s_pb[ns];
   int buf = 0;
   for (uint32_t p = blockIdx.x; p < np; p += gridDim.x) {
-    const Part pt = find_part(s_pb, ns, p, cstart, ctotal);
+    const Part pt = find_part<PART>(s_pb, ns, p, cstart, ctotal);
     unsigned long long v[kPartSteps];
     load_part(coarse, pt, wave, lane, v);
     const int tx = static_cast<int>(pt.s % static_cast<uint32_t>(sx)) * kSuper + (lane & (kSuper - 1));
@@ -1601,18 +1706,18 @@ struct BinWs {
   uint32_t* hist;
   ScanWs scan;
   OsWs os;                        // depth sort state
-  uint32_t* zero;                 // its digit counts, K, the error flag and kfine, cleared by k_depth_keys
+  uint32_t* zero;                 // its digit counts, K and the error flag, cleared by k_depth_keys
   unsigned long long* readback;   // [0] K, [1] the error flag
-  unsigned long long* kfine;      // direct emission: the tile counts' sum
-  // direct emission: chunk bounds, chunk x super-tile table, super-tile
-  // totals and starts, tile totals and starts, the parts, per part x tile
-  // counts, and the coarse list
-  uint32_t *bounds, *table, *ctotal, *cstart, *total, *start;
+  unsigned long long* kfine;      // direct emission: the tile counts' sum per chunk
+  // direct emission: chunk x super-tile table, super-tile totals and starts,
+  // tile totals and starts (and quarter counts, small frames), the parts, per
+  // part x tile counts, and the coarse list
+  uint32_t *table, *ctotal, *cstart, *total, *start, *qcnt;
   uint32_t *pbase, *ftab, *fits;
   unsigned long long* coarse;
 };
 
-constexpr int kZeroWords = kOsMaxPasses * 256 + 6;   // digit counts, K, error flag, kfine
+constexpr int kZeroWords = kOsMaxPasses * 256 + 4;   // digit counts, K, error flag
 
 static BinWs carve_bin(void* ws, int64_t n, int64_t cap, int tiles_x, int tiles_y, size_t* used) {
   Carver c(ws);
@@ -1622,37 +1727,35 @@ static BinWs carve_bin(void* ws, int64_t n, int64_t cap, int tiles_x, int tiles_
   b.dk0 = c.take<uint32_t>(N); b.dv0 = c.take<uint32_t>(N);
   b.dk1 = c.take<uint32_t>(N); b.dv1 = c.take<uint32_t>(N);
   b.order = c.take<uint32_t>(N);
-  b.cnt = c.take<uint32_t>(N); b.offs = c.take<uint32_t>(N);
   b.rect = c.take<uint2>(N); b.rect_rank = c.take<uint2>(N);
-  if (direct) {
-    b.scan.sums = c.take<uint32_t>(scan_ws_words(static_cast<int64_t>(N)));
-  } else {
+  if (!direct) {
+    b.cnt = c.take<uint32_t>(N); b.offs = c.take<uint32_t>(N);
     b.ek0 = c.take<uint32_t>(C); b.ek1 = c.take<uint32_t>(C); b.ev1 = c.take<uint32_t>(C);
     const size_t hist_words = 256 * static_cast<size_t>(ceil_div(std::max<int64_t>(cap, 1), kRsThreads * kRsItemsK));
     const int64_t maxn = std::max<int64_t>(std::max<int64_t>(n, cap), 1);
     b.hist = c.take<uint32_t>(hist_words);
     b.scan.sums = c.take<uint32_t>(scan_ws_words(std::max<int64_t>(static_cast<int64_t>(hist_words), maxn)));
   }
-  // cleared by k_depth_keys: the onesweep digit counts, then K, the error flag and kfine
+  // cleared by k_depth_keys: the onesweep digit counts, then K and the error flag
   b.zero = c.take<uint32_t>(kZeroWords);
   b.readback = reinterpret_cast<unsigned long long*>(b.zero + kOsMaxPasses * 256);
-  b.kfine = b.readback + 2;
   b.scan.total = b.readback;
   b.os.ghist = b.zero;
   b.os.err = reinterpret_cast<uint32_t*>(b.readback + 1);
-  b.os.state = c.take<uint32_t>(os_state_words(n, kOsThreads * kOsItemsN, kOsMaxPasses));
+  b.os.state = c.take<uint32_t>(os_state_words(n, kOsThreads * (n <= kOsSmallN ? kOsItemsSmall : kOsItemsN), kOsMaxPasses));
   b.os.counters = c.take<uint32_t>(kOsMaxPasses);
   if (direct) {
     const size_t nt = static_cast<size_t>(tiles_x) * tiles_y;
     const int ns = super_dim(tiles_x) * super_dim(tiles_y);
-    const size_t chunks = static_cast<size_t>(direct_max_chunks(cap));
-    const size_t parts = static_cast<size_t>(direct_max_parts(cap, ns));
-    b.bounds = c.take<uint32_t>(chunks + 1);
+    const size_t chunks = static_cast<size_t>(direct_chunks(n));
+    const size_t parts = static_cast<size_t>(direct_max_parts(n, cap, ns));
     b.table = c.take<uint32_t>(chunks * ns);
+    b.kfine = c.take<unsigned long long>(chunks);
     b.ctotal = c.take<uint32_t>(ns);
     b.cstart = c.take<uint32_t>(ns);
     b.total = c.take<uint32_t>(nt);
     b.start = c.take<uint32_t>(nt);
+    b.qcnt = c.take<uint32_t>(small_frame(n, static_cast<int64_t>(nt)) ? 4 * nt : 1);
     b.pbase = c.take<uint32_t>(ns + 1);
     b.fits = c.take<uint32_t>(1);
     b.ftab = c.take<uint32_t>(parts * 64);
@@ -1668,7 +1771,11 @@ size_t binsort_workspace(int64_t n, int64_t capacity, int tiles_x, int tiles_y) 
   return used;
 }
 
-bool binsort_direct(int tiles_x, int tiles_y) { return direct_ok(tiles_x, tiles_y); }
+// The no-wait call takes frames of at most 16,384 tiles (its documented
+// limit); the waiting one emits directly wherever the tables fit.
+bool binsort_direct(int tiles_x, int tiles_y) {
+  return static_cast<int64_t>(tiles_x) * tiles_y <= 16384 && direct_ok(tiles_x, tiles_y);
+}
 
 __global__ void k_put_zero_k(unsigned long long* __restrict__ k_dev) {
   if (threadIdx.x < 2) k_dev[threadIdx.x] = 0ull;
@@ -1685,54 +1792,70 @@ gs_status run_bin_sort(int64_t n64, const gs_projected& proj, const DevCam& cam,
   gs_status st;
   int64_t K = 0;
   if (n > 0) {
-    const unsigned g = static_cast<unsigned>(ceil_div(n, 256));
-    { TimedLaunch gs_tl("k_depth_keys", s); k_depth_keys<<<g, 256, 0, s>>>(n, proj.depth, reinterpret_cast<const float4*>(proj.records), proj.radius,
-                                   cam.tiles_x, cam.tiles_y, b.dk0, b.dv0, b.rect, b.zero, kZeroWords); }
-    if ((st = check_launch("k_depth_keys")) != GS_OK) return st;
-    // the terminal pass also gathers each rank's rectangle and its count of
-    // super tiles (direct emission) or tiles
-    if ((st = onesweep_sort_pairs<kOsItemsN, kOsThreads>(b.dk0, b.dv0, b.dk1, b.dv1, n, 32, b.os, s, b.order, b.rect,
-                                             b.rect_rank, b.cnt, b.table ? kSuperShift : 0)) != GS_OK)
-      return st;
+    if (n <= kSmallN && b.table) {
+      { TimedLaunch gs_tl("k_small_rank", s); k_small_rank<<<static_cast<unsigned>(ceil_div(n, 64)), kSmallRankThreads, 0, s>>>(
+          n, proj.depth, reinterpret_cast<const float4*>(proj.records), proj.radius, cam.tiles_x, cam.tiles_y, b.order,
+          b.rect_rank, b.zero, kZeroWords); }
+      if ((st = check_launch("k_small_rank")) != GS_OK) return st;
+    } else {
+      { TimedLaunch gs_tl("k_depth_keys", s); k_depth_keys<<<static_cast<unsigned>(ceil_div(n, 256)), 256, 0, s>>>(
+          n, proj.depth, reinterpret_cast<const float4*>(proj.records), proj.radius, cam.tiles_x, cam.tiles_y, b.dk0, b.dv0,
+          b.rect, b.zero, kZeroWords); }
+      if ((st = check_launch("k_depth_keys")) != GS_OK) return st;
+      // the terminal pass also gathers each rank's rectangle (and, for the
+      // radix tile sort, its count of tiles)
+      const auto sort = n <= kOsSmallN ? onesweep_sort_pairs<kOsItemsSmall, kOsThreads> : onesweep_sort_pairs<kOsItemsN, kOsThreads>;
+      if ((st = sort(b.dk0, b.dv0, b.dk1, b.dv1, n, 32, b.os, s, b.order, b.rect, b.rect_rank,
+                     b.table ? nullptr : b.cnt)) != GS_OK)
+        return st;
+    }
     const uint32_t* order = b.order;
     unsigned long long rb[2] = {0ull, 0ull};
     if (b.table) {
-      // direct emission, sized on the device from the scanned coarse total:
-      // no host wait between the depth sort and the placement; K (and the
-      // look-back flag) are read once at the end
+      // direct emission: no host wait between the depth sort and the
+      // placement; K (and the look-back flag) are read once at the end
       const int tx = cam.tiles_x, ty = cam.tiles_y;
-      const int sx = super_dim(tx), sy = super_dim(ty), ns = sx * sy;
-      const int cmax = static_cast<int>(direct_max_chunks(capacity));
-      const unsigned fgrid = static_cast<unsigned>(std::min<int64_t>(direct_max_parts(capacity, ns), kFineGrid));
-      const uint32_t cap32 = static_cast<uint32_t>(std::min<int64_t>(capacity, UINT32_MAX));
-      if ((st = device_chunk_bounds(b.cnt, n, b.scan,
-                                    ChunkArgs{b.bounds, cmax, static_cast<unsigned long long>(kDirectMinEntries),
-                                              static_cast<unsigned long long>(kDirectChunks), k_dev},
-                                    s)) != GS_OK)
-        return st;
-      { TimedLaunch gs_tl("k_chunk_count", s); k_chunk_count<<<cmax, kDirectThreads, sizeof(int) * (sx + 1) * (sy + 1), s>>>(
-          b.bounds, b.rect_rank, sx, sy, b.table, b.kfine); }
-      if ((st = check_launch("k_chunk_count")) != GS_OK) return st;
-      { TimedLaunch gs_tl("k_chunk_colscan", s); k_chunk_colscan<<<static_cast<unsigned>(ceil_div(ns, 64)), 1024, 0, s>>>(cmax, ns, b.table, b.ctotal); }
-      if ((st = check_launch("k_chunk_colscan")) != GS_OK) return st;
-      { TimedLaunch gs_tl("k_coarse_parts", s); k_coarse_parts<<<1, 1024, 0, s>>>(ns, b.ctotal, b.cstart, static_cast<unsigned long long>(capacity),
-                                                                                  b.pbase); }
-      if ((st = check_launch("k_coarse_parts")) != GS_OK) return st;
-      { TimedLaunch gs_tl("k_emit_coarse", s); k_emit_coarse<<<cmax, kDirectThreads, emit_dyn_lds(sx, sy), s>>>(
-          b.bounds, order, b.rect_rank, b.table, b.cstart, sx, sy, b.coarse, cap32); }
-      if ((st = check_launch("k_emit_coarse")) != GS_OK) return st;
-      const size_t pb_lds = sizeof(uint32_t) * (static_cast<size_t>(ns) + 1);
-      { TimedLaunch gs_tl("k_fine_count", s); k_fine_count<<<fgrid, kFineThreads, pb_lds, s>>>(b.pbase, ns, b.cstart, b.ctotal, b.coarse, b.ftab); }
-      if ((st = check_launch("k_fine_count")) != GS_OK) return st;
-      { TimedLaunch gs_tl("k_fine_scan", s); k_fine_scan<<<ns, 256, 0, s>>>(b.pbase, b.ftab, sx, tx, ty, b.total); }
-      if ((st = check_launch("k_fine_scan")) != GS_OK) return st;
+      const bool small = small_frame(n, ntiles);
       const StartArgs sa{ntiles, b.start, reinterpret_cast<uint2*>(ranges), static_cast<unsigned long long>(capacity),
-                         b.kfine, b.readback, k_dev, b.fits};
-      { TimedLaunch gs_tl("k_tile_starts", s); k_tile_starts<<<1, 1024, 0, s>>>(b.total, sa); }
-      if ((st = check_launch("k_tile_starts")) != GS_OK) return st;
-      { TimedLaunch gs_tl("k_fine_emit", s); k_fine_emit<<<fgrid, kFineThreads, pb_lds, s>>>(
-          b.pbase, ns, b.cstart, b.ctotal, b.coarse, b.ftab, b.start, sx, tx, ty, b.fits, point_list); }
-      if ((st = check_launch("k_fine_emit")) != GS_OK) return st;
+                         small ? 0 : direct_chunks(n), b.kfine, b.readback, k_dev, b.fits};
+      const unsigned sgrid = static_cast<unsigned>(ceil_div(ntiles, 1024));
+      if (small) {
+        { TimedLaunch gs_tl("k_small_count", s); k_small_count<<<ntiles, 256, 0, s>>>(n, b.rect_rank, tx, b.qcnt, b.total); }
+        if ((st = check_launch("k_small_count")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_tile_starts", s); k_tile_starts<<<sgrid, 1024, 0, s>>>(b.total, sa); }
+        if ((st = check_launch("k_tile_starts")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_small_emit", s); k_small_emit<<<ntiles, 256, 0, s>>>(n, order, b.rect_rank, tx, b.qcnt, b.start,
+                                                                                    b.fits, point_list); }
+        if ((st = check_launch("k_small_emit")) != GS_OK) return st;
+      } else {
+        const int sx = super_dim(tx), sy = super_dim(ty), ns = sx * sy;
+        const int ranks = direct_ranks(n), chunks = direct_chunks(n);
+        const unsigned fgrid = static_cast<unsigned>(std::min<int64_t>(direct_max_parts(n, capacity, ns), kFineGrid));
+        const uint32_t cap32 = static_cast<uint32_t>(std::min<int64_t>(capacity, UINT32_MAX));
+        { TimedLaunch gs_tl("k_chunk_count", s); k_chunk_count<<<chunks, kCountThreads, sizeof(int) * (sx + 1) * (sy + 1), s>>>(
+            n, ranks, b.rect_rank, sx, sy, b.table, b.kfine); }
+        if ((st = check_launch("k_chunk_count")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_chunk_colscan", s); k_chunk_colscan<<<static_cast<unsigned>(ceil_div(ns, 16)), 1024, 0, s>>>(chunks, ns, b.table, b.ctotal); }
+        if ((st = check_launch("k_chunk_colscan")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_coarse_parts", s); k_coarse_parts<<<1, 1024, 0, s>>>(ns, part_entries(n), b.ctotal, b.cstart, static_cast<unsigned long long>(capacity),
+                                                                                    b.pbase); }
+        if ((st = check_launch("k_coarse_parts")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_emit_coarse", s); k_emit_coarse<<<chunks, kDirectThreads, emit_dyn_lds(sx, sy), s>>>(
+            n, ranks, order, b.rect_rank, b.table, b.cstart, sx, sy, b.coarse, cap32); }
+        if ((st = check_launch("k_emit_coarse")) != GS_OK) return st;
+        const size_t pb_lds = sizeof(uint32_t) * (static_cast<size_t>(ns) + 1);
+        const bool fine = part_entries(n) == kPartSmall;
+        { TimedLaunch gs_tl("k_fine_count", s); (fine ? k_fine_count<kPartSmall> : k_fine_count<kPart>)<<<fgrid, kFineThreads, pb_lds, s>>>(
+            b.pbase, ns, b.cstart, b.ctotal, b.coarse, b.ftab); }
+        if ((st = check_launch("k_fine_count")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_fine_scan", s); k_fine_scan<<<ns, 64 * kScanWaves, 0, s>>>(b.pbase, b.ftab, sx, tx, ty, b.total); }
+        if ((st = check_launch("k_fine_scan")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_tile_starts", s); k_tile_starts<<<sgrid, 1024, 0, s>>>(b.total, sa); }
+        if ((st = check_launch("k_tile_starts")) != GS_OK) return st;
+        { TimedLaunch gs_tl("k_fine_emit", s); (fine ? k_fine_emit<kPartSmall> : k_fine_emit<kPart>)<<<fgrid, kFineThreads, pb_lds, s>>>(
+            b.pbase, ns, b.cstart, b.ctotal, b.coarse, b.ftab, b.start, sx, tx, ty, b.fits, point_list); }
+        if ((st = check_launch("k_fine_emit")) != GS_OK) return st;
+      }
       if (k_dev) return GS_OK;   // the caller checks K and the flag later
     } else if ((st = device_exclusive_scan(b.cnt, b.offs, n, b.scan, s)) != GS_OK) {
       return st;

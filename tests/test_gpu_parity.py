@@ -598,6 +598,53 @@ def test_bin_sort_wide_frame_fallback(gs, width):
     say(f"  K={k} bit-exact")
 
 
+@pytest.mark.parametrize("n,width,height,quantised", [
+    (1, 16, 16, False), (63, 100, 70, False), (64, 128, 128, True), (65, 33, 17, True), (257, 130, 250, True),
+    (4097, 640, 479, True),          # small frames: ranks by counting, each tile walks the ranks
+    (16384, 1024, 512, True),        # the largest work of that form (n x tiles = 2^25)
+    (16384, 1040, 512, True),        # just above: counted ranks, chunked emission
+    (16385, 800, 600, True),         # the radix depth sort
+    (262144, 300, 200, True), (262145, 300, 200, True),   # finer and coarser sort chunks and parts
+    (65600, 900, 700, True),         # chunks of more than 64 ranks
+    (20000, 4096, 4112, False),      # 65,792 tiles
+    (3000, 12000, 12000, False),     # 8,836 super tiles: the tables do not fit, the radix tile sort
+])
+def test_bin_sort_routes(gs, n, width, height, quantised):
+    """Every route of the binning at the sizes where it changes, with depth
+    ties (quantised), gives the oracle's lists bit for bit; so does the no-wait
+    call where it is taken (at most 16,384 tiles)."""
+    scene = scenes.uniform_scene(n, 97, log_scale_mean=-4.2, log_scale_std=0.5, sh_degree=0)
+    if quantised:
+        means = scene.means.copy()
+        means[2] = np.round(means[2] * 8) / np.float32(8)
+        scene = dataclasses.replace(scene, means=means)
+    cam = scenes.front_camera(width, height, 3.0, 60.0)
+    p, g, out = gpu_project(gs, scene, cam)
+    h = proj_host(out)
+    k, pl, ranges = gpu_bin_sort(gs, scene.n, out, cam)
+    o_pl, o_ranges, _, _ = oracle.bin_sort(h["u"], h["v"], h["radius"], h["depth"], cam.width, cam.height)
+    assert k == len(o_pl)
+    assert np.array_equal(pl[:k].cpu().numpy().view(np.uint32), o_pl), "point_list"
+    assert np.array_equal(ranges.cpu().numpy().view(np.uint32), o_ranges), "ranges"
+    cs = gs.camera_struct(cam)
+    cap = max(k, 1)
+    ws = torch.empty(gs.bin_sort_workspace(n, cap, cs), dtype=torch.uint8, device=DEV)
+    pl2, rg2 = torch.empty(cap, dtype=torch.int32, device=DEV), torch.empty_like(ranges)
+    k_dev = torch.empty(2, dtype=torch.int64, device=DEV)
+    if gs.n_tiles(cs) > 16384:
+        with pytest.raises(gs.GsError) as ei:
+            gs.bin_sort_async(n, out, cs, ws, pl2, rg2, k_dev)
+        assert ei.value.status == gs.GS_ERR_UNSUPPORTED
+        return
+    gs.bin_sort_async(n, out, cs, ws, pl2, rg2, k_dev)
+    assert k_dev.tolist() == [k, 0]
+    assert torch.equal(rg2, ranges) and np.array_equal(pl2[:k].cpu().numpy().view(np.uint32), o_pl)
+    if k > 1:   # too small a capacity: reported, every range empty
+        ws = torch.empty(gs.bin_sort_workspace(n, k - 1, cs), dtype=torch.uint8, device=DEV)
+        gs.bin_sort_async(n, out, cs, ws, pl2[:k - 1], rg2, k_dev)
+        assert k_dev.tolist() == [k, 0] and not rg2.any()
+
+
 def _slab_scene(n_small=20000, n_big=700, seed=93):
     """Small Gaussians everywhere plus large ones in a thin depth slab: rank
     groups inside the slab touch thousands of tiles, the others a few hundred."""
