@@ -1335,14 +1335,6 @@ __device__ __forceinline__ void place_entry(int rw, uint32_t e, int lo, const ui
   if (later == 0ull) s_delta[t] = static_cast<uint16_t>(within + 1u);   // at most 256
 }
 
-// A workgroup barrier that orders LDS only: the waves' outstanding global
-// stores need not drain before it (nothing in the workgroup reads them).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Coarse emission over the sx x sy super tiles (tiles_x, tiles_y below).
 // Groups of 256 ranks.  Waves 0-3 hold the group's ranks (64 each, a
 // rank-wave), loaded while the group before was placed, and build their

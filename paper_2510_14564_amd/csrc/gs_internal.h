@@ -42,14 +42,14 @@ gs_status validate_camera(const gs_camera* cam);
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Transmittance checkpoint buffer for K entries over `ntiles` tiles: the
-// checkpoints, then the forward's tile plan, then each tile's work count
-// (largest n_contrib of its pixels), which the backward plans from, then the
-// forward's per-batch colour sums (three planes laid out like the checkpoints).
+// checkpoints, then the forward's tile plan, then each tile quadrant's work
+// count (largest n_contrib of its pixels), which the backward plans from, then
+// the forward's per-batch colour sums (three planes laid out like the checkpoints).
 inline size_t ckpt_core_floats(int64_t k, int64_t ntiles) { return static_cast<size_t>(k / 256 + ntiles + 1) * 256; }
 inline size_t ckpt_floats(int64_t k, int64_t ntiles) {
-  // plan: 16-value header + one entry per tile; work counts: one per tile;
+  // plan: 16-value header + one entry per tile; work counts: four per tile;
   // then the per-batch colour sums, three planes of the checkpoint layout
-  return 4 * ckpt_core_floats(k, ntiles) + 16 + 2 * static_cast<size_t>(ntiles);
+  return 4 * ckpt_core_floats(k, ntiles) + 16 + 5 * static_cast<size_t>(ntiles);
 }
 
 // Aligned carve-out of a caller-supplied workspace.
@@ -92,6 +92,12 @@ __device__ __forceinline__ int tile_rect(float u, float v, int r, int tx, int ty
   return (x1 - x0 + 1) * (y1 - y0 + 1);
 }
 
+// A tile's work count: the largest of its quadrants'.
+__device__ __forceinline__ uint32_t tile_work_of(const uint32_t* __restrict__ work, int tile) {
+  const uint32_t* const w = work + 4 * static_cast<int64_t>(tile);
+  return max(max(w[0], w[1]), max(w[2], w[3]));
+}
+
 // Map a linear block index to a work index so that consecutive work items land
 // on the same XCD (blocks are dispatched round-robin over the 8 XCDs).
 __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
@@ -121,6 +127,14 @@ __device__ __forceinline__ global_ptr<T> soa_row(T* base, int k, int64_t n) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
   const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
   return reinterpret_cast<global_ptr<T>>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// A workgroup barrier that orders LDS only: the waves' outstanding global
+// stores need not drain before it (nothing in the workgroup reads them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Per-Gaussian gradient accumulator rows of the compositing backward (atomic

@@ -123,8 +123,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(int ntiles, const ui
 
 // Backward work items: every batch of 256 list entries that some pixel of
 // the tile walks becomes its own workgroup, (tile, batch) in tile order.  A
-// tile's walk length is min(list length, largest n_contrib) -- the count the
-// forward left in `work`.  Tiles with a count of at most light_max go to the
+// tile's walk length is min(list length, largest n_contrib) -- the counts the
+// forward left in `work`, four per tile.  Tiles with a count of at most light_max go to the
 // light list instead (a plan with H = M = 0), or nowhere when light is NULL
 // (with light_max = 0: the tiles whose pixels blend nothing).
 // items: [0] item count, from kPlanHeader pairs (tile, batch).
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_batch_plan(int ntiles, const u
 #pragma unroll
     for (int k = 0; k < kPlanRegs; ++k) {
       rg[k] = t0 + k < t1 ? ranges[t0 + k] : make_uint2(0u, 0u);
-      wk[k] = t0 + k < t1 ? work[t0 + k] : 0u;
+      wk[k] = t0 + k < t1 ? tile_work_of(work, t0 + k) : 0u;
     }
 #pragma unroll
     for (int k = 0; k < kPlanRegs; ++k) {
@@ -174,8 +174,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_batch_plan(int ntiles, const u
     }
   } else {
     for (int t = t0; t < t1; ++t) {
-      c[0] += batches_of(ranges[t], work[t]);
-      c[1] += is_light(work[t]) ? 1u : 0u;
+      c[0] += batches_of(ranges[t], tile_work_of(work, t));
+      c[1] += is_light(tile_work_of(work, t)) ? 1u : 0u;
     }
   }
   uint32_t ex[2], tot[2];
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_batch_plan(int ntiles, const u
     for (int k = 0; k < kPlanRegs; ++k)
       if (t0 + k < t1) put(t0 + k, nbr[k], lgt[k]);
   } else {
-    for (int t = t0; t < t1; ++t) put(t, batches_of(ranges[t], work[t]), is_light(work[t]));
+    for (int t = t0; t < t1; ++t) put(t, batches_of(ranges[t], tile_work_of(work, t)), is_light(tile_work_of(work, t)));
   }
   if (tid == 0) {
     items[0] = static_cast<int32_t>(tot[0]);

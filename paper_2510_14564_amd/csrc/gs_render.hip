@@ -12,7 +12,8 @@
 // reads them back as broadcasts.  The per-pair body is branch-free; a wave
 // leaves a batch as soon as all its lanes are done (ballot), and the workgroup
 // leaves the tile when all 256 pixels are done.  Tiles are mapped so that
-// neighbouring tiles run on the same XCD and share its L2.
+// neighbouring tiles run on the same XCD and share its L2.  Frames of few
+// tiles take a forward that spreads each tile over four CUs.
 //
 // This file is compiled with -ffp-contract=off: the forward and the backward
 // evaluate alpha through the same inline function with explicit fmaf, so the
@@ -84,15 +85,35 @@ __device__ __forceinline__ float conic_min_rect(float A, float B, float C, float
   return best;
 }
 
-// Quadrants of the tile whose pixel centres can reach alpha >= 1/255 (bit w =
-// quadrant of wave w): first the record's alpha-support box, then the exact
-// support ellipse q(d) <= rho^2 = 2 ln(255 o) against each remaining
-// quadrant's rectangle of pixel centres.  A wave whose bit is clear would skip
-// the entry at every pixel anyway.  The ellipse test takes twice the box's
-// slack (rho^2 x 1.04 + 4e-4, the rectangle widened by the box's 1e-3 px +
-// 1e-6 |u|), covering the FP32 error of both its own evaluation and the
-// per-pixel one for footprints with condition number up to 1e5 (larger ones
-// have an unbounded box and keep their box mask).
+// Quadrants of the tile with a pixel centre that can reach alpha >= 1/255
+// (bit w = quadrant of wave w): first the record's alpha-support box, then the
+// exact support ellipse q(d) <= rho^2 = 2 ln(255 o) against each remaining
+// quadrant's rectangle of pixel centres (xa, xb, ya, yb) = rect(k).  A wave
+// whose bit is clear would skip the entry at every pixel anyway.  The
+// ellipse test takes twice the box's slack (rho^2 x 1.04 + 4e-4, the
+// rectangle widened by the box's 1e-3 px + 1e-6 |u|), covering the FP32 error
+// of both its own evaluation and the per-pixel one for footprints with
+// condition number up to 1e5 (larger ones have an unbounded box and keep
+// their box mask).
+template <class Rect>
+__device__ __forceinline__ uint32_t ellipse_mask(uint32_t box, const float4& r0, const float4& r1, const float4& r2,
+                                                 Rect rect) {
+  if (box == 0u || !(r2.z < 1.0e30f)) return box;
+  const float u = r0.x, v = r0.y, A = r0.z, B = r0.w, C = r1.x;
+  const float iA = 1.0f / A, iC = 1.0f / C;
+  const float rho2 = (2.0f * 1.04f) * logf(255.0f * r1.y) + 4e-4f;
+  const float dl = 1e-3f + 1e-6f * fmaxf(fabsf(u), fabsf(v));
+  uint32_t m = 0u;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (!((box >> k) & 1u)) continue;
+    const float4 b = rect(k);
+    if (conic_min_rect(A, B, C, iA, iC, b.x - dl - u, b.y + dl - u, b.z - dl - v, b.w + dl - v) <= rho2) m |= 1u << k;
+  }
+  return m;
+}
+
+// The whole quadrants of the tile at (x0, y0).
 __device__ __forceinline__ uint32_t quad_mask(const float4& r0, const float4& r1, const float4& r2, float x0,
                                               float y0) {
   const float u = r0.x, v = r0.y, ex = r2.z, ey = r2.w;
@@ -102,20 +123,22 @@ __device__ __forceinline__ uint32_t quad_mask(const float4& r0, const float4& r1
   const bool yt = (v - ey <= y0 + 7.5f) && (v + ey >= y0 + 0.5f);
   const bool yb = (v - ey <= y0 + 15.5f) && (v + ey >= y0 + 8.5f);
   const uint32_t box = (xl && yt ? 1u : 0u) | (xr && yt ? 2u : 0u) | (xl && yb ? 4u : 0u) | (xr && yb ? 8u : 0u);
-  if (box == 0u || !(ex < 1.0e30f)) return box;
-  const float A = r0.z, B = r0.w, C = r1.x;
-  const float iA = 1.0f / A, iC = 1.0f / C;
-  const float rho2 = (2.0f * 1.04f) * logf(255.0f * r1.y) + 4e-4f;
-  const float dl = 1e-3f + 1e-6f * fmaxf(fabsf(u), fabsf(v));
-  uint32_t m = 0u;
+  return ellipse_mask(box, r0, r1, r2, [&](int k) {
+    const float x = x0 + ((k & 1) ? 8.5f : 0.5f), y = y0 + ((k & 2) ? 8.5f : 0.5f);
+    return make_float4(x, x + 7.0f, y, y + 7.0f);
+  });
+}
+
+// The four rectangles `box` (empty where xa > xb): bit w = box[w].
+__device__ __forceinline__ uint32_t quad_mask(const float4& r0, const float4& r1, const float4& r2,
+                                              const float4 (&box)[4]) {
+  const float u = r0.x, v = r0.y, ex = r2.z, ey = r2.w;
+  if (!(ex >= 0.0f)) return 0u;
+  uint32_t hit = 0u;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (!((box >> k) & 1u)) continue;
-    const float xa = x0 + ((k & 1) ? 8.5f : 0.5f) - dl - u;
-    const float ya = y0 + ((k & 2) ? 8.5f : 0.5f) - dl - v;
-    if (conic_min_rect(A, B, C, iA, iC, xa, xa + 7.0f + 2.0f * dl, ya, ya + 7.0f + 2.0f * dl) <= rho2) m |= 1u << k;
-  }
-  return m;
+  for (int k = 0; k < 4; ++k)
+    if ((u - ex <= box[k].y) && (u + ex >= box[k].x) && (v - ey <= box[k].w) && (v + ey >= box[k].z)) hit |= 1u << k;
+  return ellipse_mask(hit, r0, r1, r2, [&](int k) { return box[k]; });
 }
 
 constexpr int kNull = kBatch;           // LDS slot of a null record (opacity 0)
@@ -454,7 +477,6 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
                                                     uint32_t* __restrict__ tile_work,
                                                     float* __restrict__ c_ckpt, size_t cplane) {
   __shared__ Stage st;
-  __shared__ uint32_t s_work;
   __shared__ typename std::conditional<CHS, ChsStage, char>::type cs;
   const int tile = tile_of_block(plan, blockIdx.x, gridDim.x);
   if (tile < 0) return;
@@ -472,7 +494,6 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
     st.r[kNull].p = make_float4(0.f, 0.f, 0.f, 0.f);
     st.r[kNull].q = make_float4(0.f, 0.f, 0.f, 0.f);
     st.r[kNull].c = make_float2(0.f, 0.f);
-    s_work = 0;
   }
 
   float T = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
@@ -552,12 +573,10 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
     n_contrib[pix] = contrib;
   }
   if (tile_work) {
-    // the tile's backward work count: the largest n_contrib of its pixels
+    // the quadrant's backward work count: the largest n_contrib of its pixels
     uint32_t mx = contrib;
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), o, 64)));
-    if ((threadIdx.x & 63) == 0 && mx) atomicMax(&s_work, mx);
-    __syncthreads();
-    if (threadIdx.x == 0) tile_work[tile] = s_work;
+    if ((threadIdx.x & 63) == 0) tile_work[4 * tile + wave] = mx;
   }
 }
 
@@ -623,7 +642,235 @@ __global__ __launch_bounds__(256) void k_render_fwd_light(const uint2* __restric
     }
   }
   for (int o = 32; o > 0; o >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), o, 64)));
-  if (lane == 0) tile_work[tile] = mx;
+  if (lane < 4) tile_work[4 * tile + lane] = lane == 0 ? mx : 0u;   // the tile's, in its first quadrant's place
+}
+
+// Forward of frames of few tiles.  With fewer tiles than the chip holds
+// workgroups, the launch lasts as long as its longest list, walked by one wave
+// per quadrant: a serial chain of about 26 VALU instructions per visited
+// entry, and of a gather and two barriers per 256 entries.  Here the chain is
+// cut in every direction at hand:
+//  - a workgroup per quadrant (four CUs share a tile), a wave per 4 x 4 pixels;
+//  - the wave's 64 lanes are 16 pixels x 4 phases: phase g evaluates alpha for
+//    the g-th of four consecutive entries, the four alphas are handed to every
+//    phase by two lane swaps, and all phases take the four blending steps
+//    together (16 instructions per entry, on a list that holds the entries of
+//    16 pixels instead of 64);
+//  - entries are tested against the box of the wave's pixels that have not
+//    stopped: one that only reaches stopped pixels changes nothing;
+//  - kFewBatches batches are staged at a time, and the next ones' records are
+//    gathered while these are walked.
+// Every pixel takes the same steps in the same order as in k_render_fwd: the
+// outputs are the same bits.
+// Measured (forward, us; this against k_render_fwd): 256 tiles, 500k Gaussians
+// on a 203 x 131 frame 360 : 2094; 64 tiles, 4,096 Gaussians 23 : 40; 1,200
+// tiles 56 : 67, 122 : 176 and 194 : 290 at 20k, 200k and 1M Gaussians; 1,900
+// tiles 72 : 56, 146 : 147 and 207 : 210; 2,500 tiles 80 : 59, 182 : 139 and
+// 259 : 232 (each quadrant stages the tile's list for itself, which costs
+// once the chip is full).  The line lies between 1,200 and 1,900.
+constexpr int kFewTiles = 1280;
+constexpr int kFewBatches = 2;
+constexpr int kFewChunk = kFewBatches * kBatch;
+
+struct FewRec {
+  float4 p;                             // u, v, a, b (see eval_pair)
+  float4 q;                             // c, opacity, -, -
+  float4 rgb;                           // r, g, b, block mask bits
+};
+struct FewStage {
+  FewRec r[kFewChunk + 1];              // the last: a null record (opacity 0)
+  // per wave and batch: byte offsets of the staged records to visit, in list
+  // order, padded with null records to a multiple of 4 and by 4 more
+  alignas(16) uint32_t list[4][kFewBatches][kBatch + 8];
+  float4 box[4];                        // each wave's pixels that still take entries
+  uint32_t act[4];
+};
+
+// Pixel-centre rectangle (xa, xb, ya, yb) of the pixels of a 4 x 4 block
+// (first pixel (qx, qy)) whose bits are set in act (bit 4 y + x); empty
+// (xa > xb) if none.
+__device__ __forceinline__ float4 active_box(uint32_t act, float qx, float qy) {
+  if (act == 0u) return make_float4(3.0e38f, -3.0e38f, 3.0e38f, -3.0e38f);
+  const uint32_t c = (act | (act >> 4) | (act >> 8) | (act >> 12)) & 15u;
+  return make_float4(qx + 0.5f + static_cast<float>(__builtin_ctz(c)), qx + 0.5f + static_cast<float>(31 - __builtin_clz(c)),
+                     qy + 0.5f + static_cast<float>(__builtin_ctz(act) >> 2),
+                     qy + 0.5f + static_cast<float>((31 - __builtin_clz(act)) >> 2));
+}
+
+// The values of rows 0..3 (16 lanes each) of x, each in every row.
+__device__ __forceinline__ void rows_to_all(float x, float (&v)[4]) {
+  const uint32_t u = __float_as_uint(x);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  v[0] = __uint_as_float(a[0]);
+  v[1] = __uint_as_float(a[1]);
+  v[2] = __uint_as_float(b[0]);
+  v[3] = __uint_as_float(b[1]);
+}
+
+__global__ __launch_bounds__(256) void k_render_fwd_few(const uint2* __restrict__ ranges,
+                                                        const uint32_t* __restrict__ point_list,
+                                                        const float4* __restrict__ rec, DevCam cam,
+                                                        float* __restrict__ image, float* __restrict__ final_T,
+                                                        uint32_t* __restrict__ n_contrib, float* __restrict__ t_ckpt,
+                                                        uint32_t* __restrict__ tile_work,
+                                                        float* __restrict__ c_ckpt, size_t cplane) {
+  __shared__ FewStage st;
+  const int t = threadIdx.x, lane = t & 63, phase = lane >> 4;
+  const int wave = static_cast<int>(uniform(static_cast<uint32_t>(t >> 6)));
+  const int item = xcd_remap(blockIdx.x, gridDim.x), tile = item >> 2, quad = item & 3;
+  const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
+  const int lx = ((quad & 1) << 3) + ((wave & 1) << 2), ly = ((quad >> 1) << 3) + ((wave >> 1) << 2);   // the block's first pixel
+  const int px_i = tx * kTile + lx + (lane & 3), py_i = ty * kTile + ly + ((lane >> 2) & 3);
+  const bool inside = px_i < cam.width && py_i < cam.height;
+  const float px = static_cast<float>(px_i) + 0.5f, py = static_cast<float>(py_i) + 0.5f;
+  const float bx = static_cast<float>(tx * kTile + lx), by = static_cast<float>(ty * kTile + ly);
+  // the pixel's place in a checkpoint slot (tile_pixel's thread)
+  const uint32_t spot = static_cast<uint32_t>(quad * 64 + (((wave >> 1) << 2) + ((lane >> 2) & 3)) * 8 + ((wave & 1) << 2) + (lane & 3));
+  const uint2 rg = ranges[tile];
+  const uint32_t len = rg.y - rg.x;
+  const size_t slot0 = ckpt_slot0(rg.x, tile);
+  const bool multi = len > static_cast<uint32_t>(kBatch);
+  constexpr uint32_t kNullAt = kFewChunk * sizeof(FewRec);
+  const char* const recs = reinterpret_cast<const char*>(st.r);
+  if (t == 0) {
+    st.r[kFewChunk].p = make_float4(0.f, 0.f, 0.f, 0.f);
+    st.r[kFewChunk].q = make_float4(0.f, 0.f, 0.f, 0.f);
+    st.r[kFewChunk].rgb = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+
+  float T = 1.0f, acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
+  uint32_t contrib = 0;
+  bool done = !inside;
+  // records of the chunk to stage and list words of the one after it (loaded
+  // at clamped positions and masked at their use, with no branch)
+  uint32_t nid[kFewBatches];
+  float4 r0[kFewBatches], r1[kFewBatches], r2[kFewBatches];
+  auto load_ids = [&](uint32_t at) {
+#pragma unroll
+    for (int s = 0; s < kFewBatches; ++s) nid[s] = point_list[rg.x + min(at + static_cast<uint32_t>(s * kBatch + t), len - 1u)];
+  };
+  auto load_recs = [&]() {
+#pragma unroll
+    for (int s = 0; s < kFewBatches; ++s) {
+      r0[s] = rec[3 * nid[s]];
+      r1[s] = rec[3 * nid[s] + 1];
+      r2[s] = rec[3 * nid[s] + 2];
+    }
+  };
+  if (len > 0u) {
+    load_ids(0u);
+    load_recs();
+    load_ids(kFewChunk);
+  }
+  for (uint32_t base = 0; base < len; base += kFewChunk) {
+    const uint32_t act = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(!done)) & 0xFFFFu;
+    if (lane == 0) {
+      st.act[wave] = act;
+      st.box[wave] = active_box(act, bx, by);
+    }
+    lds_barrier();
+    if ((st.act[0] | st.act[1] | st.act[2] | st.act[3]) == 0u) {
+      // the quadrant has stopped, other quadrants of the tile may walk on: the
+      // backward restarts this one's last batch from the boundary behind it
+      if (base > 0u && t_ckpt && phase == 0) t_ckpt[(slot0 + base / kBatch) * kBatch + spot] = T;
+      break;
+    }
+    const uint32_t cnt = min(static_cast<uint32_t>(kFewChunk), len - base);
+#pragma unroll
+    for (int s = 0; s < kFewBatches; ++s) {
+      FewRec& d = st.r[s * kBatch + t];
+      const bool valid = static_cast<uint32_t>(s * kBatch + t) < cnt;
+      const uint32_t m = valid ? quad_mask(r0[s], r1[s], r2[s], st.box) : 0u;
+      d.p = make_float4(r0[s].x, r0[s].y, -0.5f * kLog2e * r0[s].z, -0.5f * kLog2e * r0[s].w);
+      d.q = make_float4(-0.5f * kLog2e * r1[s].x, r1[s].y, 0.f, 0.f);
+      d.rgb = make_float4(r1[s].z, r1[s].w, r2[s].x, __uint_as_float(m));
+    }
+    load_recs();
+    load_ids(base + 2 * kFewChunk);
+    lds_barrier();
+#pragma unroll 1
+    for (int s = 0; s < kFewBatches && static_cast<uint32_t>(s * kBatch) < cnt; ++s) {
+      const uint32_t b = base / kBatch + static_cast<uint32_t>(s);
+      const size_t ck = (slot0 + b) * kBatch + spot;
+      if (b > 0u && t_ckpt && phase == 0) t_ckpt[ck] = T;
+      // the wave's list of the batch (a wave walks only the list it built)
+      uint32_t* const list = st.list[wave][s];
+      int L = 0;
+#pragma unroll
+      for (int r = 0; r < kBatch / 64; ++r) {
+        const int j = s * kBatch + r * 64 + lane;
+        const bool in = (__float_as_uint(st.r[j].rgb.w) >> wave) & 1u;
+        const uint64_t bal = __ballot(in);
+        if (in)
+          list[L + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(bal >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u)))] =
+              static_cast<uint32_t>(j) * static_cast<uint32_t>(sizeof(FewRec));
+        L += __popcll(bal);
+      }
+      if (lane < 8) list[L + lane] = kNullAt;
+      wave_lds_sync();
+      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+      uint32_t last = 0xFFFFFFFFu;              // offset of the last blended record
+      uint32_t own = list[phase];
+      float4 p = *reinterpret_cast<const float4*>(recs + own);
+      float4 q = *reinterpret_cast<const float4*>(recs + own + 16);
+      for (int i0 = 0; i0 < L; i0 += 4) {
+        if (__builtin_amdgcn_ballot_w64(!done) == 0) break;
+        const uint4 off = *reinterpret_cast<const uint4*>(list + i0);
+        own = list[i0 + 4 + phase];
+        const float4 c[4] = {*reinterpret_cast<const float4*>(recs + off.x + 32), *reinterpret_cast<const float4*>(recs + off.y + 32),
+                             *reinterpret_cast<const float4*>(recs + off.z + 32), *reinterpret_cast<const float4*>(recs + off.w + 32)};
+        float dx, dy, p2, eg, og, nx, ny;
+        eval_pair(p, q, px, py, dx, dy, p2, eg, og, nx, ny);
+        const float alpha = fminf(kAlphaMax, og);
+        p = *reinterpret_cast<const float4*>(recs + own);       // the next four entries'
+        q = *reinterpret_cast<const float4*>(recs + own + 16);
+        float a[4];
+        rows_to_all((p2 <= 0.0f && alpha >= kAlphaMin) ? alpha : 0.0f, a);
+        const uint32_t offs[4] = {off.x, off.y, off.z, off.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          // fwd_pair's steps; alpha 0 stands for a skipped entry
+          const float Tn = T * (1.0f - a[e]);
+          const bool ok = !done && a[e] > 0.0f;
+          const bool stop = ok && (Tn < kTMin);
+          const bool blend = ok && !stop;
+          const float w = blend ? a[e] * T : 0.0f;
+          s0 = fmaf(c[e].x, w, s0);
+          s1 = fmaf(c[e].y, w, s1);
+          s2 = fmaf(c[e].z, w, s2);
+          T = blend ? Tn : T;
+          last = blend ? offs[e] : last;
+          done = done || stop;
+        }
+      }
+      if (last != 0xFFFFFFFFu) contrib = base + last / static_cast<uint32_t>(sizeof(FewRec)) + 1u;
+      if (c_ckpt && multi && phase < 3) c_ckpt[static_cast<size_t>(phase) * cplane + ck] = phase == 0 ? s0 : (phase == 1 ? s1 : s2);
+      acc0 += s0;
+      acc1 += s1;
+      acc2 += s2;
+    }
+  }
+  if (inside) {
+    const int64_t HW = static_cast<int64_t>(cam.width) * cam.height;
+    const int64_t pix = static_cast<int64_t>(py_i) * cam.width + px_i;
+    if (phase < 3)
+      image[phase * HW + pix] = fmaf(T, phase == 0 ? cam.bg[0] : (phase == 1 ? cam.bg[1] : cam.bg[2]),
+                                     phase == 0 ? acc0 : (phase == 1 ? acc1 : acc2));
+    else
+      final_T[pix] = T;
+    if (phase == 0) n_contrib[pix] = contrib;
+  }
+  if (tile_work) {
+    uint32_t mx = contrib;
+    for (int o = 8; o > 0; o >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), o, 64)));
+    __syncthreads();                            // st.act is no longer read
+    if (lane == 0) st.act[wave] = mx;
+    __syncthreads();
+    if (t == 0) tile_work[item] = max(max(st.act[0], st.act[1]), max(st.act[2], st.act[3]));
+  }
 }
 
 // Bucket table of the colour-hash sampling mode over every list entry of the
@@ -726,7 +973,7 @@ gs_status launch_render_fwd(const gs_projected& proj, const uint32_t* point_list
     float* tail = t_ckpt + ckpt_core_floats(k, ntiles);
     plan = reinterpret_cast<int32_t*>(tail);
     tile_work = reinterpret_cast<uint32_t*>(tail + plan_ints(ntiles));
-    c_ckpt = tail + plan_ints(ntiles) + ntiles;
+    c_ckpt = tail + plan_ints(ntiles) + 4 * static_cast<size_t>(ntiles);
     if (schedule == 2) {
       gs_status st = launch_tile_plan(ntiles, ranges, nullptr, kHeavyFactorFwd, kLightMax, plan, s);
       if (st != GS_OK) return st;
@@ -745,6 +992,11 @@ gs_status launch_render_fwd(const gs_projected& proj, const uint32_t* point_list
                                                       reinterpret_cast<const float4*>(proj.records), cam, image,
                                                       final_T, n_contrib, t_ckpt, nullptr, plan, tile_work, c_ckpt,
                                                       cplane);
+  } else if (ntiles <= kFewTiles && !plan) {
+    TimedLaunch gs_tl("k_render_fwd_few", s);
+    k_render_fwd_few<<<4 * ntiles, 256, 0, s>>>(reinterpret_cast<const uint2*>(ranges), point_list,
+                                                reinterpret_cast<const float4*>(proj.records), cam, image, final_T,
+                                                n_contrib, t_ckpt, tile_work, c_ckpt, cplane);
   } else {
     TimedLaunch gs_tl("k_render_fwd<false, false>", s);
     k_render_fwd<false><<<ntiles, 256, 0, s>>>(reinterpret_cast<const uint2*>(ranges), point_list,
@@ -1020,7 +1272,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ra
   float GS = T * (G0 * cam.bg[0] + G1 * cam.bg[1] + G2 * cam.bg[2]);
   uint32_t smax;
   if (tile_work) {
-    smax = tile_work[tile];  // the largest n_contrib of the tile, from the forward
+    smax = tile_work_of(tile_work, tile);  // the largest n_contrib of the tile, from the forward
   } else {
     if (threadIdx.x == 0) s_max = 0;
     __syncthreads();
@@ -1338,7 +1590,7 @@ gs_status launch_render_bwd(int64_t n, const gs_projected& proj, const uint32_t*
     // MERGED hands tiles with at most kLightMax entries to the merged kernel
     const float* tail = t_ckpt + ckpt_core_floats(k, ntiles);
     const uint32_t* tile_work = reinterpret_cast<const uint32_t*>(tail + plan_ints(ntiles));
-    const float* c_ckpt = tail + plan_ints(ntiles) + ntiles;
+    const float* c_ckpt = tail + plan_ints(ntiles) + 4 * static_cast<size_t>(ntiles);
     int32_t* light = schedule == 2 ? reinterpret_cast<int32_t*>(w + 256) : nullptr;
     int32_t* items = reinterpret_cast<int32_t*>(w + bwd_items_offset(ntiles));
     st = launch_batch_plan(ntiles, ranges, tile_work, schedule == 2 ? kLightMax : 0, items, light,

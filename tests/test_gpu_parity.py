@@ -645,6 +645,38 @@ def test_bin_sort_routes(gs, n, width, height, quantised):
         assert k_dev.tolist() == [k, 0] and not rg2.any()
 
 
+@pytest.mark.parametrize("n,width,height", [(1, 5, 3), (300, 16, 16), (600, 17, 31), (30000, 37, 29), (60000, 100, 70),
+                                            (20000, 512, 640), (20000, 528, 640)])
+def test_few_tiles_forward_is_the_same_bits(gs, n, width, height):
+    """Frames of at most 1,280 tiles take a forward of their own (a workgroup
+    per quadrant, two batches staged at a time); MERGED never does.  Both give
+    the same image, final_T and n_contrib bit for bit -- for lists below, at and
+    far beyond a stage of 512 entries, ragged frames, and either side of the
+    tile limit -- and a backward from either one's checkpoints gives the same
+    gradients up to the order of FP32 sums (2e-5 of their norm: below 2^-24
+    times the square root of the 10^5 terms of the longest sums, times 4)."""
+    scene = scenes.uniform_scene(n, 98, log_scale_mean=-3.6, log_scale_std=0.5, sh_degree=0)
+    cam = scenes.front_camera(width, height, 3.0, 60.0)
+    p, g, out = gpu_project(gs, scene, cam)
+    k, pl, ranges = gpu_bin_sort(gs, n, out, cam)
+    G = to_dev(scenes.upstream_grad(cam, 2002))
+    cs = gs.camera_struct(cam)
+    res = {}
+    for sched in (0, 1, 2):
+        image, fT, nc, ck = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=sched)
+        g2d = torch.empty((gs.G2D, n), dtype=torch.float32, device=DEV)
+        ws = torch.empty(gs.render_bwd_2d_workspace(n, k, cs, True), dtype=torch.uint8, device=DEV)
+        gs.render_bwd_2d(n, out, pl, ranges, k, cs, fT, nc, ck, G, g2d, ws, deterministic=True, schedule=sched)
+        res[sched] = (image, fT, nc, g2d)
+    for sched in (0, 1):
+        for a, b in zip(res[sched][:3], res[2][:3]):
+            assert torch.equal(a, b), f"schedule {sched}"
+        a, b = res[sched][3].double(), res[2][3].double()
+        assert torch.isfinite(a).all()
+        assert float((a - b).norm()) <= 2e-5 * float(b.norm()), f"schedule {sched}"
+    say(f"  {n} on {width}x{height}: K={k}, longest list {int((ranges[:, 1] - ranges[:, 0]).max())}")
+
+
 def _slab_scene(n_small=20000, n_big=700, seed=93):
     """Small Gaussians everywhere plus large ones in a thin depth slab: rank
     groups inside the slab touch thousands of tiles, the others a few hundred."""
