@@ -178,9 +178,9 @@ gs_status launch_tile_plan(int ntiles, const uint32_t* ranges, const uint32_t* c
 // Also clears zero[0, zero_n4) (float4s) in the same launch when zero_n4 > 0.
 gs_status launch_batch_plan(int ntiles, const uint32_t* ranges, const uint32_t* work, int light_max, int32_t* items,
                             int32_t* light, float4* zero, int64_t zero_n4, hipStream_t s);
-// Backward work items (pairs) for K entries over ntiles tiles, with header.
+// Backward work items (four ints) for K entries over ntiles tiles, with header.
 inline size_t batch_item_ints(int64_t k, int64_t ntiles) {
-  return 16 + 2 * static_cast<size_t>(k / 256 + ntiles + 1);
+  return 16 + 4 * static_cast<size_t>(k / 256 + ntiles + 1);
 }
 // Record gradients handed to the projection backward: g2d[9][n] (rows ==
 // false) or the compositing backward's accumulator rows acc[n][kAccStride]

@@ -124,113 +124,122 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(int ntiles, const ui
 // Backward work items: every batch of 256 list entries that some pixel of
 // the tile walks becomes its own workgroup, (tile, batch) in tile order.  A
 // tile's walk length is min(list length, largest n_contrib) -- the counts the
-// forward left in `work`, four per tile.  Tiles with a count of at most light_max go to the
-// light list instead (a plan with H = M = 0), or nowhere when light is NULL
-// (with light_max = 0: the tiles whose pixels blend nothing).
-// items: [0] item count, from kPlanHeader pairs (tile, batch).
-// Workgroup 0 builds the plan; the others, if any, clear zero[0, zero_n4)
-// meanwhile (the backward's accumulator rows), so that the fill runs under
-// the one-workgroup plan instead of after it.
+// forward left in `work`, four per tile.  Tiles with a count of at most
+// light_max go to the light list instead (a plan with H = M = 0), or nowhere
+// when light is NULL (with light_max = 0: the tiles whose pixels blend
+// nothing).
+// items: [0] item count, from kPlanHeader four ints per item: the tile, the
+// batch, the tile's first list position and its walk length (so that the
+// workgroup's list loads wait for nothing else).
+// The first ceil(ntiles / 1024) workgroups build the plan, 1,024 tiles each:
+// every one adds up the batches of all tiles before its own itself (24 bytes
+// per tile, read from L2; one workgroup writing every item took 22.5 us against
+// 17.3 for 6,700 tiles and 1M rows to clear).  The others, if any, clear
+// zero[0, zero_n4) meanwhile (the backward's accumulator rows).
+
+// Sums over the workgroup of two values per thread (s_w: two words per wave,
+// free again on return).
+__device__ __forceinline__ void block_sum2(uint32_t& a, uint32_t& b, uint32_t (*s_w)[2]) {
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    b += __shfl_xor(b, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_w[threadIdx.x >> 6][0] = a;
+    s_w[threadIdx.x >> 6][1] = b;
+  }
+  __syncthreads();
+  a = b = 0u;
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
+    a += s_w[w][0];
+    b += s_w[w][1];
+  }
+  __syncthreads();
+}
+// Exclusive prefixes over the workgroup of two values per thread.
+__device__ __forceinline__ void block_prefix2(uint32_t& a, uint32_t& b, uint32_t (*s_w)[2]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t ia = a, ib = b;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = __shfl_up(ia, o, 64), v = __shfl_up(ib, o, 64);
+    if (lane >= o) { ia += u; ib += v; }
+  }
+  if (lane == 63) { s_w[wave][0] = ia; s_w[wave][1] = ib; }
+  __syncthreads();
+  a = ia - a;
+  b = ib - b;
+  for (int w = 0; w < wave; ++w) {
+    a += s_w[w][0];
+    b += s_w[w][1];
+  }
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(kPlanThreads) void k_batch_plan(int ntiles, const uint2* __restrict__ ranges,
                                                              const uint32_t* __restrict__ work, int light_max,
                                                              int32_t* __restrict__ items,
                                                              int32_t* __restrict__ light,
                                                              float4* __restrict__ zero, int64_t zero_n4) {
-  if (blockIdx.x > 0) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x - 1) * kPlanThreads;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x - 1) * kPlanThreads + threadIdx.x; i < zero_n4; i += stride)
+  const int plans = (ntiles + kPlanThreads - 1) / kPlanThreads;
+  if (static_cast<int>(blockIdx.x) >= plans) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x - plans) * kPlanThreads;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x - plans) * kPlanThreads + threadIdx.x; i < zero_n4; i += stride)
       zero[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
   }
-  __shared__ uint32_t s_scan[2][kPlanThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per = (ntiles + kPlanThreads - 1) / kPlanThreads;
-  const int t0 = min(ntiles, tid * per), t1 = min(ntiles, t0 + per);
-  auto batches_of = [&](uint2 rg, uint32_t wk) -> uint32_t {
-    const uint32_t len = min(rg.y - rg.x, wk);
-    return static_cast<int>(wk) <= light_max ? 0u : (len + 255u) / 256u;
+  __shared__ uint32_t s_w[kPlanThreads / 64][2];
+  const int tid = threadIdx.x, first = blockIdx.x * kPlanThreads;
+  // a tile's first list position, walk length (0: no items) and whether it is light
+  struct Walk {
+    uint32_t first, len;
+    bool light;
   };
-  auto is_light = [&](uint32_t wk) -> bool { return wk > 0u && static_cast<int>(wk) <= light_max; };
-  // up to kPlanRegs tiles per thread are read once, all loads in flight
-  // together; larger grids read them in the loops
-  const bool regs = per <= kPlanRegs;
-  uint32_t nbr[kPlanRegs];
-  bool lgt[kPlanRegs];
-  uint32_t c[2] = {0u, 0u};
-  if (regs) {
-    uint2 rg[kPlanRegs];
-    uint32_t wk[kPlanRegs];
-#pragma unroll
-    for (int k = 0; k < kPlanRegs; ++k) {
-      rg[k] = t0 + k < t1 ? ranges[t0 + k] : make_uint2(0u, 0u);
-      wk[k] = t0 + k < t1 ? tile_work_of(work, t0 + k) : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kPlanRegs; ++k) {
-      nbr[k] = t0 + k < t1 ? batches_of(rg[k], wk[k]) : 0u;
-      lgt[k] = t0 + k < t1 && is_light(wk[k]);
-      c[0] += nbr[k];
-      c[1] += lgt[k] ? 1u : 0u;
-    }
-  } else {
-    for (int t = t0; t < t1; ++t) {
-      c[0] += batches_of(ranges[t], tile_work_of(work, t));
-      c[1] += is_light(tile_work_of(work, t)) ? 1u : 0u;
-    }
-  }
-  uint32_t ex[2], tot[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    uint32_t incl = c[k];
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
-    }
-    ex[k] = incl - c[k];
-    if (lane == 63) s_scan[k][wave] = incl;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    uint32_t before = 0, all = 0;
-    for (int w = 0; w < kPlanThreads / 64; ++w) {
-      const uint32_t v = s_scan[k][w];
-      before += (w < wave) ? v : 0u;
-      all += v;
-    }
-    ex[k] += before;
-    tot[k] = all;
-  }
-  // (tile, batch) pairs, two per 16-byte store where they pair up (items
-  // is 16-byte aligned)
-  int2* const pairs = reinterpret_cast<int2*>(items + kPlanHeader);
-  int4* const quads = reinterpret_cast<int4*>(items + kPlanHeader);
-  auto put = [&](int t, uint32_t nb, bool lt) {
-    uint32_t e = ex[0], j = 0;
-    if ((e & 1u) && j < nb) pairs[e++] = make_int2(t, static_cast<int32_t>(j++));
-    for (; j + 1 < nb; j += 2, e += 2)
-      quads[e >> 1] = make_int4(t, static_cast<int32_t>(j), t, static_cast<int32_t>(j + 1));
-    if (j < nb) pairs[e++] = make_int2(t, static_cast<int32_t>(j++));
-    ex[0] = e;
-    if (light && lt) light[kPlanHeader + ex[1]++] = t;
+  auto walk_at = [&](int t) -> Walk {
+    const uint2 rg = t < ntiles ? ranges[t] : make_uint2(0u, 0u);
+    const uint32_t wk = t < ntiles ? tile_work_of(work, t) : 0u;
+    const bool small = static_cast<int>(wk) <= light_max;
+    return Walk{rg.x, small ? 0u : min(rg.y - rg.x, wk), small && wk > 0u};
   };
-  if (regs) {
+  auto batches = [](uint32_t len) -> uint32_t { return (len + 255u) / 256u; };
+  // items and light tiles before this workgroup's; up to kPlanRegs tiles per
+  // thread have all their loads in flight together
+  uint32_t at = 0u, lat = 0u;
+  auto count = [&](const Walk& w) {
+    at += batches(w.len);
+    lat += w.light ? 1u : 0u;
+  };
+  const int before = static_cast<int>(blockIdx.x);
+  if (before <= kPlanRegs) {
+    Walk w[kPlanRegs];
 #pragma unroll
-    for (int k = 0; k < kPlanRegs; ++k)
-      if (t0 + k < t1) put(t0 + k, nbr[k], lgt[k]);
+    for (int k = 0; k < kPlanRegs; ++k) w[k] = k < before ? walk_at(k * kPlanThreads + tid) : Walk{0u, 0u, false};
+#pragma unroll
+    for (int k = 0; k < kPlanRegs; ++k) count(w[k]);
   } else {
-    for (int t = t0; t < t1; ++t) put(t, batches_of(ranges[t], tile_work_of(work, t)), is_light(tile_work_of(work, t)));
+    for (int k = 0; k < before; ++k) count(walk_at(k * kPlanThreads + tid));
   }
-  if (tid == 0) {
-    items[0] = static_cast<int32_t>(tot[0]);
-    if (light) { light[0] = 0; light[1] = 0; light[2] = static_cast<int32_t>(tot[1]); light[3] = 0; }
+  const Walk own = walk_at(first + tid);
+  const uint32_t n = batches(own.len);
+  block_sum2(at, lat, s_w);
+  uint32_t pa = n, pl = own.light ? 1u : 0u;
+  block_prefix2(pa, pl, s_w);
+  at += pa;
+  lat += pl;
+  int4* const out = reinterpret_cast<int4*>(items + kPlanHeader);   // items is 16-byte aligned
+  for (uint32_t b = 0; b < n; ++b)
+    out[at + b] = make_int4(first + tid, static_cast<int>(b), static_cast<int>(own.first), static_cast<int>(own.len));
+  if (light && own.light) light[kPlanHeader + lat] = first + tid;
+  // the last tile's thread knows the totals
+  if (first + tid == ntiles - 1) {
+    items[0] = static_cast<int32_t>(at + n);
+    if (light) { light[0] = 0; light[1] = 0; light[2] = static_cast<int32_t>(lat + (own.light ? 1u : 0u)); light[3] = 0; }
   }
 }
 
 gs_status launch_batch_plan(int ntiles, const uint32_t* ranges, const uint32_t* work, int light_max, int32_t* items,
                             int32_t* light, float4* zero, int64_t zero_n4, hipStream_t s) {
   const unsigned fill = zero_n4 > 0 ? static_cast<unsigned>(std::min<int64_t>(ceil_div(zero_n4, kPlanThreads), 1024)) : 0u;
-  { TimedLaunch gs_tl("k_batch_plan", s); k_batch_plan<<<1 + fill, kPlanThreads, 0, s>>>(ntiles, reinterpret_cast<const uint2*>(ranges), work, light_max, items,
+  { TimedLaunch gs_tl("k_batch_plan", s); k_batch_plan<<<static_cast<unsigned>(ceil_div(ntiles, kPlanThreads)) + fill, kPlanThreads, 0, s>>>(ntiles, reinterpret_cast<const uint2*>(ranges), work, light_max, items,
                                           light, zero, zero_n4); }
   return check_launch("k_batch_plan");
 }

@@ -65,24 +65,22 @@ __device__ __forceinline__ void tile_pixel(int tid, int& lx, int& ly) {
 }
 
 // Smallest q(d) = A dx^2 + 2 B dx dy + C dy^2 over the rectangle
-// dx in [xa, xb], dy in [ya, yb] (A, C > 0, A C > B^2): zero if it holds
-// the origin, else the least of the four edge minima (on an edge q is a
-// parabola in the free coordinate, minimised at -B X / C or -B Y / A and
-// clamped to the edge).
-__device__ __forceinline__ float conic_min_rect(float A, float B, float C, float iA, float iC, float xa, float xb,
+// dx in [xa, xb], dy in [ya, yb] (A, C > 0, A C > B^2).  q is convex with its
+// minimum at the origin, so from a point of the rectangle q falls on the way
+// to the origin: the least value lies on the edges that face the origin --
+// x = X, the x range's point nearest 0, and y = Y likewise (inside the
+// rectangle X = Y = 0 gives 0).  On such a line q is a parabola in the free
+// coordinate, minimised at -B X / C or -B Y / A and clamped to the edge;
+// mC = -B / C and mA = -B / A may be off by a few ulp: q there is still a
+// value that q takes on the rectangle, larger than the least by second order.
+__device__ __forceinline__ float clamp3(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+__device__ __forceinline__ float conic_min_rect(float A, float B2, float C, float mA, float mC, float xa, float xb,
                                                 float ya, float yb) {
-  if (xa <= 0.0f && xb >= 0.0f && ya <= 0.0f && yb >= 0.0f) return 0.0f;
-  float best = 3.0e38f;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const float X = k ? xb : xa;
-    const float y = fminf(fmaxf(-B * X * iC, ya), yb);
-    best = fminf(best, fmaf(fmaf(A, X, 2.0f * B * y), X, C * y * y));
-    const float Y = k ? yb : ya;
-    const float x = fminf(fmaxf(-B * Y * iA, xa), xb);
-    best = fminf(best, fmaf(fmaf(C, Y, 2.0f * B * x), Y, A * x * x));
-  }
-  return best;
+  const float X = clamp3(0.0f, xa, xb), Y = clamp3(0.0f, ya, yb);
+  const float y = clamp3(mC * X, ya, yb), x = clamp3(mA * Y, xa, xb);
+  const float q1 = fmaf(fmaf(A, X, B2 * y), X, C * y * y);
+  const float q2 = fmaf(fmaf(C, Y, B2 * x), Y, A * x * x);
+  return fminf(q1, q2);
 }
 
 // Quadrants of the tile with a pixel centre that can reach alpha >= 1/255
@@ -100,15 +98,16 @@ __device__ __forceinline__ uint32_t ellipse_mask(uint32_t box, const float4& r0,
                                                  Rect rect) {
   if (box == 0u || !(r2.z < 1.0e30f)) return box;
   const float u = r0.x, v = r0.y, A = r0.z, B = r0.w, C = r1.x;
-  const float iA = 1.0f / A, iC = 1.0f / C;
-  const float rho2 = (2.0f * 1.04f) * logf(255.0f * r1.y) + 4e-4f;
+  const float mA = -B * __builtin_amdgcn_rcpf(A), mC = -B * __builtin_amdgcn_rcpf(C), B2 = 2.0f * B;
+  // ln(255 o) by the hardware base-2 logarithm (absolute error below 1e-6)
+  const float rho2 = (2.0f * 1.04f * 0.6931471805599453f) * __builtin_amdgcn_logf(255.0f * r1.y) + 4e-4f;
   const float dl = 1e-3f + 1e-6f * fmaxf(fabsf(u), fabsf(v));
   uint32_t m = 0u;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     if (!((box >> k) & 1u)) continue;
     const float4 b = rect(k);
-    if (conic_min_rect(A, B, C, iA, iC, b.x - dl - u, b.y + dl - u, b.z - dl - v, b.w + dl - v) <= rho2) m |= 1u << k;
+    if (conic_min_rect(A, B2, C, mA, mC, b.x - dl - u, b.y + dl - u, b.z - dl - v, b.w + dl - v) <= rho2) m |= 1u << k;
   }
   return m;
 }
@@ -156,18 +155,21 @@ constexpr int kListStride = kBatch + 4; // per-wave list of staged slots, padded
 // merge light tiles.
 constexpr float kHeavyFactorFwd = 3.0e38f;
 
-// Tile of workgroup `bid`.  Plain form: XCD-aware spatial map.  With a plan
-// (balanced form): heavy tiles first, largest first, one per workgroup in
-// dispatch order (so they spread over the XCDs and start at once), then the
-// others through the XCD-aware map of their own sequence.
+// Tile of workgroup `bid`.  Plain form: row by row, so that neighbouring tiles,
+// which share Gaussians, are walked at the same time on all eight XCDs.  (A
+// contiguous eighth of the frame to each XCD, for its L2's sake, leaves the
+// XCD with the densest part to finish alone: forward 162 us against 145 on the
+// 1M-Gaussian 1600 x 1064 workload, 447 against 362 at 1M on 3840 x 2160.)
+// With a plan (balanced form): heavy tiles first, largest first, then the
+// others in tile order.
 // Light tiles (no more than kLightMax entries to walk) go to the merged
 // kernels instead; -1 = nothing for this workgroup.
-__device__ __forceinline__ int tile_of_block(const int32_t* __restrict__ plan, int bid, int ntiles) {
-  if (!plan) return xcd_remap(bid, ntiles);
+__device__ __forceinline__ int tile_of_block(const int32_t* __restrict__ plan, int bid) {
+  if (!plan) return bid;
   const int H = plan[0], M = plan[1];
   const int32_t* order = plan + kPlanHeader;
   if (bid < H) return order[bid];
-  return bid < H + M ? order[H + xcd_remap(bid - H, M)] : -1;
+  return bid < H + M ? order[bid] : -1;
 }
 
 constexpr int kLightMax = 64;
@@ -207,7 +209,7 @@ __device__ __forceinline__ void stage_light(LightStage& ls, const float4* __rest
 
 // Shared per-batch staging: records (pre-scaled conic), colour + quadrant mask,
 // and each wave's list of the staged slots it must visit, in list order and
-// padded with the null slot to a multiple of kUnroll.
+// padded with the null slot to a multiple of kUnroll (forward).
 // One staged record, all fields at one LDS address (a wave-uniform index
 // reads them with one base register and immediate offsets).
 struct StageRec {
@@ -219,29 +221,42 @@ struct StageRec {
 };
 struct Stage {
   StageRec r[kBatch + 1];
-  alignas(16) uint32_t list[4][kListStride];
+  alignas(16) uint16_t list[4][kListStride];
   int len[4];
 };
 
-__device__ __forceinline__ void stage_batch(Stage& st, const float4* __restrict__ rec,
-                                            const uint32_t* __restrict__ point_list, uint32_t first, int cnt,
-                                            float x0, float y0) {
+// Entry t of a batch as loaded (r0-r2: its record), and its staging: the
+// batch holds cnt entries.
+struct Loaded {
+  uint32_t gid;
+  float4 r0, r1, r2;
+};
+__device__ __forceinline__ void load_record(const float4* __restrict__ rec, uint32_t gid, Loaded& l) {
+  l.gid = gid;
+  l.r0 = rec[3 * gid];
+  l.r1 = rec[3 * gid + 1];
+  l.r2 = rec[3 * gid + 2];
+}
+__device__ __forceinline__ void stage_record(Stage& st, const Loaded& l, int cnt, float x0, float y0) {
   const int t = threadIdx.x;
   if (t < cnt) {
-    const uint32_t gid = point_list[first + t];
-    const float4 r0 = rec[3 * gid];
-    const float4 r1 = rec[3 * gid + 1];
-    const float4 r2 = rec[3 * gid + 2];
-    st.r[t].p = make_float4(r0.x, r0.y, -0.5f * kLog2e * r0.z, -0.5f * kLog2e * r0.w);
-    st.r[t].q = make_float4(-0.5f * kLog2e * r1.x, r1.y, r1.z, r1.w);
-    st.r[t].c = make_float2(r2.x, __uint_as_float(quad_mask(r0, r1, r2, x0, y0)));
-    st.r[t].gid = gid;
+    st.r[t].p = make_float4(l.r0.x, l.r0.y, -0.5f * kLog2e * l.r0.z, -0.5f * kLog2e * l.r0.w);
+    st.r[t].q = make_float4(-0.5f * kLog2e * l.r1.x, l.r1.y, l.r1.z, l.r1.w);
+    st.r[t].c = make_float2(l.r2.x, __uint_as_float(quad_mask(l.r0, l.r1, l.r2, x0, y0)));
+    st.r[t].gid = l.gid;
   } else {
     st.r[t].p = make_float4(0.f, 0.f, 0.f, 0.f);
     st.r[t].q = make_float4(0.f, 0.f, 0.f, 0.f);
     st.r[t].c = make_float2(0.f, __uint_as_float(0u));
     st.r[t].gid = 0u;
   }
+}
+__device__ __forceinline__ void stage_batch(Stage& st, const float4* __restrict__ rec,
+                                            const uint32_t* __restrict__ point_list, uint32_t first, int cnt,
+                                            float x0, float y0) {
+  Loaded l{};
+  if (static_cast<int>(threadIdx.x) < cnt) load_record(rec, point_list[first + threadIdx.x], l);
+  stage_record(st, l, cnt, x0, y0);
 }
 
 // The wave's LDS writes are visible to its own lanes (no workgroup barrier).
@@ -252,7 +267,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // Stream compaction of the staged batch for this wave (ballot + prefix count).
-// all = true keeps every staged entry (no culling).
+// Slots below cnt; all = true keeps every one of them (no culling).  The list
+// is padded with the null slot to a multiple of PAD.
+template <int PAD>
 __device__ __forceinline__ void build_list(Stage& st, int cnt, bool all) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint64_t below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
@@ -262,10 +279,10 @@ __device__ __forceinline__ void build_list(Stage& st, int cnt, bool all) {
     const int j = r * 64 + lane;
     const bool in = (j < cnt) && (all || ((__float_as_uint(st.r[j].c.y) >> wave) & 1u));
     const uint64_t bal = __ballot(in);
-    if (in) st.list[wave][L + __popcll(bal & below)] = static_cast<uint32_t>(j);
+    if (in) st.list[wave][L + __popcll(bal & below)] = static_cast<uint16_t>(j);
     L += __popcll(bal);
   }
-  const int Lp = (L + kUnroll - 1) & ~(kUnroll - 1);
+  const int Lp = (L + PAD - 1) & ~(PAD - 1);
   if (lane < Lp - L) st.list[wave][L + lane] = kNull;
   if (lane == 0) st.len[wave] = Lp;
 }
@@ -303,8 +320,9 @@ __device__ __forceinline__ uint32_t chs_bucket(float r, float g, float b) {
   return chs_level(r) * 256u + chs_level(g) * 16u + chs_level(b);
 }
 
+// The bucket table (kChsBuckets words of LDS, apart): byte w of a bucket's word
+// is 1 + the lane of wave w's first member of the bucket (0: none).
 struct ChsStage {
-  uint32_t table[kChsBuckets];  // byte w: 1 + lane of wave w's first member of the bucket (0: none)
   uint64_t wmask[kBatch];       // at a wave's first member of a bucket: the wave's members of it
   uint32_t rep[kBatch];         // slot of the group's representative (groups of >= 2), else kChsNone
   float share_o[kBatch];        // product over the group's other members of (1 - o)
@@ -318,8 +336,9 @@ struct ChsSlot {
   bool wave_first;
 };
 
-__device__ __forceinline__ void chs_clear(ChsStage& cs) {
-  for (int i = threadIdx.x; i < kChsBuckets; i += 256) cs.table[i] = 0u;
+__device__ __forceinline__ void chs_clear(uint32_t* table) {
+  uint4* const t4 = reinterpret_cast<uint4*>(table);
+  for (int i = threadIdx.x; i < kChsBuckets / 4; i += 256) t4[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Alpha-support box of a representative whose opacity rose from o to o_hat:
@@ -342,10 +361,10 @@ __device__ __forceinline__ void chs_support(float o, float o_hat, float u, float
 // rewrites it in place: a representative of a group of two or more gets the
 // mean colour, the accumulated opacity and the quadrant mask of that opacity;
 // the other members get an empty quadrant mask.  SHARES also fills rep,
-// share_o and inv_n for the backward.  cs.table must be zero on entry; call
+// share_o and inv_n for the backward.  `table` must be zero on entry; call
 // chs_release after the next workgroup barrier.  One barrier inside.
 template <bool SHARES>
-__device__ ChsSlot chs_group(Stage& st, ChsStage& cs, const float4* __restrict__ rec, int cnt, float x0, float y0) {
+__device__ ChsSlot chs_group(Stage& st, ChsStage& cs, uint32_t* table, const float4* __restrict__ rec, int cnt, float x0, float y0) {
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const bool valid = t < cnt;
   const uint32_t h = valid ? chs_bucket(st.r[t].q.z, st.r[t].q.w, st.r[t].c.x) : 0u;
@@ -360,12 +379,12 @@ __device__ ChsSlot chs_group(Stage& st, ChsStage& cs, const float4* __restrict__
   const bool wfirst = valid && static_cast<int>(__builtin_ctzll(same)) == lane;
   if (wfirst) {
     cs.wmask[t] = same;
-    atomicOr(&cs.table[h], static_cast<uint32_t>(lane + 1) << (8 * wave));
+    atomicOr(&table[h], static_cast<uint32_t>(lane + 1) << (8 * wave));
   }
   if (SHARES) cs.rep[t] = kChsNone;
   __syncthreads();
   if (valid) {
-    const uint32_t word = cs.table[h];
+    const uint32_t word = table[h];
     const int w0 = static_cast<int>(__builtin_ctz(word)) >> 3;
     const int r = 64 * w0 + static_cast<int>((word >> (8 * w0)) & 0xFFu) - 1;
     int n = 0;
@@ -434,8 +453,8 @@ __device__ ChsSlot chs_group(Stage& st, ChsStage& cs, const float4* __restrict__
   return ChsSlot{h, wfirst};
 }
 
-__device__ __forceinline__ void chs_release(ChsStage& cs, const ChsSlot& sl) {
-  if (sl.wave_first) cs.table[sl.bucket] = 0u;
+__device__ __forceinline__ void chs_release(uint32_t* table, const ChsSlot& sl) {
+  if (sl.wave_first) table[sl.bucket] = 0u;
 }
 
 // ------------------------------------------------------------------- forward
@@ -478,9 +497,10 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
                                                     float* __restrict__ c_ckpt, size_t cplane) {
   __shared__ Stage st;
   __shared__ typename std::conditional<CHS, ChsStage, char>::type cs;
-  const int tile = tile_of_block(plan, blockIdx.x, gridDim.x);
+  __shared__ alignas(16) uint32_t table[CHS ? kChsBuckets : 1];
+  const int tile = tile_of_block(plan, blockIdx.x);
   if (tile < 0) return;
-  if constexpr (CHS) chs_clear(cs);
+  if constexpr (CHS) chs_clear(table);
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   int lx, ly;
   tile_pixel(threadIdx.x, lx, ly);
@@ -513,13 +533,13 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
     __syncthreads();
     ChsSlot sl{0u, false};
     if constexpr (CHS) {
-      sl = chs_group<false>(st, cs, rec, cnt, x0, y0);
+      sl = chs_group<false>(st, cs, table, rec, cnt, x0, y0);
       __syncthreads();
     }
-    build_list(st, cnt, COUNT);
+    build_list<kUnroll>(st, cnt, COUNT);
     if constexpr (CHS) {
       __syncthreads();
-      chs_release(cs, sl);
+      chs_release(table, sl);
     } else {
       wave_lds_sync();   // a wave walks only the list it built
     }
@@ -530,8 +550,9 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
     float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
     for (int i0 = 0; i0 < L; i0 += kUnroll) {
       if (__builtin_amdgcn_ballot_w64(!done) == 0) break;  // whole wave finished: leave the batch
-      const uint4 jj = *reinterpret_cast<const uint4*>(&st.list[wave_u][i0]);
-      const uint32_t js[kUnroll] = {uniform(jj.x), uniform(jj.y), uniform(jj.z), uniform(jj.w)};
+      const uint2 jj = *reinterpret_cast<const uint2*>(&st.list[wave_u][i0]);
+      const uint32_t j01 = uniform(jj.x), j23 = uniform(jj.y);
+      const uint32_t js[kUnroll] = {j01 & 0xFFFFu, j01 >> 16, j23 & 0xFFFFu, j23 >> 16};
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const uint32_t j = js[u];
@@ -887,6 +908,7 @@ __global__ __launch_bounds__(256) void k_chs_table(const uint2* __restrict__ ran
                                                    uint16_t* __restrict__ bucket_out, uint32_t* __restrict__ rep_out) {
   __shared__ Stage st;
   __shared__ ChsStage cs;
+  __shared__ alignas(16) uint32_t table[kChsBuckets];
   __shared__ float4 s_sum[kBatch];    // colour and opacity sums of a group, at its representative
   __shared__ uint32_t s_n[kBatch];
   const int tile = blockIdx.x;
@@ -894,7 +916,7 @@ __global__ __launch_bounds__(256) void k_chs_table(const uint2* __restrict__ ran
   const float x0 = static_cast<float>(tx * kTile), y0 = static_cast<float>(ty * kTile);
   const uint2 rg = ranges[tile];
   const int t = threadIdx.x;
-  chs_clear(cs);
+  chs_clear(table);
   for (uint32_t base = rg.x; base < rg.y; base += kBatch) {
     const int cnt = static_cast<int>(min(static_cast<uint32_t>(kBatch), rg.y - base));
     __syncthreads();
@@ -905,9 +927,9 @@ __global__ __launch_bounds__(256) void k_chs_table(const uint2* __restrict__ ran
     const bool valid = t < cnt;
     // the entry's own colour and opacity, before the grouping rewrites the batch
     const float4 own = valid ? make_float4(st.r[t].q.z, st.r[t].q.w, st.r[t].c.x, st.r[t].q.y) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const ChsSlot sl = chs_group<true>(st, cs, rec, cnt, x0, y0);
+    const ChsSlot sl = chs_group<true>(st, cs, table, rec, cnt, x0, y0);
     __syncthreads();
-    chs_release(cs, sl);
+    chs_release(table, sl);
     const int r = valid && cs.rep[t] != kChsNone ? static_cast<int>(cs.rep[t]) : t;
     if (valid) {
       if (bucket_out) bucket_out[base + t] = static_cast<uint16_t>(sl.bucket);
@@ -1206,6 +1228,19 @@ __global__ __launch_bounds__(256) void k_det_reduce(int n, const uint32_t* __res
 // atomics of an instruction meet in one or two L2 lines (the [9][n] output
 // is written from it afterwards).  DET: the sums go to the entry's row of `part` instead
 // (deterministic reduction above).
+//
+// The per-pair terms, their sums over the wave and the order of the items are
+// kept as they are for the sake of the accumulators: a large Gaussian's row
+// collects thousands of sums of either sign, and taking the items in tile
+// order, or the wave's sums from the matrix cores (moments of dL/dpower over
+// the quadrant, on exact BF16 splits, 266 us against 273), moved the largest
+// scale gradients of stretched Gaussians by up to 8e-3 of the gradients' rms.
+// (So did walking several batches per workgroup, 621 us against 660 at 1.5M
+// stretched Gaussians.)  With the item carrying
+// its list position, 16-bit lists and the shorter support test it runs eight
+// waves per SIMD (63 registers against 71): 265 us against 273 at 1M Gaussians,
+// 622 against 682 at 1.5M stretched ones, and with colour-hash sampling, where
+// four workgroups now share a CU's LDS instead of three, 201 against 270.
 template <bool DET, bool CHS = false>
 __global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ point_list,
@@ -1228,22 +1263,31 @@ __global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ra
   // CHS: the grouping, and per staged entry the sums of the gradient reaching
   // its group's aggregated opacity and colour (representatives only)
   __shared__ typename std::conditional<CHS, ChsStage, char>::type cs;
+  __shared__ alignas(16) uint32_t table[CHS ? kChsBuckets : 1];
   __shared__ float4 s_chs4[CHS ? kBatch : 1];
   float* const s_chs = reinterpret_cast<float*>(s_chs4);
   // items: this workgroup walks one batch of one tile (the batch plan);
   // otherwise the whole tile (plain map, or the plan's order)
-  int tile, b_only = -1;
+  int tile, b_hi = 0, b_lo = 0;
+  uint32_t first, len;                  // the tile's list and its walked length
   if (items) {
     const int nitems = items[0];
     if (static_cast<int>(blockIdx.x) >= nitems) return;
-    const int it = xcd_remap(blockIdx.x, nitems);
-    tile = items[kPlanHeader + 2 * it];
-    b_only = items[kPlanHeader + 2 * it + 1];
+    const int4 it = reinterpret_cast<const int4*>(items + kPlanHeader)[xcd_remap(blockIdx.x, nitems)];
+    tile = it.x;
+    b_hi = b_lo = it.y;
+    first = static_cast<uint32_t>(it.z);
+    len = static_cast<uint32_t>(it.w);
   } else {
-    tile = tile_of_block(plan, blockIdx.x, gridDim.x);
+    tile = tile_of_block(plan, blockIdx.x);
     if (tile < 0) return;
+    const uint2 rg = ranges[tile];
+    first = rg.x;
+    len = rg.y - rg.x;
   }
-  if constexpr (CHS) chs_clear(cs);
+  // CHS groups whole 256-entry windows of the list, walked or not
+  uint32_t list_len = len;
+  if constexpr (CHS) list_len = ranges[tile].y - first;
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   int lx, ly;
   tile_pixel(threadIdx.x, lx, ly);
@@ -1251,13 +1295,21 @@ __global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ra
   const bool inside = px_i < cam.width && py_i < cam.height;
   const float px = static_cast<float>(px_i) + 0.5f, py = static_cast<float>(py_i) + 0.5f;
   const float x0 = static_cast<float>(tx * kTile), y0 = static_cast<float>(ty * kTile);
-  const uint2 rg = ranges[tile];
-  const int wave = threadIdx.x >> 6;
+  // the wave's row as a scalar: the loop control is scalar
+  const int wave = static_cast<int>(uniform(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const bool lo8 = (lane & 8) == 0;
   const int out_slot = (lane == 63) ? 8 : kReduceSlot[((lane >> 4) << 1) | ((lane >> 3) & 1)];
   const bool writer = ((lane & 7) == 0) || lane == 63;
+  if constexpr (CHS) chs_clear(table);
+  // list words of batch bi, at clamped positions (masked when staged)
+  auto load_id = [&](int bi) {
+    const uint32_t at = static_cast<uint32_t>(max(bi, 0)) * kBatch;
+    return point_list[first + min(at + threadIdx.x, list_len - 1u)];
+  };
 
+  uint32_t id = 0u;
+  if (items) id = load_id(b_hi);
   float G0 = 0.f, G1 = 0.f, G2 = 0.f, T = 1.0f;
   uint32_t ncon = 0;
   if (inside) {
@@ -1268,67 +1320,87 @@ __global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ra
     ncon = n_contrib[pix];
   }
   const float T_final = T;
-  const size_t slot0 = ckpt_slot0(rg.x, tile);
+  const size_t slot0 = ckpt_slot0(first, tile);
   float GS = T * (G0 * cam.bg[0] + G1 * cam.bg[1] + G2 * cam.bg[2]);
-  uint32_t smax;
-  if (tile_work) {
-    smax = tile_work_of(tile_work, tile);  // the largest n_contrib of the tile, from the forward
+  // the largest n_contrib of this wave's quadrant (from the forward)
+  uint32_t wmax;
+  if (items) {
+    wmax = tile_work[4 * tile + wave];
   } else {
+    wmax = ncon;
+    for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(wmax), o, 64)));
+    wmax = uniform(wmax);
     if (threadIdx.x == 0) s_max = 0;
     __syncthreads();
-    if (ncon) atomicMax(&s_max, ncon);
+    if (lane == 0) atomicMax(&s_max, wmax);
     __syncthreads();
-    smax = s_max;
+    len = min(len, s_max);  // n_contrib never exceeds the list
+    if (len == 0u) return;
+    b_hi = static_cast<int>((len - 1u) / kBatch);
+    id = load_id(b_hi);
   }
-  const uint32_t len = min(rg.y - rg.x, smax);  // n_contrib never exceeds the list
   const int nbatch = static_cast<int>((len + kBatch - 1) / kBatch);
-  int b_hi = nbatch - 1, b_lo = 0;
-  if (b_only >= 0) {
-    b_hi = b_lo = b_only;
+  // T at the end of batch bi, from the forward's checkpoint there
+  auto load_T = [&](int bi) { return (bi + 1 < nbatch) ? t_ckpt[(slot0 + bi + 1) * kBatch + threadIdx.x] : T_final; };
+  float T_next = load_T(b_hi);
+  Loaded rc;
+  load_record(rec, id, rc);
+  if (items) {
     // light behind the end of this batch: the forward's colour sums of the
-    // pixel's later batches (each a sum of non-negative terms), dotted with G
+    // pixel's later batches (each a sum of non-negative terms), dotted with
+    // G; four batches' loads in flight together
     const int last = ncon ? static_cast<int>((ncon - 1) / kBatch) : -1;
-    for (int bb = b_only + 1; bb <= last; ++bb) {
-      const size_t o = (slot0 + bb) * kBatch + threadIdx.x;
-      GS += G0 * c_ckpt[o] + G1 * c_ckpt[cplane + o] + G2 * c_ckpt[2 * cplane + o];
+    for (int b0 = b_hi + 1; b0 <= last; b0 += 4) {
+      float c[4][3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const size_t o = (slot0 + min(b0 + u, last)) * kBatch + threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[u][k] = c_ckpt[k * cplane + o];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (b0 + u <= last) GS += G0 * c[u][0] + G1 * c[u][1] + G2 * c[u][2];
     }
   }
 
   for (int bi = b_hi; bi >= b_lo; --bi) {
     const uint32_t m0 = static_cast<uint32_t>(bi) * kBatch;
     const int cnt = static_cast<int>(min(static_cast<uint32_t>(kBatch), len - m0));
-    T = (bi + 1 < nbatch) ? t_ckpt[(slot0 + bi + 1) * kBatch + threadIdx.x] : T_final;
-    // CHS groups the whole 256-entry window, walked or not, as the forward did
-    const int cnt_all = CHS ? static_cast<int>(min(static_cast<uint32_t>(kBatch), rg.y - rg.x - m0)) : cnt;
-    __syncthreads();
-    stage_batch(st, rec, point_list, rg.x + m0, cnt_all, x0, y0);
+    const int cnt_all = static_cast<int>(min(static_cast<uint32_t>(kBatch), list_len - m0));
+    T = T_next;
+    if (bi < b_hi) load_record(rec, id, rc);
+    lds_barrier();
+    stage_record(st, rc, CHS ? cnt_all : cnt, x0, y0);
+    if (bi > b_lo) {   // for the batch before this one
+      T_next = load_T(bi - 1);
+      id = load_id(bi - 1);
+    }
     if constexpr (DET) {
       for (int i = threadIdx.x; i < 4 * kBatch * kDetRow / 4; i += 256) s_part4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if constexpr (CHS) s_chs4[threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
+    lds_barrier();
     ChsSlot sl{0u, false};
     if constexpr (CHS) {
-      sl = chs_group<true>(st, cs, rec, cnt_all, x0, y0);
+      sl = chs_group<true>(st, cs, table, rec, cnt_all, x0, y0);
       __syncthreads();
     }
-    build_list(st, cnt, false);
+    // the wave's list, cut behind its last pixel's last entry
+    const int reach = static_cast<int>(min(wmax > m0 ? wmax - m0 : 0u, static_cast<uint32_t>(cnt)));
+    build_list<1>(st, reach, false);
     if constexpr (CHS) {
       __syncthreads();
-      chs_release(cs, sl);
+      chs_release(table, sl);
     } else {
       wave_lds_sync();   // a wave walks only the list it built
     }
-    // the wave's list length and row as scalars: the loop control is scalar
-    const int wave_u = static_cast<int>(uniform(static_cast<uint32_t>(wave)));
     // entry m0 + j reaches this pixel iff j < ncon - m0 (one compare per entry)
     const uint32_t nrel = ncon > m0 ? ncon - m0 : 0u;
-    for (int i = static_cast<int>(uniform(static_cast<uint32_t>(st.len[wave_u]))) - 1; i >= 0; --i) {
-      const uint32_t j = uniform(st.list[wave_u][i]);
-      if (j == kNull) continue;
+    for (int i = static_cast<int>(uniform(static_cast<uint32_t>(st.len[wave]))) - 1; i >= 0; --i) {
+      const uint32_t j = uniform(st.list[wave][i]);
       const bool live = j < nrel;
-      const uint64_t reach = __builtin_amdgcn_ballot_w64(live);
-      if (reach == 0) continue;  // no lane of this wave reaches entry m yet
+      const uint64_t reached = __builtin_amdgcn_ballot_w64(live);
       const float4 p = st.r[j].p;
       const float4 q = st.r[j].q;
       const float cb = st.r[j].c.x;
@@ -1338,7 +1410,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ra
       const bool ok = live && (p2 <= 0.0f) && (alpha >= kAlphaMin);
       // the wave's test from the compares' own masks (a ballot of the
       // combined bool would first turn it into an integer and back)
-      if ((reach & __builtin_amdgcn_ballot_w64(p2 <= 0.0f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin)) == 0)
+      if ((reached & __builtin_amdgcn_ballot_w64(p2 <= 0.0f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin)) == 0)
         continue;
       float v[9];
       bwd_terms(q, cb, ok, nx, ny, alpha, eg, og, G0, G1, G2, T, GS, v);
@@ -1425,7 +1497,6 @@ __global__ __launch_bounds__(256) void k_render_bwd_light(const uint2* __restric
   const bool lo8 = (lane & 8) == 0;
   const int out_slot = (lane == 63) ? 8 : kReduceSlot[((lane >> 4) << 1) | ((lane >> 3) & 1)];
   const bool writer = ((lane & 7) == 0) || lane == 63;
-  float* const g_out = acc + out_slot;
   const int64_t HW = static_cast<int64_t>(cam.width) * cam.height;
   float G0[4], G1[4], G2[4], T[4], GS[4], px[4], py[4];
   uint32_t ncon[4];
@@ -1480,7 +1551,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_light(const uint2* __restric
       const uint32_t r = det_row(row_of[ls.gid[j]], tx, ty);
       if (writer && r < rows) part[static_cast<size_t>(r) * kDetRow + out_slot] = lane == 63 ? red9 : red8;
     } else {
-      if (writer) unsafeAtomicAdd(&g_out[static_cast<int64_t>(ls.gid[j]) * kAccStride], lane == 63 ? red9 : red8);
+      if (writer) unsafeAtomicAdd(acc + static_cast<int64_t>(ls.gid[j]) * kAccStride + out_slot, lane == 63 ? red9 : red8);
     }
   }
 }

@@ -646,13 +646,13 @@ def test_bin_sort_routes(gs, n, width, height, quantised):
 
 
 @pytest.mark.parametrize("n,width,height", [(1, 5, 3), (300, 16, 16), (600, 17, 31), (30000, 37, 29), (60000, 100, 70),
-                                            (20000, 512, 640), (20000, 528, 640)])
+                                            (20000, 512, 640), (20000, 528, 640), (3000, 4096, 4112)])
 def test_few_tiles_forward_is_the_same_bits(gs, n, width, height):
     """Frames of at most 1,280 tiles take a forward of their own (a workgroup
     per quadrant, two batches staged at a time); MERGED never does.  Both give
     the same image, final_T and n_contrib bit for bit -- for lists below, at and
     far beyond a stage of 512 entries, ragged frames, and either side of the
-    tile limit -- and a backward from either one's checkpoints gives the same
+    tile limit, more tiles than the backward's plan keeps in registers -- and a backward from either one's checkpoints gives the same
     gradients up to the order of FP32 sums (2e-5 of their norm: below 2^-24
     times the square root of the 10^5 terms of the longest sums, times 4)."""
     scene = scenes.uniform_scene(n, 98, log_scale_mean=-3.6, log_scale_std=0.5, sh_degree=0)
