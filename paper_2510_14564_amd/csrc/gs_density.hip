@@ -6,21 +6,25 @@
 // nearest dense pairs within mu_d + gamma sigma_d.
 //
 // The neighbour searches run on a uniform grid of cells of side h = 1.07 r,
-// hashed into a power-of-two table and counting-sorted by bucket (one pass of
-// atomics, then the library's exclusive scan).  A point's cell is
-// floor(x / h) per axis in FP32; with every coordinate below 2^18 h in
-// magnitude the FP32 cell coordinates of two points differ from their exact
-// value by less than 1/16 of a cell, so a point within r of another lies in
-// the same or an adjacent cell (27 cells cover the radius search), and after
-// the cells up to Chebyshev offset R have been scanned every point closer
-// than (R - 1/16) h has been seen (the k-nearest search stops on that
-// guarantee).  One thread per query scans rings 0-2; a query whose k-th
-// nearest lies farther (isolated points, a few per cent) goes on to a wave
-// of its own that scans rings 0-7 with the 64 lanes sharing each ring's cells,
-// and the few left after that to a whole workgroup that scans every point;
-// partial top-k lists are merged in LDS.
-// Several cells can share a bucket; a scan visits only the points whose own
-// cell is the one it wants, so nothing is counted twice.
+// counting-sorted by bucket (one pass of atomics, whose returned values are
+// the ranks, then the library's exclusive scan).  A row of cells along x
+// starts at a hash of its (y, z) in a power-of-two table and its cells follow
+// one another there, so the cells x - R .. x + R of a row are one contiguous
+// run of points and a search over (2R + 1)^3 cells reads (2R + 1)^2 runs.
+// A point's cell is floor(x / h) per axis in FP32; with every coordinate below
+// 2^18 h in magnitude the FP32 cell coordinates of two points differ from
+// their exact value by less than 1/16 of a cell, so a point within r of
+// another lies in the same or an adjacent cell (27 cells cover the radius
+// search), and after the cells up to Chebyshev offset R have been scanned
+// every point closer than (R - 1/16) h has been seen (the k-nearest search
+// stops on that guarantee).  One pass over the 27 cells, eight lanes per query,
+// gives a query's density and the k nearest of them; a query whose k-th nearest
+// lies farther (one in seven at a 100x density skew with 20 neighbours in r)
+// goes on to a wave of its own that scans R = 2, 4 and 7, and the few left
+// after that to workgroups that scan every point.
+// Rows can share buckets; a scan counts only the points whose own row is the
+// one it wants (a row's run holds each of its points once), so nothing is
+// counted twice.
 //
 // Every decision is taken exactly as the definition states it in the
 // precision it names: FP32 squared distances (each operation rounded, no
@@ -36,25 +40,18 @@
 
 namespace gs {
 
-constexpr int kDcRingsThread = 3;    // rings a thread scans alone (0-2)
-constexpr int kDcRingsWave = 8;      // rings a wave scans for a query (0-7) before every point is scanned
 constexpr float kDcCellScale = 1.07f;
+constexpr uint32_t kDcSlots = 64;    // slots of the statistics' sums (one per lane of the wave that adds them up)
 
-struct DcPoint {   // a point in bucket order: position and its own cell
-  float4 p;        // x, y, z, index (bits)
-  int4 c;          // cell x, y, z, unused
-};
+__device__ __forceinline__ float dc_floor(float x, float inv_h) { return floorf(__fmul_rn(x, inv_h)); }
 
-__device__ __forceinline__ uint32_t dc_hash(int cx, int cy, int cz, uint32_t mask) {
-  uint32_t h = static_cast<uint32_t>(cx) * 73856093u ^ static_cast<uint32_t>(cy) * 19349663u ^
-               static_cast<uint32_t>(cz) * 83492791u;
+// Position of cell (0, cy, cz) in the table; the row's cell cx lies cx further on, modulo the table.
+__device__ __forceinline__ uint32_t dc_row(int cy, int cz) {
+  uint32_t h = static_cast<uint32_t>(cy) * 19349663u ^ static_cast<uint32_t>(cz) * 83492791u;
   h ^= h >> 15;
   h *= 0x2c1b3c6du;
-  h ^= h >> 12;
-  return h & mask;
+  return h ^ h >> 12;
 }
-
-__device__ __forceinline__ int dc_cell(float x, float inv_h) { return static_cast<int>(floorf(__fmul_rn(x, inv_h))); }
 
 // FP32 squared distance from the query q to point p, rounded step by step.
 __device__ __forceinline__ float dc_d2(const float4& q, const float4& p) {
@@ -74,30 +71,38 @@ __host__ __device__ __forceinline__ uint32_t far_splits(uint32_t count) {
   return count == 0 || count > kFarSlots ? 1u : (kFarSlots / count < kFarSplitMax ? kFarSlots / count : kFarSplitMax);
 }
 
+struct DcSums {            // one slot of the statistics' sums, a cache line of its own
+  unsigned long long c1, c2;  // rho, rho^2
+  double a1, a2;              // nearest distance, its square
+  unsigned long long pad[4];
+};
+
+struct DcReport {          // what the host reads back, in one copy
+  double stat[8];          // mu, sigma, rho_low, rho_high, mu_d, sigma_d, d_merge, unused
+  unsigned long long total;   // kept + new (from the scan)
+  uint32_t kept;
+  uint32_t range;          // set if a coordinate is out of the cells' range
+};
+
 struct DcWs {
   uint32_t* count;      // [T] points per bucket, then their exclusive prefix (bucket starts)
-  uint32_t* fill;       // [T]
-  uint32_t* sums;       // scan block sums
-  DcPoint* pts;         // [n] in bucket order
-  int4* cell;           // [n] each point's cell and bucket
+  uint32_t* scan;       // scan block sums
+  float4* pts;          // [n] x, y, z, index (bits) in bucket order
+  uint2* cell;          // [n] each point's bucket and rank in it
   int32_t* rho;         // [n]
   int32_t* nn;          // [n] nearest other point
   float* dnn;           // [n] its distance
   float* dbar;          // [n] mean distance to the k nearest
-  uint32_t* keep;       // [n] 1 if the point survives, then its exclusive prefix
-  uint32_t* low;        // [n] 1 if the point spawns a new one, then its exclusive prefix
+  uint32_t* pos;        // [2n] 1 if the point survives, then 1 if it spawns a new one; then their exclusive prefix,
+                        // which is the output position of each
   int32_t* partner;     // [n] merge partner or -1
-  unsigned long long* isum;  // [2] sum rho, sum rho^2
-  double* dsum;         // [2] sum dnn, sum dnn^2 (FP64 atomics)
-  double* stat;         // [8] mu, sigma, rho_low, rho_high, mu_d, sigma_d, d_merge, unused
-  unsigned long long* total;  // [2] kept, low counts (from the scans)
-  uint32_t* range;      // [1] set if a coordinate is out of the cells' range
-  uint32_t* far;        // [n] queries the thread kernel left, [1] their count (far_n)
+  DcSums* sums;         // [kDcSlots]
+  DcReport* rep;        // [1]
+  uint32_t* far;        // [n] queries the 27 cells left, [1] their count (far_n)
   uint32_t* far_n;
   uint32_t* far2;       // [n] queries the wave kernel left, [1] their count
   uint32_t* far2_n;
-  float* cand_d;        // [kFarSlots][8] partial k-nearest lists of the split far search
-  int32_t* cand_i;
+  double* cand;         // [kFarSlots][8] partial k-nearest lists of the split far search
   size_t bytes;
 };
 
@@ -113,391 +118,371 @@ static DcWs carve_dc(void* base, int64_t n) {
   const uint32_t T = dc_table(n);
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
   w.count = c.take<uint32_t>(T);
-  w.fill = c.take<uint32_t>(T);
-  w.sums = c.take<uint32_t>(std::max(scan_sums_words(T), scan_sums_words(n)));
-  w.pts = c.take<DcPoint>(nn);
-  w.cell = c.take<int4>(nn);
+  w.scan = c.take<uint32_t>(std::max(scan_sums_words(T), scan_sums_words(2 * n)));
+  w.pts = c.take<float4>(nn);
+  w.cell = c.take<uint2>(nn);
   w.rho = c.take<int32_t>(nn);
   w.nn = c.take<int32_t>(nn);
   w.dnn = c.take<float>(nn);
   w.dbar = c.take<float>(nn);
-  w.keep = c.take<uint32_t>(nn);
-  w.low = c.take<uint32_t>(nn);
+  w.pos = c.take<uint32_t>(2 * nn);
   w.partner = c.take<int32_t>(nn);
-  w.isum = c.take<unsigned long long>(2);
-  w.dsum = c.take<double>(2);
-  w.stat = c.take<double>(8);
-  w.total = c.take<unsigned long long>(2);
-  w.range = c.take<uint32_t>(1);
+  w.sums = c.take<DcSums>(kDcSlots);
+  w.rep = c.take<DcReport>(1);
   w.far = c.take<uint32_t>(nn);
   w.far_n = c.take<uint32_t>(1);
   w.far2 = c.take<uint32_t>(nn);
   w.far2_n = c.take<uint32_t>(1);
-  w.cand_d = c.take<float>(static_cast<size_t>(kFarSlots) * 8);
-  w.cand_i = c.take<int32_t>(static_cast<size_t>(kFarSlots) * 8);
+  w.cand = c.take<double>(static_cast<size_t>(kFarSlots) * 8);
   w.bytes = c.off;
   return w;
 }
 
 size_t density_workspace(int64_t n) { return carve_dc(nullptr, n).bytes; }
 
-__global__ __launch_bounds__(256) void k_dc_clear(uint32_t* __restrict__ a, uint32_t* __restrict__ b, uint32_t T,
-                                                  unsigned long long* __restrict__ isum, double* __restrict__ dsum,
-                                                  unsigned long long* __restrict__ total, uint32_t* __restrict__ range,
-                                                  uint32_t* __restrict__ far_n, uint32_t* __restrict__ far2_n) {
+__global__ __launch_bounds__(256) void k_dc_clear(uint32_t* __restrict__ count, uint32_t T, DcSums* __restrict__ sums,
+                                                  DcReport* __restrict__ rep, uint32_t* __restrict__ far_n,
+                                                  uint32_t* __restrict__ far2_n) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i < T) { a[i] = 0u; b[i] = 0u; }
+  if (i < T) count[i] = 0u;
+  if (i < kDcSlots) sums[i] = DcSums{};
   if (i == 0) {
-    isum[0] = 0ull; isum[1] = 0ull; dsum[0] = 0.0; dsum[1] = 0.0;
-    total[0] = 0ull; total[1] = 0ull; range[0] = 0u; far_n[0] = 0u; far2_n[0] = 0u;
+    *rep = DcReport{};
+    far_n[0] = 0u; far2_n[0] = 0u;
   }
 }
 
-// Each point's cell and bucket, and the bucket counts.  A coordinate of 2^18
-// cells or more (or not finite) sets *range: the cell guarantees above need
-// |x| < 2^18 h.
+// Each point's bucket and its rank there (the bucket's count when it came).  A
+// coordinate of 2^18 cells or more (or not finite) sets the report's range
+// flag: the cell guarantees above need |x| < 2^18 h.
 __global__ __launch_bounds__(256) void k_dc_cells(int n, const float* __restrict__ means, float inv_h, uint32_t mask,
-                                                  int4* __restrict__ cell, uint32_t* __restrict__ count,
-                                                  uint32_t* __restrict__ range) {
+                                                  uint2* __restrict__ cell, uint32_t* __restrict__ count,
+                                                  DcReport* __restrict__ rep) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   const float x = means[i], y = means[static_cast<int64_t>(n) + i], z = means[2 * static_cast<int64_t>(n) + i];
   const float lim = 262144.0f;
-  if (!(fabsf(__fmul_rn(x, inv_h)) < lim && fabsf(__fmul_rn(y, inv_h)) < lim && fabsf(__fmul_rn(z, inv_h)) < lim)) {
-    atomicOr(range, 1u);
-    cell[i] = make_int4(0, 0, 0, 0);
-    atomicAdd(&count[0], 1u);
-    return;
+  uint32_t b = 0u;
+  if (fabsf(__fmul_rn(x, inv_h)) < lim && fabsf(__fmul_rn(y, inv_h)) < lim && fabsf(__fmul_rn(z, inv_h)) < lim) {
+    b = (dc_row(static_cast<int>(dc_floor(y, inv_h)), static_cast<int>(dc_floor(z, inv_h))) +
+         static_cast<uint32_t>(static_cast<int>(dc_floor(x, inv_h)))) & mask;
+  } else {
+    atomicOr(&rep->range, 1u);
   }
-  const int cx = dc_cell(x, inv_h), cy = dc_cell(y, inv_h), cz = dc_cell(z, inv_h);
-  const uint32_t b = dc_hash(cx, cy, cz, mask);
-  cell[i] = make_int4(cx, cy, cz, static_cast<int>(b));
-  atomicAdd(&count[b], 1u);
+  cell[i] = make_uint2(b, atomicAdd(&count[b], 1u));
 }
 
 __global__ __launch_bounds__(256) void k_dc_scatter(int n, const float* __restrict__ means,
-                                                    const int4* __restrict__ cell, const uint32_t* __restrict__ start,
-                                                    uint32_t* __restrict__ fill, DcPoint* __restrict__ pts) {
+                                                    const uint2* __restrict__ cell, const uint32_t* __restrict__ start,
+                                                    float4* __restrict__ pts) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  const int4 c = cell[i];
-  const uint32_t b = static_cast<uint32_t>(c.w);
-  const uint32_t pos = start[b] + atomicAdd(&fill[b], 1u);
-  DcPoint d;
-  d.p = make_float4(means[i], means[static_cast<int64_t>(n) + i], means[2 * static_cast<int64_t>(n) + i], __int_as_float(i));
-  d.c = make_int4(c.x, c.y, c.z, 0);
-  pts[pos] = d;
+  const uint2 c = cell[i];
+  pts[start[c.x] + c.y] =
+      make_float4(means[i], means[static_cast<int64_t>(n) + i], means[2 * static_cast<int64_t>(n) + i], __int_as_float(i));
 }
 
-// rho_i = other points within r; sums of rho and rho^2 for the thresholds.
-__global__ __launch_bounds__(256) void k_dc_density(int n, const DcPoint* __restrict__ pts,
-                                                    const uint32_t* __restrict__ start, uint32_t T, float r2,
-                                                    int32_t* __restrict__ rho, unsigned long long* __restrict__ isum) {
-  const int s = blockIdx.x * 256 + threadIdx.x;
-  unsigned long long c1 = 0, c2 = 0;
-  if (s < n) {
-    const DcPoint q = pts[s];
-    const int qi = __float_as_int(q.p.w);
-    int cnt = 0;
-    for (int dz = -1; dz <= 1; ++dz)
-      for (int dy = -1; dy <= 1; ++dy)
-        for (int dx = -1; dx <= 1; ++dx) {
-          const int cx = q.c.x + dx, cy = q.c.y + dy, cz = q.c.z + dz;
-          const uint32_t b = dc_hash(cx, cy, cz, T - 1u);
-          const uint32_t e = b + 1u < T ? start[b + 1u] : static_cast<uint32_t>(n);
-          for (uint32_t p = start[b]; p < e; ++p) {
-            const DcPoint o = pts[p];
-            if (o.c.x != cx || o.c.y != cy || o.c.z != cz || __float_as_int(o.p.w) == qi) continue;
-            if (dc_d2(q.p, o.p) <= r2) ++cnt;
-          }
-        }
-    rho[qi] = cnt;
-    c1 = static_cast<unsigned long long>(cnt);
-    c2 = c1 * c1;
-  }
-  // wave sums, then one atomic per wave
-  for (int o = 32; o > 0; o >>= 1) {
-    c1 += __shfl_xor(c1, o, 64);
-    c2 += __shfl_xor(c2, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0 && (c1 || c2)) {
-    atomicAdd(&isum[0], c1);
-    atomicAdd(&isum[1], c2);
-  }
-}
+// A candidate as one ordered value: the FP32 squared distance's bits above the
+// index, read as a double.  Both parts are non-negative, so doubles compare as
+// (distance, index) does, and keeping the K best sorted is 2K - 1 minima and
+// maxima with no branch.  3.0e38 (no candidate) and everything above it -- an
+// overflowed distance, a NaN, kDcNone -- never displaces an empty slot.
+__device__ __forceinline__ double dc_key(float d2, int i) { return __hiloint2double(__float_as_int(d2), i); }
+__device__ __forceinline__ double dc_empty() { return dc_key(3.0e38f, 0x7fffffff); }
+constexpr float kDcNone = __builtin_huge_valf();
+__device__ __forceinline__ float dc_key_d2(double k) { return __int_as_float(__double2hiint(k)); }
 
-// Thresholds from the exact integer sums, in FP64 with correctly rounded operations:
-// mu = S1/n, sigma = sqrt(max(S2/n - mu^2, 0)), rho_low = mu - alpha sigma, rho_high = mu + beta sigma.
-__global__ void k_dc_thresholds(int n, const unsigned long long* __restrict__ isum, double alpha, double beta,
-                                double* __restrict__ stat) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const double dn = static_cast<double>(n);
-  const double mu = n > 0 ? __ddiv_rn(static_cast<double>(isum[0]), dn) : 0.0;
-  const double var = n > 0 ? __dsub_rn(__ddiv_rn(static_cast<double>(isum[1]), dn), __dmul_rn(mu, mu)) : 0.0;
-  const double sigma = __dsqrt_rn(var > 0.0 ? var : 0.0);
-  stat[0] = mu;
-  stat[1] = sigma;
-  stat[2] = __dsub_rn(mu, __dmul_rn(alpha, sigma));
-  stat[3] = __dadd_rn(mu, __dmul_rn(beta, sigma));
-}
-
-// Insert (d, j) into the K best, kept sorted by (d, index) in registers
-// (unused slots hold (3e38, INT_MAX)): each slot keeps the smaller of its
-// entry and the carried one and passes the larger on; the last falls off.
 template <int K>
-__device__ __forceinline__ void dc_insert(float (&bd)[K], int (&bi)[K], float d, int j) {
-  if (!(d < bd[K - 1] || (d == bd[K - 1] && j < bi[K - 1]))) return;
-  float cd = d;
-  int cj = j;
+__device__ __forceinline__ void dc_insert(double (&b)[K], double c) {
 #pragma unroll
   for (int m = 0; m < K; ++m) {
-    const bool less = cd < bd[m] || (cd == bd[m] && cj < bi[m]);
-    const float td = less ? bd[m] : cd;
-    const int tj = less ? bi[m] : cj;
-    bd[m] = less ? cd : bd[m];
-    bi[m] = less ? cj : bi[m];
-    cd = td;
-    cj = tj;
+    const double lo = __builtin_fmin(b[m], c);
+    c = __builtin_fmax(b[m], c);
+    b[m] = lo;
   }
 }
 
-// A query's results from its K best: nearest point, its distance and the
-// mean distance of the keff nearest; a1, a2 += the nearest distance and its square.
+// The value of the lane that a DPP control names.
+template <int CTRL>
+__device__ __forceinline__ double dc_dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+template <int K, int CTRL>
+__device__ __forceinline__ void dc_merge_dpp(double (&b)[K]) {
+  double o[K];
+#pragma unroll
+  for (int m = 0; m < K; ++m) o[m] = dc_dpp<CTRL>(b[m]);
+#pragma unroll
+  for (int m = 0; m < K; ++m) dc_insert<K>(b, o[m]);
+}
+
 template <int K>
-__device__ __forceinline__ void dc_finish(const float (&bd)[K], const int (&bi)[K], int keff, int qi,
-                                          int32_t* __restrict__ nn, float* __restrict__ dnn,
-                                          float* __restrict__ dbar, double& a1, double& a2) {
+__device__ __forceinline__ void dc_merge_shfl(double (&b)[K], int off) {
+  double o[K];
+#pragma unroll
+  for (int m = 0; m < K; ++m) o[m] = __shfl_xor(b[m], off, 64);
+#pragma unroll
+  for (int m = 0; m < K; ++m) dc_insert<K>(b, o[m]);
+}
+
+// The K best of 8 lanes' lists, in each of the 8.  (After the first two steps
+// the four lanes of a quad hold the same list, so the mirror of the eight
+// brings the other quad's.)
+template <int K>
+__device__ __forceinline__ void dc_merge8(double (&b)[K]) {
+  dc_merge_dpp<K, kDppXor1>(b);
+  dc_merge_dpp<K, kDppXor2>(b);
+  dc_merge_dpp<K, kDppHalfMirror>(b);
+}
+
+template <int K>
+__device__ __forceinline__ void dc_merge64(double (&b)[K]) {
+  dc_merge8<K>(b);
+  dc_merge_dpp<K, kDppMirror>(b);
+  dc_merge_shfl<K>(b, 16);
+  dc_merge_shfl<K>(b, 32);
+}
+
+// A query's results from its K best: nearest point, its distance and the mean
+// distance of the keff nearest (FP32: square roots summed in order, over
+// keff).  Returns the nearest distance.
+template <int K>
+__device__ __forceinline__ float dc_finish(const double (&b)[K], int keff, int qi, int32_t* __restrict__ nn,
+                                           float* __restrict__ dnn, float* __restrict__ dbar) {
   float sum = 0.0f;
 #pragma unroll
   for (int m = 0; m < K; ++m)
-    if (m < keff) sum = __fadd_rn(sum, sqrtf(bd[m]));
-  const float d0 = keff > 0 ? sqrtf(bd[0]) : 0.0f;
-  nn[qi] = keff > 0 ? bi[0] : -1;
+    if (m < keff) sum = __fadd_rn(sum, sqrtf(dc_key_d2(b[m])));
+  const float d0 = keff > 0 ? sqrtf(dc_key_d2(b[0])) : 0.0f;
+  nn[qi] = keff > 0 ? __double2loint(b[0]) : -1;
   dnn[qi] = d0;
   dbar[qi] = keff > 0 ? sum / static_cast<float>(keff) : 0.0f;
-  if (keff > 0) {
-    a1 += static_cast<double>(d0);
-    a2 += static_cast<double>(d0) * static_cast<double>(d0);
-  }
+  return d0;
 }
 
-// Wave sums of the nearest-distance statistics, one atomic per wave.
-__device__ __forceinline__ void dc_dsum(double a1, double a2, double* __restrict__ dsum) {
+// A workgroup's share of the statistics (from its 256 threads) into a slot:
+// one set of atomics per workgroup, spread over kDcSlots lines.
+template <bool COUNTS>
+__device__ __forceinline__ void dc_add_sums(unsigned long long c1, unsigned long long c2, double a1, double a2,
+                                            DcSums* __restrict__ sums) {
+  __shared__ DcSums s[4];
+#pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
+    if (COUNTS) {
+      c1 += __shfl_xor(c1, o, 64);
+      c2 += __shfl_xor(c2, o, 64);
+    }
     a1 += __shfl_xor(a1, o, 64);
     a2 += __shfl_xor(a2, o, 64);
   }
-  if ((threadIdx.x & 63) == 0 && (a1 != 0.0 || a2 != 0.0)) {
-    unsafeAtomicAdd(&dsum[0], a1);
-    unsafeAtomicAdd(&dsum[1], a2);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) s[wave] = DcSums{c1, c2, a1, a2, {}};
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) {
+      c1 += s[w].c1; c2 += s[w].c2; a1 += s[w].a1; a2 += s[w].a2;
+    }
+    DcSums* d = sums + blockIdx.x % kDcSlots;
+    if (COUNTS && c2) {
+      atomicAdd(&d->c1, c1);
+      atomicAdd(&d->c2, c2);
+    }
+    if (a2 != 0.0) {
+      unsafeAtomicAdd(&d->a1, a1);
+      unsafeAtomicAdd(&d->a2, a2);
+    }
   }
 }
 
-// The k nearest other points of every point, by (FP32 d2, index): nearest
-// point, its distance and the mean distance of the k (FP32: square roots
-// summed in order, over k); sums of the nearest distances for d_merge.
+// Points [x, y) in bucket order of the cells cx - R .. cx + R of row (cy, cz);
+// where the run wraps round the table y exceeds n, and position p >= n is p - n.
+__device__ __forceinline__ uint2 dc_run(const uint32_t* __restrict__ start, uint32_t T, int n, int cx, int cy, int cz,
+                                        int R) {
+  const uint32_t mask = T - 1u;
+  const uint32_t b0 = (dc_row(cy, cz) + static_cast<uint32_t>(cx - R)) & mask;
+  const uint32_t b1 = (b0 + 2u * static_cast<uint32_t>(R)) & mask;   // 2R + 1 < T buckets
+  const uint32_t s = start[b0];
+  const uint32_t e = b1 < mask ? start[b1 + 1u] : static_cast<uint32_t>(n);
+  return make_uint2(s, b1 < b0 ? e + static_cast<uint32_t>(n) : e);
+}
+
+__device__ __forceinline__ float4 dc_at(const float4* __restrict__ pts, uint32_t p, int n) {
+  return pts[min(p, p - static_cast<uint32_t>(n))];
+}
+
+// Densities and near neighbours, eight lanes per query over the nine runs of
+// its 27 cells: rho = other points within r, the sums of rho and rho^2, and
+// where the K nearest lie inside the 27 cells' guarantee the K-nearest results
+// (a query left goes to the wave kernel).
 template <int K>
-__global__ __launch_bounds__(256) void k_dc_knn(int n, const DcPoint* __restrict__ pts,
-                                                const uint32_t* __restrict__ start, uint32_t T, float h,
-                                                int32_t* __restrict__ nn, float* __restrict__ dnn,
-                                                float* __restrict__ dbar, double* __restrict__ dsum,
-                                                uint32_t* __restrict__ far, uint32_t* __restrict__ far_n) {
-  const int s = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void k_dc_near(int n, const float4* __restrict__ pts,
+                                                 const uint32_t* __restrict__ start, uint32_t T, float h, float inv_h,
+                                                 float r2, int32_t* __restrict__ rho, int32_t* __restrict__ nn,
+                                                 float* __restrict__ dnn, float* __restrict__ dbar,
+                                                 DcSums* __restrict__ sums, uint32_t* __restrict__ far,
+                                                 uint32_t* __restrict__ far_n) {
+  const int l = threadIdx.x & 7;
+  const int s = blockIdx.x * 32 + (threadIdx.x >> 3);
+  unsigned long long c1 = 0, c2 = 0;
   double a1 = 0.0, a2 = 0.0;
-  if (s < n) {
-    const DcPoint q = pts[s];
-    const int qi = __float_as_int(q.p.w);
-    const int keff = min(K, n - 1);
-    float bd[K];
-    int bi[K];
+  const bool live = s < n;
+  const float4 q = pts[live ? s : n - 1];
+  const int qi = __float_as_int(q.w);
+  const float fy = dc_floor(q.y, inv_h), fz = dc_floor(q.z, inv_h);
+  const int cx = static_cast<int>(dc_floor(q.x, inv_h)), cy = static_cast<int>(fy), cz = static_cast<int>(fz);
+  // run r = 3 (dz + 1) + dy + 1: lane l looks up run l, every lane the ninth
+  uint2 mine = dc_run(start, T, n, cx, cy + l % 3 - 1, cz + l / 3 - 1, 1);
+  uint2 last = dc_run(start, T, n, cx, cy + 1, cz + 1, 1);
+  if (!live) mine.y = mine.x, last.y = last.x;
+  double b[K];
 #pragma unroll
-    for (int m = 0; m < K; ++m) { bd[m] = 3.0e38f; bi[m] = 0x7fffffff; }
-    // fewer than K other points: no rings, straight to the scan of every point
-    bool done = false;
-    for (int R = 0; R < kDcRingsThread && !done && keff == K; ++R) {
-      for (int dz = -R; dz <= R; ++dz)
-        for (int dy = -R; dy <= R; ++dy)
-          for (int dx = -R; dx <= R; ++dx) {
-            if (max(max(abs(dx), abs(dy)), abs(dz)) != R) continue;   // the shell of ring R
-            const int cx = q.c.x + dx, cy = q.c.y + dy, cz = q.c.z + dz;
-            const uint32_t b = dc_hash(cx, cy, cz, T - 1u);
-            const uint32_t e = b + 1u < T ? start[b + 1u] : static_cast<uint32_t>(n);
-            for (uint32_t p = start[b]; p < e; ++p) {
-              const DcPoint o = pts[p];
-              const int oi = __float_as_int(o.p.w);
-              if (o.c.x != cx || o.c.y != cy || o.c.z != cz || oi == qi) continue;
-              dc_insert<K>(bd, bi, dc_d2(q.p, o.p), oi);
-            }
-          }
-      // every point closer than (R - 1/16) h has been seen; the K-th best
-      // (3e38 while fewer than K are held) must lie inside that
-      const float g = (static_cast<float>(R) - 0.0625f) * h;
-      if (g > 0.0f && bd[K - 1] <= g * g * 0.9999f) done = true;
-    }
-    if (!done) {
-      // far neighbours (or fewer than K points): the wave kernel goes on with this query
-      far[atomicAdd(far_n, 1u)] = static_cast<uint32_t>(s);
-    } else {
-      dc_finish<K>(bd, bi, keff, qi, nn, dnn, dbar, a1, a2);
+  for (int m = 0; m < K; ++m) b[m] = dc_empty();
+  int cnt = 0;
+  for (int r = 0; r < 9; ++r) {
+    const int src = (threadIdx.x & 56) | (r & 7);
+    const uint32_t p0 = r < 8 ? __shfl(mine.x, src, 64) : last.x;
+    const uint32_t p1 = r < 8 ? __shfl(mine.y, src, 64) : last.y;
+    const float wy = fy + static_cast<float>(r % 3 - 1), wz = fz + static_cast<float>(r / 3 - 1);
+    for (uint32_t p = p0 + l; p < p1; p += 8) {
+      const float4 o = dc_at(pts, p, n);
+      const int oi = __float_as_int(o.w);
+      const bool in = dc_floor(o.y, inv_h) == wy && dc_floor(o.z, inv_h) == wz && oi != qi;
+      const float d2 = in ? dc_d2(q, o) : kDcNone;
+      cnt += d2 <= r2 && in ? 1 : 0;
+      dc_insert<K>(b, dc_key(d2, oi));
     }
   }
-  dc_dsum(a1, a2, dsum);
-}
-
-// Cell t of the shell of ring R (Chebyshev offset exactly R), t < shell(R):
-// the two faces z = -R and z = +R ((2R+1)^2 cells each), then the ring of
-// the 2R-1 layers between them (8R cells each).
-__device__ __forceinline__ int3 dc_shell_cell(int R, int t) {
-  const int side = 2 * R + 1, face = side * side;
-  if (t < 2 * face) {
-    const int z = t < face ? -R : R;
-    const int u = t % face;
-    return make_int3(u % side - R, u / side - R, z);
+  dc_merge8<K>(b);
+  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppXor1, 0xf, 0xf, true);
+  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppXor2, 0xf, 0xf, true);
+  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppHalfMirror, 0xf, 0xf, true);
+  // every point closer than (1 - 1/16) h has been seen
+  const float g = 0.9375f * h;
+  const bool mineout = live && l == 0;
+  const bool done = n - 1 >= K && dc_key_d2(b[K - 1]) <= g * g * 0.9999f;
+  if (mineout) {
+    rho[qi] = cnt;
+    c1 = static_cast<unsigned long long>(cnt);
+    c2 = c1 * c1;
+    if (done) {
+      a1 = static_cast<double>(dc_finish<K>(b, K, qi, nn, dnn, dbar));
+      a2 = a1 * a1;
+    }
   }
-  t -= 2 * face;
-  const int per = 8 * R;
-  const int z = t / per - (R - 1);
-  int u = t % per;
-  // walk the square's boundary: bottom row, right column, top row, left column
-  if (u < side) return make_int3(u - R, -R, z);
-  u -= side;
-  if (u < side - 2) return make_int3(R, u - R + 1, z);
-  u -= side - 2;
-  if (u < side) return make_int3(R - u, R, z);
-  u -= side;
-  return make_int3(-R, R - 1 - u, z);
+  const uint64_t open = __ballot(mineout && !done);
+  if (open) {
+    uint32_t at = 0;
+    if ((threadIdx.x & 63) == 0) at = atomicAdd(far_n, static_cast<uint32_t>(__popcll(open)));
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (mineout && !done) far[at + __popcll(open & ((1ull << (threadIdx.x & 63)) - 1ull))] = static_cast<uint32_t>(s);
+  }
+  dc_add_sums<true>(c1, c2, a1, a2, sums);
 }
 
-__device__ __forceinline__ int dc_shell_size(int R) { return R == 0 ? 1 : (2 * R + 1) * (2 * R + 1) * 2 + 8 * R * (2 * R - 1); }
-
-// Queries the thread kernel left, one wave per query: rings 0-7, each ring's
-// cells dealt to the 64 lanes, each lane its own top-k; the wave stops once
-// K of the points its lanes hold lie inside the ring's guarantee.  Queries
-// still open go on to the all-points kernel.
+// Queries the 27 cells left, one wave per query: the cells up to R = 2, then
+// 4, then 7, their runs dealt to the lanes (two lanes to each of the 25 runs of
+// R = 2, where nine in ten end), each lane its own K best, merged over the wave;
+// the wave stops once the K lie inside R's guarantee.  Queries still open go on
+// to the all-points kernel.
 template <int K>
-__global__ __launch_bounds__(256) void k_dc_knn_wave(int n, const DcPoint* __restrict__ pts,
-                                                     const uint32_t* __restrict__ start, uint32_t T, float h,
+__global__ __launch_bounds__(256) void k_dc_knn_wave(int n, const float4* __restrict__ pts,
+                                                     const uint32_t* __restrict__ start, uint32_t T, float h, float inv_h,
                                                      const uint32_t* __restrict__ far, const uint32_t* __restrict__ far_n,
                                                      uint32_t* __restrict__ far2, uint32_t* __restrict__ far2_n,
                                                      int32_t* __restrict__ nn, float* __restrict__ dnn,
-                                                     float* __restrict__ dbar, double* __restrict__ dsum) {
-  __shared__ float s_d[4][64 * K];
-  __shared__ int s_i[4][64 * K];
+                                                     float* __restrict__ dbar, DcSums* __restrict__ sums) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t count = *far_n;
+  double a1 = 0.0, a2 = 0.0;
   for (uint32_t f = blockIdx.x * 4 + wave; f < count; f += gridDim.x * 4) {
-    const uint32_t slot = far[f];
-    const DcPoint q = pts[slot];
-    const int qi = __float_as_int(q.p.w);
-    float bd[K];
-    int bi[K];
-#pragma unroll
-    for (int m = 0; m < K; ++m) { bd[m] = 3.0e38f; bi[m] = 0x7fffffff; }
+    const uint32_t slot = __builtin_amdgcn_readfirstlane(far[f]);
+    const float4 q = pts[slot];
+    const int qi = __float_as_int(q.w);
+    const float fy = dc_floor(q.y, inv_h), fz = dc_floor(q.z, inv_h);
+    const int cx = static_cast<int>(dc_floor(q.x, inv_h)), cy = static_cast<int>(fy), cz = static_cast<int>(fz);
+    double b[K];
     bool done = false;
-    const bool enough = n - 1 >= K;
-    for (int R = 0; R < kDcRingsWave && !done && enough; ++R) {
-      const int cells = dc_shell_size(R);
-      for (int t = lane; t < cells; t += 64) {
-        const int3 d = dc_shell_cell(R, t);
-        const int cx = q.c.x + d.x, cy = q.c.y + d.y, cz = q.c.z + d.z;
-        const uint32_t b = dc_hash(cx, cy, cz, T - 1u);
-        const uint32_t e = b + 1u < T ? start[b + 1u] : static_cast<uint32_t>(n);
-        for (uint32_t p = start[b]; p < e; ++p) {
-          const DcPoint o = pts[p];
-          const int oi = __float_as_int(o.p.w);
-          if (o.c.x != cx || o.c.y != cy || o.c.z != cz || oi == qi) continue;
-          dc_insert<K>(bd, bi, dc_d2(q.p, o.p), oi);
+    for (int R = 2; R < 8 && !done && n - 1 >= K; R = R == 2 ? 4 : R + 3) {
+#pragma unroll
+      for (int m = 0; m < K; ++m) b[m] = dc_empty();
+      const int side = 2 * R + 1, per = R == 2 ? 2 : 1;
+      for (int t = lane; t < side * side * per; t += 64) {
+        const int u = t / per, dy = u % side - R, dz = u / side - R;
+        const uint2 run = dc_run(start, T, n, cx, cy + dy, cz + dz, R);
+        const float wy = fy + static_cast<float>(dy), wz = fz + static_cast<float>(dz);
+        for (uint32_t p = run.x + t % per; p < run.y; p += per) {
+          const float4 o = dc_at(pts, p, n);
+          const int oi = __float_as_int(o.w);
+          const bool in = dc_floor(o.y, inv_h) == wy && dc_floor(o.z, inv_h) == wz && oi != qi;
+          dc_insert<K>(b, dc_key(in ? dc_d2(q, o) : kDcNone, oi));
         }
       }
+      dc_merge64<K>(b);
       const float g = (static_cast<float>(R) - 0.0625f) * h;
-      if (g > 0.0f) {
-        const float g2 = g * g * 0.9999f;
-        int inside = 0;
-#pragma unroll
-        for (int m = 0; m < K; ++m) inside += __popcll(__ballot(bd[m] <= g2));
-        done = inside >= K;
+      done = dc_key_d2(b[K - 1]) <= g * g * 0.9999f;
+    }
+    if (lane == 0) {
+      if (done) {
+        const double d0 = static_cast<double>(dc_finish<K>(b, K, qi, nn, dnn, dbar));
+        a1 += d0;
+        a2 += d0 * d0;
+      } else {
+        far2[atomicAdd(far2_n, 1u)] = slot;
       }
     }
-    if (!done) {
-      if (lane == 0) far2[atomicAdd(far2_n, 1u)] = slot;
-      continue;
-    }
-#pragma unroll
-    for (int m = 0; m < K; ++m) {
-      s_d[wave][lane * K + m] = bd[m];
-      s_i[wave][lane * K + m] = bi[m];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane == 0) {
-      for (int l = 1; l < 64; ++l)
-        for (int m = 0; m < K; ++m) dc_insert<K>(bd, bi, s_d[wave][l * K + m], s_i[wave][l * K + m]);
-      double a1 = 0.0, a2 = 0.0;
-      dc_finish<K>(bd, bi, K, qi, nn, dnn, dbar, a1, a2);
-      unsafeAtomicAdd(&dsum[0], a1);
-      unsafeAtomicAdd(&dsum[1], a2);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
+  dc_add_sums<false>(0, 0, a1, a2, sums);
 }
 
-// The queries the ring search left: a workgroup per (query, range of points)
-// scans its range (each thread a strided share, its own top-k) and thread 0
-// merges the 256 lists in LDS; with S > 1 ranges the lists go to cand_d /
-// cand_i for k_dc_knn_far_merge, with one range the result is written here.
+// The queries the wave search left (fewer than K other points: every query): a
+// workgroup per (query, range of points) scans its range (each thread a strided
+// share, its own K best) and merges the 256 lists; with S > 1 ranges the lists
+// go to cand for k_dc_knn_far_merge, with one range the result is written here.
 // Splitting keeps a few isolated queries from each holding one workgroup
 // over every point (at 1M Gaussians, 44 queries took 1.7 ms that way).
 template <int K>
-__global__ __launch_bounds__(256) void k_dc_knn_far(int n, const DcPoint* __restrict__ pts,
+__global__ __launch_bounds__(256) void k_dc_knn_far(int n, const float4* __restrict__ pts,
                                                     const uint32_t* __restrict__ far, const uint32_t* __restrict__ far_n,
                                                     int32_t* __restrict__ nn, float* __restrict__ dnn,
-                                                    float* __restrict__ dbar, double* __restrict__ dsum,
-                                                    float* __restrict__ cand_d, int32_t* __restrict__ cand_i) {
-  __shared__ float s_d[256 * K];
-  __shared__ int s_i[256 * K];
+                                                    float* __restrict__ dbar, DcSums* __restrict__ sums,
+                                                    double* __restrict__ cand) {
+  __shared__ double s_b[4][K];
   const uint32_t count = *far_n;
   const uint32_t S = far_splits(count);
   const uint32_t span = (static_cast<uint32_t>(n) + S - 1u) / S;
   // items (query f, range r): points [r span, (r + 1) span)
   for (uint32_t it = blockIdx.x; it < count * S; it += gridDim.x) {
     const uint32_t f = it / S, r = it - f * S;
-    const DcPoint q = pts[far[f]];
-    const int qi = __float_as_int(q.p.w);
-    float bd[K];
-    int bi[K];
+    const float4 q = pts[far[f]];
+    const int qi = __float_as_int(q.w);
+    double b[K];
 #pragma unroll
-    for (int m = 0; m < K; ++m) { bd[m] = 3.0e38f; bi[m] = 0x7fffffff; }
+    for (int m = 0; m < K; ++m) b[m] = dc_empty();
     const int p0 = static_cast<int>(r * span), p1 = min(n, static_cast<int>((r + 1u) * span));
     for (int p = p0 + threadIdx.x; p < p1; p += 256) {
-      const DcPoint o = pts[p];
-      const int oi = __float_as_int(o.p.w);
-      if (oi != qi) dc_insert<K>(bd, bi, dc_d2(q.p, o.p), oi);
+      const float4 o = pts[p];
+      const int oi = __float_as_int(o.w);
+      dc_insert<K>(b, dc_key(oi != qi ? dc_d2(q, o) : kDcNone, oi));
     }
+    dc_merge64<K>(b);
+    if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-    for (int m = 0; m < K; ++m) {
-      s_d[threadIdx.x * K + m] = bd[m];
-      s_i[threadIdx.x * K + m] = bi[m];
+      for (int m = 0; m < K; ++m) s_b[threadIdx.x >> 6][m] = b[m];
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-      for (int t = 1; t < 256; ++t)
-        for (int m = 0; m < K; ++m) dc_insert<K>(bd, bi, s_d[t * K + m], s_i[t * K + m]);
+      for (int w = 1; w < 4; ++w)
+        for (int m = 0; m < K; ++m) dc_insert<K>(b, s_b[w][m]);
       if (S == 1) {
-        double a1 = 0.0, a2 = 0.0;
-        dc_finish<K>(bd, bi, min(K, n - 1), qi, nn, dnn, dbar, a1, a2);
-        if (a1 != 0.0 || a2 != 0.0) {
-          unsafeAtomicAdd(&dsum[0], a1);
-          unsafeAtomicAdd(&dsum[1], a2);
-        }
+        const double d0 = static_cast<double>(dc_finish<K>(b, min(K, n - 1), qi, nn, dnn, dbar));
+        unsafeAtomicAdd(&sums[blockIdx.x % kDcSlots].a1, d0);
+        unsafeAtomicAdd(&sums[blockIdx.x % kDcSlots].a2, d0 * d0);
       } else {
 #pragma unroll
-        for (int m = 0; m < K; ++m) {
-          cand_d[static_cast<size_t>(it) * 8 + m] = bd[m];
-          cand_i[static_cast<size_t>(it) * 8 + m] = bi[m];
-        }
+        for (int m = 0; m < K; ++m) cand[static_cast<size_t>(it) * 8 + m] = b[m];
       }
     }
     __syncthreads();
@@ -506,85 +491,80 @@ __global__ __launch_bounds__(256) void k_dc_knn_far(int n, const DcPoint* __rest
 
 // Merge of the split far search: query f's K nearest among its S ranges'
 // lists, in (distance, index) order as every search keeps them.  One wave per
-// query: lane r takes range r's list (r < S <= 64), then a butterfly over the
-// lanes merges the lists pairwise (exact: the order is total).
+// query: lane r takes range r's list (r < S <= 64), and the lists are merged
+// over the wave (exact: the order is total).
 template <int K>
-__global__ __launch_bounds__(64) void k_dc_knn_far_merge(int n, const DcPoint* __restrict__ pts,
+__global__ __launch_bounds__(64) void k_dc_knn_far_merge(int n, const float4* __restrict__ pts,
                                                          const uint32_t* __restrict__ far,
                                                          const uint32_t* __restrict__ far_n, int32_t* __restrict__ nn,
                                                          float* __restrict__ dnn, float* __restrict__ dbar,
-                                                         double* __restrict__ dsum, const float* __restrict__ cand_d,
-                                                         const int32_t* __restrict__ cand_i) {
+                                                         DcSums* __restrict__ sums, const double* __restrict__ cand) {
   const uint32_t count = *far_n;
   const uint32_t S = far_splits(count);
   if (S == 1u) return;
   const uint32_t lane = threadIdx.x;
   for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
-    float bd[K];
-    int bi[K];
+    double b[K];
 #pragma unroll
-    for (int m = 0; m < K; ++m) {
-      const size_t o = (static_cast<size_t>(f) * S + lane) * 8 + m;
-      bd[m] = lane < S ? cand_d[o] : 3.0e38f;
-      bi[m] = lane < S ? cand_i[o] : 0x7fffffff;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      float od[K];
-      int oi[K];
-#pragma unroll
-      for (int m = 0; m < K; ++m) {
-        od[m] = __shfl_xor(bd[m], off, 64);
-        oi[m] = __shfl_xor(bi[m], off, 64);
-      }
-#pragma unroll
-      for (int m = 0; m < K; ++m) dc_insert<K>(bd, bi, od[m], oi[m]);
-    }
+    for (int m = 0; m < K; ++m) b[m] = lane < S ? cand[(static_cast<size_t>(f) * S + lane) * 8 + m] : dc_empty();
+    dc_merge64<K>(b);
     if (lane == 0) {
-      const int qi = __float_as_int(pts[far[f]].p.w);
-      double a1 = 0.0, a2 = 0.0;
-      dc_finish<K>(bd, bi, min(K, n - 1), qi, nn, dnn, dbar, a1, a2);
-      if (a1 != 0.0 || a2 != 0.0) {
-        unsafeAtomicAdd(&dsum[0], a1);
-        unsafeAtomicAdd(&dsum[1], a2);
-      }
+      const int qi = __float_as_int(pts[far[f]].w);
+      const double d0 = static_cast<double>(dc_finish<K>(b, min(K, n - 1), qi, nn, dnn, dbar));
+      unsafeAtomicAdd(&sums[f % kDcSlots].a1, d0);
+      unsafeAtomicAdd(&sums[f % kDcSlots].a2, d0 * d0);
     }
   }
 }
 
-// d_merge = mu_d + gamma sigma_d over the nearest-neighbour distances.
-__global__ void k_dc_merge_radius(int n, const double* __restrict__ dsum, double gamma, double* __restrict__ stat) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int m = n > 1 ? n : 0;
-  const double dn = static_cast<double>(m);
-  const double mu = m ? dsum[0] / dn : 0.0;
-  const double var = m ? dsum[1] / dn - mu * mu : 0.0;
-  const double sigma = sqrt(var > 0.0 ? var : 0.0);
-  stat[4] = mu;
-  stat[5] = sigma;
-  stat[6] = mu + gamma * sigma;
-}
-
-// Classes and the merge pairing: keep[i] = 0 for the higher index of a
-// merged pair, low[i] = 1 for a point that spawns a new one.
+// The thresholds from the statistics' sums (every wave adds the slots up by
+// itself, in the same order): mu = S1/n, sigma = sqrt(max(S2/n - mu^2, 0)),
+// rho_low = mu - alpha sigma, rho_high = mu + beta sigma from the exact integer
+// sums in FP64 with correctly rounded operations, and d_merge = mu_d + gamma
+// sigma_d over the nearest distances; then each point's class and the merge
+// pairing: pos[i] = 0 for the higher index of a merged pair, pos[n + i] = 1 for
+// a point that spawns a new one.
 __global__ __launch_bounds__(256) void k_dc_classify(int n, const int32_t* __restrict__ rho,
                                                      const int32_t* __restrict__ nn, const float* __restrict__ dnn,
-                                                     const double* __restrict__ stat, uint32_t* __restrict__ keep,
-                                                     uint32_t* __restrict__ low, int32_t* __restrict__ partner,
+                                                     const DcSums* __restrict__ sums, double alpha, double beta,
+                                                     double gamma, DcReport* __restrict__ rep,
+                                                     uint32_t* __restrict__ pos, int32_t* __restrict__ partner,
                                                      uint8_t* __restrict__ cls_out) {
+  const DcSums mine = sums[threadIdx.x & (kDcSlots - 1u)];
+  unsigned long long c1 = mine.c1, c2 = mine.c2;
+  double a1 = mine.a1, a2 = mine.a2;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    c1 += __shfl_xor(c1, o, 64);
+    c2 += __shfl_xor(c2, o, 64);
+    a1 += __shfl_xor(a1, o, 64);
+    a2 += __shfl_xor(a2, o, 64);
+  }
+  const double dn = static_cast<double>(n);
+  const double mu = __ddiv_rn(static_cast<double>(c1), dn);
+  const double var = __dsub_rn(__ddiv_rn(static_cast<double>(c2), dn), __dmul_rn(mu, mu));
+  const double sigma = __dsqrt_rn(var > 0.0 ? var : 0.0);
+  const double lo = __dsub_rn(mu, __dmul_rn(alpha, sigma)), hi = __dadd_rn(mu, __dmul_rn(beta, sigma));
+  const double mud = n > 1 ? a1 / dn : 0.0;
+  const double vard = n > 1 ? a2 / dn - mud * mud : 0.0;
+  const double sigmad = sqrt(vard > 0.0 ? vard : 0.0);
+  const double dm = mud + gamma * sigmad;
   const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) {
+    rep->stat[0] = mu; rep->stat[1] = sigma; rep->stat[2] = lo; rep->stat[3] = hi;
+    rep->stat[4] = mud; rep->stat[5] = sigmad; rep->stat[6] = dm;
+  }
   if (i >= n) return;
-  const double lo = stat[2], hi = stat[3], dm = stat[6];
   auto cls = [&](int k) -> int {
     const double r = static_cast<double>(rho[k]);
     return r < lo ? 1 : (r > hi ? 2 : 0);
   };
   const int c = cls(i);
   const int j = nn[i];
-  const bool pair = c == 2 && j >= 0 && cls(j) == 2 && nn[j] == i && static_cast<double>(dnn[i]) <= dm;
+  const bool pair = c == 2 && j >= 0 && j < n && cls(j) == 2 && nn[j] == i && static_cast<double>(dnn[i]) <= dm;
   partner[i] = pair ? j : -1;
-  keep[i] = (pair && j < i) ? 0u : 1u;
-  low[i] = c == 1 ? 1u : 0u;
+  pos[i] = (pair && j < i) ? 0u : 1u;
+  pos[static_cast<int64_t>(n) + i] = c == 1 ? 1u : 0u;
   if (cls_out) cls_out[i] = static_cast<uint8_t>(c);
 }
 
@@ -598,30 +578,55 @@ struct DcArrays {
   int nsh;  // 3 (D + 1)^2
 };
 
+constexpr int kDcComps = 12;   // spherical-harmonics planes that a workgroup of k_dc_write copies
+
 // Output of every point: its own values, a merged pair's (at the lower index),
-// and a new point next to each sparse point (after all kept points).
-__global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint32_t* __restrict__ keep_pos,
-                                                  const uint32_t* __restrict__ low_pos,
+// and a new point next to each sparse point (after all kept points).  Workgroup
+// row 0 writes the geometry, row y > 0 the colour planes 12 (y - 1) to 12 y - 1.
+__global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint32_t* __restrict__ pos,
                                                   const int32_t* __restrict__ partner, const float* __restrict__ dbar,
                                                   const float* __restrict__ noise, float spread, float jitter,
-                                                  const unsigned long long* __restrict__ total,
-                                                  int32_t* __restrict__ fate) {
+                                                  DcReport* __restrict__ rep, int32_t* __restrict__ fate) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
+  const int64_t N = n, cap = A.cap;
   const int j = partner[i];
   const bool kept = !(j >= 0 && j < i);
-  const int64_t cap = A.cap;
-  const int64_t o = static_cast<int64_t>(keep_pos[i]);
+  const int64_t o = static_cast<int64_t>(pos[i]);
+  // where a new point goes; the flag itself is recovered from the next prefix (or the total)
+  const int64_t q = static_cast<int64_t>(pos[N + i]);
+  const int64_t next = i + 1 < n ? static_cast<int64_t>(pos[N + i + 1]) : static_cast<int64_t>(rep->total);
+  const bool put = kept && o < cap, spawn = next > q && q < cap;
+  if (blockIdx.y > 0) {
+    const int c0 = (static_cast<int>(blockIdx.y) - 1) * kDcComps, c1 = min(c0 + kDcComps, A.nsh);
+    if (put && j >= 0) {
+      const float oi = dc_sigmoid(A.logits[i]), oj = dc_sigmoid(A.logits[j]);
+      const float w = oi + oj;
+      for (int c = c0; c < c1; ++c) A.o_sh[c * cap + o] = (oi * A.sh[c * N + i] + oj * A.sh[c * N + j]) / w;
+    }
+    const bool copy = put && j < 0;
+    if (copy || spawn) {
+      float v[kDcComps];
+#pragma unroll
+      for (int c = 0; c < kDcComps; ++c) v[c] = c0 + c < c1 ? A.sh[(c0 + c) * N + i] : 0.0f;
+#pragma unroll
+      for (int c = 0; c < kDcComps; ++c) {
+        if (copy && c0 + c < c1) A.o_sh[(c0 + c) * cap + o] = v[c];
+        if (spawn && c0 + c < c1) A.o_sh[(c0 + c) * cap + q] = v[c];
+      }
+    }
+    return;
+  }
+  if (i == 0) rep->kept = pos[N];
   if (fate) fate[i] = kept ? static_cast<int32_t>(o) : -1;
-  if (kept && o < cap) {
+  if (put) {
     if (j < 0) {
       for (int c = 0; c < 3; ++c) {
-        A.o_means[c * cap + o] = A.means[c * static_cast<int64_t>(n) + i];
-        A.o_ls[c * cap + o] = A.ls[c * static_cast<int64_t>(n) + i];
+        A.o_means[c * cap + o] = A.means[c * N + i];
+        A.o_ls[c * cap + o] = A.ls[c * N + i];
       }
-      for (int c = 0; c < 4; ++c) A.o_quats[c * cap + o] = A.quats[c * static_cast<int64_t>(n) + i];
+      for (int c = 0; c < 4; ++c) A.o_quats[c * cap + o] = A.quats[c * N + i];
       A.o_logits[o] = A.logits[i];
-      for (int c = 0; c < A.nsh; ++c) A.o_sh[c * cap + o] = A.sh[static_cast<int64_t>(c) * n + i];
     } else {
       // merge with j (j > i): opacity-weighted position and colour, mean
       // scale, accumulated opacity, the more opaque one's rotation
@@ -629,37 +634,25 @@ __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint3
       const float oi = dc_sigmoid(li), oj = dc_sigmoid(lj);
       const float w = oi + oj;
       for (int c = 0; c < 3; ++c) {
-        A.o_means[c * cap + o] = (oi * A.means[c * static_cast<int64_t>(n) + i] + oj * A.means[c * static_cast<int64_t>(n) + j]) / w;
-        A.o_ls[c * cap + o] = logf(0.5f * (expf(A.ls[c * static_cast<int64_t>(n) + i]) + expf(A.ls[c * static_cast<int64_t>(n) + j])));
+        A.o_means[c * cap + o] = (oi * A.means[c * N + i] + oj * A.means[c * N + j]) / w;
+        A.o_ls[c * cap + o] = logf(0.5f * (expf(A.ls[c * N + i]) + expf(A.ls[c * N + j])));
       }
       const int qs = oj > oi ? j : i;
-      for (int c = 0; c < 4; ++c) A.o_quats[c * cap + o] = A.quats[c * static_cast<int64_t>(n) + qs];
+      for (int c = 0; c < 4; ++c) A.o_quats[c * cap + o] = A.quats[c * N + qs];
       // logit of 1 - (1 - oi)(1 - oj): log(o) + softplus(li) + softplus(lj)
       A.o_logits[o] = logf(oi + oj - oi * oj) + dc_softplus(li) + dc_softplus(lj);
-      for (int c = 0; c < A.nsh; ++c) {
-        const int64_t ci = static_cast<int64_t>(c) * n;
-        A.o_sh[c * cap + o] = (oi * A.sh[ci + i] + oj * A.sh[ci + j]) / w;
-      }
     }
   }
-  const int64_t nl = static_cast<int64_t>(low_pos[i]);
-  // low points: low_pos is the exclusive prefix of the low flags; the flag
-  // itself is recovered from the next prefix (or the total)
-  const int64_t next = i + 1 < n ? static_cast<int64_t>(low_pos[i + 1]) : static_cast<int64_t>(total[1]);
-  if (next > nl) {
-    const int64_t q = static_cast<int64_t>(total[0]) + nl;
-    if (q < cap) {
-      const float t = __fmul_rn(spread, dbar[i]);
-      for (int c = 0; c < 3; ++c) {
-        float p = __fadd_rn(A.means[c * static_cast<int64_t>(n) + i], __fmul_rn(t, noise[c * static_cast<int64_t>(n) + i]));
-        p = __fadd_rn(p, __fmul_rn(jitter, noise[(3 + c) * static_cast<int64_t>(n) + i]));
-        A.o_means[c * cap + q] = p;
-        A.o_ls[c * cap + q] = A.ls[c * static_cast<int64_t>(n) + i];
-      }
-      for (int c = 0; c < 4; ++c) A.o_quats[c * cap + q] = A.quats[c * static_cast<int64_t>(n) + i];
-      A.o_logits[q] = A.logits[i];
-      for (int c = 0; c < A.nsh; ++c) A.o_sh[c * cap + q] = A.sh[static_cast<int64_t>(c) * n + i];
+  if (spawn) {
+    const float t = __fmul_rn(spread, dbar[i]);
+    for (int c = 0; c < 3; ++c) {
+      float p = __fadd_rn(A.means[c * N + i], __fmul_rn(t, noise[c * N + i]));
+      p = __fadd_rn(p, __fmul_rn(jitter, noise[(3 + c) * N + i]));
+      A.o_means[c * cap + q] = p;
+      A.o_ls[c * cap + q] = A.ls[c * N + i];
     }
+    for (int c = 0; c < 4; ++c) A.o_quats[c * cap + q] = A.quats[c * N + i];
+    A.o_logits[q] = A.logits[i];
   }
 }
 
@@ -674,35 +667,29 @@ gs_status launch_density_control(const gs_gaussians& g, const gs_density_params&
   const float r2 = prm.radius * prm.radius;  // r r, rounded once
   const unsigned gn = static_cast<unsigned>(std::max<int64_t>(ceil_div(n, 256), 1));
   gs_status st;
-  { TimedLaunch t("k_dc_clear", s); k_dc_clear<<<static_cast<unsigned>(ceil_div(T, 256)), 256, 0, s>>>(w.count, w.fill, T, w.isum, w.dsum,
-                                                                                               w.total, w.range, w.far_n, w.far2_n); }
-  if ((st = check_launch("k_dc_clear")) != GS_OK) return st;
+  DcReport r{};
   if (n > 0) {
-    { TimedLaunch t("k_dc_cells", s); k_dc_cells<<<gn, 256, 0, s>>>(n, g.means, inv_h, T - 1u, w.cell, w.count, w.range); }
+    { TimedLaunch t("k_dc_clear", s); k_dc_clear<<<static_cast<unsigned>(ceil_div(T, 256)), 256, 0, s>>>(w.count, T, w.sums, w.rep,
+                                                                                                 w.far_n, w.far2_n); }
+    if ((st = check_launch("k_dc_clear")) != GS_OK) return st;
+    { TimedLaunch t("k_dc_cells", s); k_dc_cells<<<gn, 256, 0, s>>>(n, g.means, inv_h, T - 1u, w.cell, w.count, w.rep); }
     if ((st = check_launch("k_dc_cells")) != GS_OK) return st;
-    if ((st = launch_exclusive_scan(w.count, w.count, T, w.sums, nullptr, s)) != GS_OK) return st;
-    { TimedLaunch t("k_dc_scatter", s); k_dc_scatter<<<gn, 256, 0, s>>>(n, g.means, w.cell, w.count, w.fill, w.pts); }
+    if ((st = launch_exclusive_scan(w.count, w.count, T, w.scan, nullptr, s)) != GS_OK) return st;
+    { TimedLaunch t("k_dc_scatter", s); k_dc_scatter<<<gn, 256, 0, s>>>(n, g.means, w.cell, w.count, w.pts); }
     if ((st = check_launch("k_dc_scatter")) != GS_OK) return st;
-    { TimedLaunch t("k_dc_density", s); k_dc_density<<<gn, 256, 0, s>>>(n, w.pts, w.count, T, r2, w.rho, w.isum); }
-    if ((st = check_launch("k_dc_density")) != GS_OK) return st;
-  }
-  { TimedLaunch t("k_dc_thresholds", s); k_dc_thresholds<<<1, 64, 0, s>>>(n, w.isum, static_cast<double>(prm.alpha),
-                                                                         static_cast<double>(prm.beta), w.stat); }
-  if ((st = check_launch("k_dc_thresholds")) != GS_OK) return st;
-  if (n > 0) {
-#define GS_DC_KNN(K)                                                                                             \
-  {                                                                                                              \
-    { TimedLaunch t("k_dc_knn<" #K ">", s);                                                                     \
-      k_dc_knn<K><<<gn, 256, 0, s>>>(n, w.pts, w.count, T, h, w.nn, w.dnn, w.dbar, w.dsum, w.far, w.far_n); }   \
-    { TimedLaunch t("k_dc_knn_wave<" #K ">", s);                                                                \
-      k_dc_knn_wave<K><<<2048, 256, 0, s>>>(n, w.pts, w.count, T, h, w.far, w.far_n, w.far2, w.far2_n, w.nn,      \
-                                            w.dnn, w.dbar, w.dsum); }                                             \
-    { TimedLaunch t("k_dc_knn_far<" #K ">", s);                                                                 \
-      k_dc_knn_far<K><<<1024, 256, 0, s>>>(n, w.pts, w.far2, w.far2_n, w.nn, w.dnn, w.dbar, w.dsum, w.cand_d,     \
-                                           w.cand_i); }                                                          \
-    { TimedLaunch t("k_dc_knn_far_merge<" #K ">", s);                                                           \
-      k_dc_knn_far_merge<K><<<256, 64, 0, s>>>(n, w.pts, w.far2, w.far2_n, w.nn, w.dnn, w.dbar, w.dsum, w.cand_d,  \
-                                              w.cand_i); }                                                       \
+#define GS_DC_KNN(K)                                                                                              \
+  {                                                                                                               \
+    { TimedLaunch t("k_dc_near<" #K ">", s);                                                                      \
+      k_dc_near<K><<<static_cast<unsigned>(ceil_div(n, 32)), 256, 0, s>>>(n, w.pts, w.count, T, h, inv_h, r2, w.rho, \
+                                                                          w.nn, w.dnn, w.dbar, w.sums, w.far,     \
+                                                                          w.far_n); }                             \
+    { TimedLaunch t("k_dc_knn_wave<" #K ">", s);                                                                  \
+      k_dc_knn_wave<K><<<2048, 256, 0, s>>>(n, w.pts, w.count, T, h, inv_h, w.far, w.far_n, w.far2, w.far2_n,     \
+                                            w.nn, w.dnn, w.dbar, w.sums); }                                       \
+    { TimedLaunch t("k_dc_knn_far<" #K ">", s);                                                                   \
+      k_dc_knn_far<K><<<1024, 256, 0, s>>>(n, w.pts, w.far2, w.far2_n, w.nn, w.dnn, w.dbar, w.sums, w.cand); }    \
+    { TimedLaunch t("k_dc_knn_far_merge<" #K ">", s);                                                             \
+      k_dc_knn_far_merge<K><<<256, 64, 0, s>>>(n, w.pts, w.far2, w.far2_n, w.nn, w.dnn, w.dbar, w.sums, w.cand); }  \
   }
     switch (prm.knn) {
       case 1: GS_DC_KNN(1); break;
@@ -716,16 +703,12 @@ gs_status launch_density_control(const gs_gaussians& g, const gs_density_params&
     }
 #undef GS_DC_KNN
     if ((st = check_launch("k_dc_knn")) != GS_OK) return st;
-  }
-  { TimedLaunch t("k_dc_merge_radius", s); k_dc_merge_radius<<<1, 64, 0, s>>>(n, w.dsum, static_cast<double>(prm.gamma), w.stat); }
-  if ((st = check_launch("k_dc_merge_radius")) != GS_OK) return st;
-  int64_t kept = 0, nlow = 0;
-  if (n > 0) {
-    { TimedLaunch t("k_dc_classify", s); k_dc_classify<<<gn, 256, 0, s>>>(n, w.rho, w.nn, w.dnn, w.stat, w.keep, w.low, w.partner,
-                                                                       pts_out ? pts_out->cls : nullptr); }
+    { TimedLaunch t("k_dc_classify", s);
+      k_dc_classify<<<gn, 256, 0, s>>>(n, w.rho, w.nn, w.dnn, w.sums, static_cast<double>(prm.alpha),
+                                       static_cast<double>(prm.beta), static_cast<double>(prm.gamma), w.rep, w.pos,
+                                       w.partner, pts_out ? pts_out->cls : nullptr); }
     if ((st = check_launch("k_dc_classify")) != GS_OK) return st;
     if (pts_out) {
-      // the per-point statistics, before the scans overwrite the flags
       if (pts_out->rho && (st = check_hip(hipMemcpyAsync(pts_out->rho, w.rho, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s),
                                           "hipMemcpyAsync(rho)")) != GS_OK) return st;
       if (pts_out->nn && (st = check_hip(hipMemcpyAsync(pts_out->nn, w.nn, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s),
@@ -733,41 +716,33 @@ gs_status launch_density_control(const gs_gaussians& g, const gs_density_params&
       if (pts_out->dbar && (st = check_hip(hipMemcpyAsync(pts_out->dbar, w.dbar, sizeof(float) * n, hipMemcpyDeviceToDevice, s),
                                            "hipMemcpyAsync(dbar)")) != GS_OK) return st;
     }
-    if ((st = launch_exclusive_scan(w.keep, w.keep, n, w.sums, &w.total[0], s)) != GS_OK) return st;
-    if ((st = launch_exclusive_scan(w.low, w.low, n, w.sums, &w.total[1], s)) != GS_OK) return st;
+    if ((st = launch_exclusive_scan(w.pos, w.pos, 2 * static_cast<int64_t>(n), w.scan, &w.rep->total, s)) != GS_OK) return st;
     DcArrays A{g.means, g.log_scales, g.quats, g.logits, g.sh,
                out.means, out.log_scales, out.quats, out.logits, out.sh, cap, 3 * (g.sh_degree + 1) * (g.sh_degree + 1)};
-    { TimedLaunch t("k_dc_write", s); k_dc_write<<<gn, 256, 0, s>>>(n, A, w.keep, w.low, w.partner, w.dbar, noise, prm.spread, prm.jitter,
-                                                                 w.total, pts_out ? pts_out->fate : nullptr); }
+    const dim3 gw(gn, 1u + static_cast<unsigned>(ceil_div(A.nsh, kDcComps)));
+    { TimedLaunch t("k_dc_write", s); k_dc_write<<<gw, 256, 0, s>>>(n, A, w.pos, w.partner, w.dbar, noise, prm.spread, prm.jitter,
+                                                                 w.rep, pts_out ? pts_out->fate : nullptr); }
     if ((st = check_launch("k_dc_write")) != GS_OK) return st;
-    unsigned long long tot[2] = {0, 0};
-    uint32_t range = 0;
-    if ((st = check_hip(hipMemcpyAsync(tot, w.total, sizeof tot, hipMemcpyDeviceToHost, s), "hipMemcpyAsync(total)")) != GS_OK)
-      return st;
-    if ((st = check_hip(hipMemcpyAsync(&range, w.range, sizeof range, hipMemcpyDeviceToHost, s), "hipMemcpyAsync(range)")) != GS_OK)
-      return st;
-    double stat[8];
-    if ((st = check_hip(hipMemcpyAsync(stat, w.stat, sizeof stat, hipMemcpyDeviceToHost, s), "hipMemcpyAsync(stat)")) != GS_OK)
+    if ((st = check_hip(hipMemcpyAsync(&r, w.rep, sizeof r, hipMemcpyDeviceToHost, s), "hipMemcpyAsync(report)")) != GS_OK)
       return st;
     if ((st = check_hip(hipStreamSynchronize(s), "hipStreamSynchronize")) != GS_OK) return st;
-    if (range)
+    if (r.range)
       return fail(GS_ERR_UNSUPPORTED, "gs_density_control: a coordinate is not finite or lies 2^18 cells (of 1.07 r) "
                                       "or more from the origin; the outputs are undefined");
-    kept = static_cast<int64_t>(tot[0]);
-    nlow = static_cast<int64_t>(tot[1]);
     if (rep) {
-      rep->rho_mean = stat[0]; rep->rho_std = stat[1]; rep->rho_low = stat[2]; rep->rho_high = stat[3];
-      rep->d_mean = stat[4]; rep->d_std = stat[5]; rep->d_merge = stat[6];
+      rep->rho_mean = r.stat[0]; rep->rho_std = r.stat[1]; rep->rho_low = r.stat[2]; rep->rho_high = r.stat[3];
+      rep->d_mean = r.stat[4]; rep->d_std = r.stat[5]; rep->d_merge = r.stat[6];
     }
   }
+  const int64_t kept = static_cast<int64_t>(r.kept), total = static_cast<int64_t>(r.total);
   if (rep) {
     rep->n_in = n;
     rep->n_merged = n - kept;
-    rep->n_new = nlow;
-    rep->n_out = kept + nlow;
+    rep->n_new = total - kept;
+    rep->n_out = total;
   }
-  if (kept + nlow > cap)
-    return fail(GS_ERR_CAPACITY, "gs_density_control: the output needs " + std::to_string(kept + nlow) +
+  if (total > cap)
+    return fail(GS_ERR_CAPACITY, "gs_density_control: the output needs " + std::to_string(total) +
                                      " Gaussians, the capacity is " + std::to_string(cap));
   return GS_OK;
 }

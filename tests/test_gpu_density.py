@@ -157,3 +157,28 @@ def test_density_control_reports_capacity(gs):
     with pytest.raises(gs.GsError) as e:
         _run(gs, scene, prm, noise, capacity=rep["n_out"] - 1)
     assert e.value.status == gs.GS_ERR_CAPACITY and e.value.report["n_out"] == rep["n_out"]
+
+
+@pytest.mark.parametrize("n,knn,radius,copies,stretch", [
+    (1, 3, 0.1, 1, 1), (2, 1, 0.5, 1, 1), (3, 3, 0.5, 1, 1), (4, 3, 0.5, 1, 1), (9, 8, 0.1, 1, 1),   # n - 1 around k
+    (31, 2, 0.3, 1, 1), (33, 7, 0.3, 1, 1), (257, 4, 0.2, 1, 1),                                    # blocks of 32 queries
+    (2000, 3, 0.3, 1, 1), (2000, 6, 0.06, 1, 1), (2000, 1, 0.03, 1, 1), (2000, 8, 0.018, 1, 1),     # every reach
+    (1500, 3, 0.1, 5, 1), (1200, 2, 0.02, 3, 1),                                                    # coincident points
+    (400, 3, 0.05, 1, 300),                                                 # rows longer than the table of cells
+])
+def test_density_control_searches_at_their_edges(gs, n, knn, radius, copies, stretch):
+    """Everything decided from the searches is exact: equal to the oracle's, no tolerance."""
+    scene = scenes.uniform_scene(n, 17 + n, sh_degree=0)
+    scene.means[:, :] = np.repeat(scene.means[:, :-(-n // copies)], copies, axis=1)[:, :n]
+    scene.means[0] *= stretch
+    say(f"[density edges] n={n} k={knn} r={radius} copies={copies} stretch={stretch}")
+    prm = _prm(radius, knn=knn)
+    noise = scenes.density_noise(n, 5)
+    rep, pts, _ = _run(gs, scene, prm, noise)
+    o = oracle.density_control(scene, _oracle_prm(prm), noise)
+    assert np.array_equal(pts["rho"], o["rho"]), "densities"
+    assert np.array_equal(pts["nn"].astype(np.int64), o["nn"]), "nearest neighbours"
+    assert np.array_equal(pts["dbar"], o["dbar"]), "mean k-nearest distances"
+    assert np.array_equal(pts["cls"].astype(np.int8), o["cls"]), "classes"
+    assert rep["n_new"] == int((o["cls"] == 1).sum())
+    assert rep["d_mean"] == pytest.approx(o["stats"]["mu_d"], rel=1e-12)
