@@ -17,14 +17,15 @@
 // another lies in the same or an adjacent cell (27 cells cover the radius
 // search), and after the cells up to Chebyshev offset R have been scanned
 // every point closer than (R - 1/16) h has been seen (the k-nearest search
-// stops on that guarantee).  One pass over the 27 cells, eight lanes per query,
+// stops on that guarantee).  One pass over the 27 cells, four lanes per query,
 // gives a query's density and the k nearest of them; a query whose k-th nearest
 // lies farther (one in seven at a 100x density skew with 20 neighbours in r)
-// goes on to a wave of its own that scans R = 2, 4 and 7, and the few left
-// after that to workgroups that scan every point.
-// Rows can share buckets; a scan counts only the points whose own row is the
-// one it wants (a row's run holds each of its points once), so nothing is
-// counted twice.
+// goes on to half a wave that scans R = 2 and 3, one in fifty of those to a
+// workgroup that scans R = 7, and the few left after that to workgroups that
+// scan every point.
+// Rows can share buckets; where two runs of a search share one, only the points
+// whose own row is the run's count (a row's run holds each of its points once),
+// so nothing is counted twice.
 //
 // Every decision is taken exactly as the definition states it in the
 // precision it names: FP32 squared distances (each operation rounded, no
@@ -41,6 +42,7 @@
 namespace gs {
 
 constexpr float kDcCellScale = 1.07f;
+constexpr int kDcLanes = 4;         // lanes per query of the search over 27 cells (4 or 8)
 constexpr uint32_t kDcSlots = 64;    // slots of the statistics' sums (one per lane of the wave that adds them up)
 
 __device__ __forceinline__ float dc_floor(float x, float inv_h) { return floorf(__fmul_rn(x, inv_h)); }
@@ -100,8 +102,9 @@ struct DcWs {
   DcReport* rep;        // [1]
   uint32_t* far;        // [n] queries the 27 cells left, [1] their count (far_n)
   uint32_t* far_n;
-  uint32_t* far2;       // [n] queries the wave kernel left, [1] their count
+  uint32_t* far2;       // [n] queries the half waves left, [1] their count
   uint32_t* far2_n;
+  uint32_t* far3_n;     // [1] count of the queries the workgroups left (they take the place of far's)
   double* cand;         // [kFarSlots][8] partial k-nearest lists of the split far search
   size_t bytes;
 };
@@ -133,6 +136,7 @@ static DcWs carve_dc(void* base, int64_t n) {
   w.far_n = c.take<uint32_t>(1);
   w.far2 = c.take<uint32_t>(nn);
   w.far2_n = c.take<uint32_t>(1);
+  w.far3_n = c.take<uint32_t>(1);
   w.cand = c.take<double>(static_cast<size_t>(kFarSlots) * 8);
   w.bytes = c.off;
   return w;
@@ -142,13 +146,13 @@ size_t density_workspace(int64_t n) { return carve_dc(nullptr, n).bytes; }
 
 __global__ __launch_bounds__(256) void k_dc_clear(uint32_t* __restrict__ count, uint32_t T, DcSums* __restrict__ sums,
                                                   DcReport* __restrict__ rep, uint32_t* __restrict__ far_n,
-                                                  uint32_t* __restrict__ far2_n) {
+                                                  uint32_t* __restrict__ far2_n, uint32_t* __restrict__ far3_n) {
   const uint32_t i = blockIdx.x * 256 + threadIdx.x;
   if (i < T) count[i] = 0u;
   if (i < kDcSlots) sums[i] = DcSums{};
   if (i == 0) {
     *rep = DcReport{};
-    far_n[0] = 0u; far2_n[0] = 0u;
+    far_n[0] = 0u; far2_n[0] = 0u; far3_n[0] = 0u;
   }
 }
 
@@ -185,11 +189,12 @@ __global__ __launch_bounds__(256) void k_dc_scatter(int n, const float* __restri
 // A candidate as one ordered value: the FP32 squared distance's bits above the
 // index, read as a double.  Both parts are non-negative, so doubles compare as
 // (distance, index) does, and keeping the K best sorted is 2K - 1 minima and
-// maxima with no branch.  3.0e38 (no candidate) and everything above it -- an
-// overflowed distance, a NaN, kDcNone -- never displaces an empty slot.
+// maxima with no branch.  An empty slot holds 3.0e38; everything above it -- an
+// overflowed distance, or the NaN that stands for no candidate -- never
+// displaces one.
 __device__ __forceinline__ double dc_key(float d2, int i) { return __hiloint2double(__float_as_int(d2), i); }
 __device__ __forceinline__ double dc_empty() { return dc_key(3.0e38f, 0x7fffffff); }
-constexpr float kDcNone = __builtin_huge_valf();
+__device__ __forceinline__ float dc_none() { return __int_as_float(0x7fc00000); }
 __device__ __forceinline__ float dc_key_d2(double k) { return __int_as_float(__double2hiint(k)); }
 
 template <int K>
@@ -263,30 +268,22 @@ __device__ __forceinline__ float dc_finish(const double (&b)[K], int keff, int q
   return d0;
 }
 
-// A workgroup's share of the statistics (from its 256 threads) into a slot:
-// one set of atomics per workgroup, spread over kDcSlots lines.
-template <bool COUNTS>
-__device__ __forceinline__ void dc_add_sums(unsigned long long c1, unsigned long long c2, double a1, double a2,
-                                            DcSums* __restrict__ sums) {
-  __shared__ DcSums s[4];
+// A workgroup's share of the statistics into a slot: one set of atomics per
+// workgroup, spread over kDcSlots lines (the first wave; lane t has a query's
+// density and nearest distance, or zeros).
+__device__ __forceinline__ void dc_add_sums(int cnt, float d0, DcSums* __restrict__ sums) {
+  unsigned long long c1 = static_cast<unsigned long long>(cnt), c2 = c1 * c1;
+  double a1 = static_cast<double>(d0), a2 = a1 * a1;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    if (COUNTS) {
-      c1 += __shfl_xor(c1, o, 64);
-      c2 += __shfl_xor(c2, o, 64);
-    }
+    c1 += __shfl_xor(c1, o, 64);
+    c2 += __shfl_xor(c2, o, 64);
     a1 += __shfl_xor(a1, o, 64);
     a2 += __shfl_xor(a2, o, 64);
   }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) s[wave] = DcSums{c1, c2, a1, a2, {}};
-  __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) {
-      c1 += s[w].c1; c2 += s[w].c2; a1 += s[w].a1; a2 += s[w].a2;
-    }
     DcSums* d = sums + blockIdx.x % kDcSlots;
-    if (COUNTS && c2) {
+    if (c2) {
       atomicAdd(&d->c1, c1);
       atomicAdd(&d->c2, c2);
     }
@@ -297,26 +294,46 @@ __device__ __forceinline__ void dc_add_sums(unsigned long long c1, unsigned long
   }
 }
 
-// Points [x, y) in bucket order of the cells cx - R .. cx + R of row (cy, cz);
-// where the run wraps round the table y exceeds n, and position p >= n is p - n.
-__device__ __forceinline__ uint2 dc_run(const uint32_t* __restrict__ start, uint32_t T, int n, int cx, int cy, int cz,
-                                        int R) {
+// The first bucket of the cells cx - R .. cx + R of row (cy, cz).
+__device__ __forceinline__ uint32_t dc_bucket(uint32_t T, int cx, int cy, int cz, int R) {
+  return (dc_row(cy, cz) + static_cast<uint32_t>(cx - R)) & (T - 1u);
+}
+
+// Points [x, y) in bucket order of the 2R + 1 < T buckets from b0; where they
+// wrap round the table y exceeds n, and position p >= n is p - n.
+__device__ __forceinline__ uint2 dc_run(const uint32_t* __restrict__ start, uint32_t T, int n, uint32_t b0, int R) {
   const uint32_t mask = T - 1u;
-  const uint32_t b0 = (dc_row(cy, cz) + static_cast<uint32_t>(cx - R)) & mask;
-  const uint32_t b1 = (b0 + 2u * static_cast<uint32_t>(R)) & mask;   // 2R + 1 < T buckets
+  const uint32_t b1 = (b0 + 2u * static_cast<uint32_t>(R)) & mask;
   const uint32_t s = start[b0];
   const uint32_t e = b1 < mask ? start[b1 + 1u] : static_cast<uint32_t>(n);
   return make_uint2(s, b1 < b0 ? e + static_cast<uint32_t>(n) : e);
+}
+
+__device__ __forceinline__ void dc_wave_sync() {   // a wave's own LDS writes are visible to its lanes
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ float4 dc_at(const float4* __restrict__ pts, uint32_t p, int n) {
   return pts[min(p, p - static_cast<uint32_t>(n))];
 }
 
-// Densities and near neighbours, eight lanes per query over the nine runs of
-// its 27 cells: rho = other points within r, the sums of rho and rho^2, and
-// where the K nearest lie inside the 27 cells' guarantee the K-nearest results
-// (a query left goes to the wave kernel).
+// Densities and near neighbours, G lanes per query over the nine runs of its 27
+// cells: rho = other points within r, the sums of rho and rho^2, and where the
+// K nearest lie inside the 27 cells' guarantee the K-nearest results (a query
+// left goes to the wave kernel).
+//
+// As long as no two of a query's runs share a bucket, each point comes up at
+// most once whatever rows share its bucket, and a point of another row is only
+// one more point whose distance is looked at; so a candidate's own row is
+// looked at only by waves of which a query has overlapping runs (36 pairs,
+// 5/T each), or one that wraps round the table.
+// Instruction issue bounds it (30 VALU instructions a candidate, 171 candidates
+// a query, three quarters of the lanes busy): 64 us at 200,000 points, radius
+// 0.03.  One thread per query over hashed cells, density and neighbours apart,
+// took 341 + 810 us; with the row looked at for every candidate, 133.  Eight lanes
+// per query take the same time and more registers.
 template <int K>
 __global__ __launch_bounds__(256) void k_dc_near(int n, const float4* __restrict__ pts,
                                                  const uint32_t* __restrict__ start, uint32_t T, float h, float inv_h,
@@ -324,69 +341,217 @@ __global__ __launch_bounds__(256) void k_dc_near(int n, const float4* __restrict
                                                  float* __restrict__ dnn, float* __restrict__ dbar,
                                                  DcSums* __restrict__ sums, uint32_t* __restrict__ far,
                                                  uint32_t* __restrict__ far_n) {
-  const int l = threadIdx.x & 7;
-  const int s = blockIdx.x * 32 + (threadIdx.x >> 3);
-  unsigned long long c1 = 0, c2 = 0;
-  double a1 = 0.0, a2 = 0.0;
+  constexpr int G = kDcLanes, kHeld = (9 + G - 1) / G;   // runs that a lane looks up: l, l + G, ..
+  __shared__ int s_cnt[256 / G];
+  __shared__ float s_d0[256 / G];
+  const int l = threadIdx.x & (G - 1), group = threadIdx.x / G;
+  const int s = blockIdx.x * (256 / G) + group;
   const bool live = s < n;
   const float4 q = pts[live ? s : n - 1];
   const int qi = __float_as_int(q.w);
   const float fy = dc_floor(q.y, inv_h), fz = dc_floor(q.z, inv_h);
   const int cx = static_cast<int>(dc_floor(q.x, inv_h)), cy = static_cast<int>(fy), cz = static_cast<int>(fz);
-  // run r = 3 (dz + 1) + dy + 1: lane l looks up run l, every lane the ninth
-  uint2 mine = dc_run(start, T, n, cx, cy + l % 3 - 1, cz + l / 3 - 1, 1);
-  uint2 last = dc_run(start, T, n, cx, cy + 1, cz + 1, 1);
-  if (!live) mine.y = mine.x, last.y = last.x;
+  // run r = 3 (dz + 1) + dy + 1, its first bucket and its points
+  uint32_t b0[kHeld];
+  uint2 run[kHeld];
+#pragma unroll
+  for (int k = 0; k < kHeld; ++k) {
+    const int r = min(l + k * G, 8);
+    b0[k] = dc_bucket(T, cx, cy + r % 3 - 1, cz + r / 3 - 1, 1);
+    run[k] = dc_run(start, T, n, b0[k], 1);
+  }
+  bool shared = false;
+#pragma unroll
+  for (int k = 0; k < kHeld; ++k) {
+    shared |= run[k].y > static_cast<uint32_t>(n);
+    if (!live) run[k].y = run[k].x;
+  }
+#pragma unroll
+  for (int r = 0; r < 9; ++r) {
+    const uint32_t o = __shfl(b0[r / G], (threadIdx.x & (64 - G)) | (r % G), 64);
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k) shared |= ((b0[k] - o + 2u) & (T - 1u)) <= 4u && min(l + k * G, 8) != r;
+  }
   double b[K];
 #pragma unroll
   for (int m = 0; m < K; ++m) b[m] = dc_empty();
-  int cnt = 0;
-  for (int r = 0; r < 9; ++r) {
-    const int src = (threadIdx.x & 56) | (r & 7);
-    const uint32_t p0 = r < 8 ? __shfl(mine.x, src, 64) : last.x;
-    const uint32_t p1 = r < 8 ? __shfl(mine.y, src, 64) : last.y;
-    const float wy = fy + static_cast<float>(r % 3 - 1), wz = fz + static_cast<float>(r / 3 - 1);
-    for (uint32_t p = p0 + l; p < p1; p += 8) {
-      const float4 o = dc_at(pts, p, n);
-      const int oi = __float_as_int(o.w);
-      const bool in = dc_floor(o.y, inv_h) == wy && dc_floor(o.z, inv_h) == wz && oi != qi;
-      const float d2 = in ? dc_d2(q, o) : kDcNone;
-      cnt += d2 <= r2 && in ? 1 : 0;
-      dc_insert<K>(b, dc_key(d2, oi));
+  int cnt = 0;   // the query itself is counted too
+  if (!__any(shared)) {
+    // a candidate is loaded while the one before it is looked at, a run's first while the run before is
+    const uint32_t top = static_cast<uint32_t>(n) - 1u;
+    uint32_t p = __shfl(run[0].x, threadIdx.x & (64 - G), 64) + l;
+    float4 o = pts[min(p, top)];
+#pragma unroll
+    for (int r = 0; r < 9; ++r) {
+      const uint32_t p1 = __shfl(run[r / G].y, (threadIdx.x & (64 - G)) | (r % G), 64);
+      uint32_t q0 = 0;
+      float4 o0 = o;
+      if (r < 8) {
+        q0 = __shfl(run[(r + 1) / G].x, (threadIdx.x & (64 - G)) | ((r + 1) % G), 64) + l;
+        o0 = pts[min(q0, top)];
+      }
+      while (p < p1) {
+        p += G;
+        const float4 o1 = pts[min(p, top)];
+        const int oi = __float_as_int(o.w);
+        const float d2 = dc_d2(q, o);
+        cnt += d2 <= r2 ? 1 : 0;
+        dc_insert<K>(b, dc_key(oi != qi ? d2 : dc_none(), oi));
+        o = o1;
+      }
+      p = q0;
+      o = o0;
+    }
+  } else {
+    for (int r = 0; r < 9; ++r) {
+      uint2 v = run[0];
+#pragma unroll
+      for (int k = 1; k < kHeld; ++k) v = r / G == k ? run[k] : v;
+      const int src = (threadIdx.x & (64 - G)) | (r % G);
+      const uint32_t p1 = __shfl(v.y, src, 64);
+      const float wy = fy + static_cast<float>(r % 3 - 1), wz = fz + static_cast<float>(r / 3 - 1);
+      for (uint32_t p = __shfl(v.x, src, 64) + l; p < p1; p += G) {
+        const float4 o = dc_at(pts, p, n);
+        const int oi = __float_as_int(o.w);
+        const float d2 = dc_floor(o.y, inv_h) == wy && dc_floor(o.z, inv_h) == wz ? dc_d2(q, o) : dc_none();
+        cnt += d2 <= r2 ? 1 : 0;
+        dc_insert<K>(b, dc_key(oi != qi ? d2 : dc_none(), oi));
+      }
+    }
+  }
+  dc_merge_dpp<K, kDppXor1>(b);
+  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppXor1, 0xf, 0xf, true);
+  dc_merge_dpp<K, kDppXor2>(b);
+  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppXor2, 0xf, 0xf, true);
+  if (G == 8) {
+    dc_merge_dpp<K, kDppHalfMirror>(b);
+    cnt += __builtin_amdgcn_mov_dpp(cnt, kDppHalfMirror, 0xf, 0xf, true);
+  }
+  cnt -= 1;   // the query itself
+  // every point closer than (1 - 1/16) h has been seen
+  const float g = 0.9375f * h;
+  const bool first = live && l == 0;
+  const bool done = n - 1 >= K && dc_key_d2(b[K - 1]) <= g * g * 0.9999f;
+  if (first) {
+    rho[qi] = cnt;
+    s_cnt[group] = cnt;
+    s_d0[group] = done ? dc_finish<K>(b, K, qi, nn, dnn, dbar) : -1.0f;
+  }
+  // one append per workgroup: one per wave, 16 queries, was 35 us of 103 at 200,000 points
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int t = threadIdx.x, s0 = blockIdx.x * (256 / G);
+  const bool here = t < 256 / G && s0 + t < n;
+  const float d0 = here ? s_d0[t] : 0.0f;
+  const uint64_t open = __ballot(d0 < 0.0f);
+  if (open) {
+    uint32_t at = 0;
+    if (t == 0) at = atomicAdd(far_n, static_cast<uint32_t>(__popcll(open)));
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (d0 < 0.0f) far[at + __popcll(open & ((1ull << t) - 1ull))] = static_cast<uint32_t>(s0 + t);
+  }
+  dc_add_sums(here ? s_cnt[t] : 0, d0 < 0.0f ? 0.0f : d0, sums);
+}
+
+// The K nearest among the cells up to R of a query, found by LANES lanes (half a
+// wave, or a workgroup; each lane ends with the K best): the lanes look the
+// (2R + 1)^2 runs up, and then share all of their points evenly; the runs' ends,
+// added up in LDS, tell a lane which run its next point is in.  Returns whether
+// they lie inside R's guarantee.
+template <int K, int R, int LANES>
+__device__ __forceinline__ bool dc_search(double (&b)[K], int n, const float4* __restrict__ pts,
+                                          const uint32_t* __restrict__ start, uint32_t T, float h, float inv_h,
+                                          const float4& q, uint32_t* __restrict__ end, uint32_t* __restrict__ at,
+                                          double* __restrict__ lists) {
+  constexpr int kSide = 2 * R + 1, kRuns = kSide * kSide, kWave = LANES < 64 ? LANES : 64;
+  const int lane = threadIdx.x & (LANES - 1);
+  const float fy = dc_floor(q.y, inv_h), fz = dc_floor(q.z, inv_h);
+  const int cx = static_cast<int>(dc_floor(q.x, inv_h)), cy = static_cast<int>(fy), cz = static_cast<int>(fz);
+  const int qi = __float_as_int(q.w);
+  auto sync = [] {
+    if (LANES > 64) __syncthreads();
+    else dc_wave_sync();
+  };
+  uint32_t total = 0;
+  sync();   // the search before has read the LDS
+#pragma unroll
+  for (int t0 = 0; t0 < kRuns; t0 += LANES) {
+    const int t = t0 + lane;
+    uint2 run = make_uint2(0u, 0u);
+    if (t < kRuns) run = dc_run(start, T, n, dc_bucket(T, cx, cy + t % kSide - R, cz + t / kSide - R, R), R);
+    const uint32_t len = run.y - run.x;
+    uint32_t sum = len;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t v = __shfl_up(sum, o, kWave);
+      sum += (lane & (kWave - 1)) >= o ? v : 0u;
+    }
+    if (LANES > 64) {
+      if ((lane & 63) == 63) at[lane >> 6] = sum;
+      __syncthreads();
+      uint32_t before = 0, all = 0;
+#pragma unroll
+      for (int w = 0; w < LANES / 64; ++w) {
+        before += w < lane >> 6 ? at[w] : 0u;
+        all += at[w];
+      }
+      __syncthreads();
+      sum += before;
+      end[t] = sum;
+      at[t] = run.x - (sum - len);
+      total = all;
+    } else {
+      end[t] = total + sum;                   // points of the runs up to this one
+      at[t] = run.x - (total + sum - len);    // its first point less the points before it
+      total += __shfl(sum, kWave - 1, kWave);
+    }
+  }
+  sync();
+#pragma unroll
+  for (int m = 0; m < K; ++m) b[m] = dc_empty();
+  for (uint32_t c0 = lane; c0 < total; c0 += 2 * LANES) {
+    // two points at a time: the search for a point's run is a chain of LDS reads
+    float4 o[2];
+    int u[2] = {0, 0};   // the run that holds the point: the number of runs that end at or before it
+    uint32_t c[2] = {c0, min(c0 + LANES, total - 1u)};
+#pragma unroll
+    for (int step = kRuns < 32 ? 16 : (kRuns < 64 ? 32 : 128); step > 0; step >>= 1)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (end[min(u[i] + step, kRuns) - 1] <= c[i]) u[i] += step;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) o[i] = dc_at(pts, at[u[i]] + c[i], n);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int oi = __float_as_int(o[i].w);
+      const bool in = dc_floor(o[i].y, inv_h) == fy + static_cast<float>(u[i] % kSide - R) &&
+                      dc_floor(o[i].z, inv_h) == fz + static_cast<float>(u[i] / kSide - R) && oi != qi &&
+                      c0 + i * LANES < total;
+      dc_insert<K>(b, dc_key(in ? dc_d2(q, o[i]) : dc_none(), oi));
     }
   }
   dc_merge8<K>(b);
-  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppXor1, 0xf, 0xf, true);
-  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppXor2, 0xf, 0xf, true);
-  cnt += __builtin_amdgcn_mov_dpp(cnt, kDppHalfMirror, 0xf, 0xf, true);
-  // every point closer than (1 - 1/16) h has been seen
-  const float g = 0.9375f * h;
-  const bool mineout = live && l == 0;
-  const bool done = n - 1 >= K && dc_key_d2(b[K - 1]) <= g * g * 0.9999f;
-  if (mineout) {
-    rho[qi] = cnt;
-    c1 = static_cast<unsigned long long>(cnt);
-    c2 = c1 * c1;
-    if (done) {
-      a1 = static_cast<double>(dc_finish<K>(b, K, qi, nn, dnn, dbar));
-      a2 = a1 * a1;
+  dc_merge_dpp<K, kDppMirror>(b);
+  dc_merge_shfl<K>(b, 16);
+  if (LANES > 64) {
+    dc_merge_shfl<K>(b, 32);
+    if ((lane & 63) == 0) {
+#pragma unroll
+      for (int m = 0; m < K; ++m) lists[(lane >> 6) * K + m] = b[m];
     }
+    __syncthreads();
+    for (int w = 0; w < LANES / 64; ++w)
+      if (w != lane >> 6)
+        for (int m = 0; m < K; ++m) dc_insert<K>(b, lists[w * K + m]);
   }
-  const uint64_t open = __ballot(mineout && !done);
-  if (open) {
-    uint32_t at = 0;
-    if ((threadIdx.x & 63) == 0) at = atomicAdd(far_n, static_cast<uint32_t>(__popcll(open)));
-    at = __builtin_amdgcn_readfirstlane(at);
-    if (mineout && !done) far[at + __popcll(open & ((1ull << (threadIdx.x & 63)) - 1ull))] = static_cast<uint32_t>(s);
-  }
-  dc_add_sums<true>(c1, c2, a1, a2, sums);
+  const float g = (static_cast<float>(R) - 0.0625f) * h;
+  return dc_key_d2(b[K - 1]) <= g * g * 0.9999f;
 }
 
-// Queries the 27 cells left, one wave per query: the cells up to R = 2, then
-// 4, then 7, their runs dealt to the lanes (two lanes to each of the 25 runs of
-// R = 2, where nine in ten end), each lane its own K best, merged over the wave;
-// the wave stops once the K lie inside R's guarantee.  Queries still open go on
-// to the all-points kernel.
+// Queries the 27 cells left, half a wave each: the cells up to R = 2, where nine
+// in ten end, then 3; the one in fifty that is left goes on to a workgroup.  (A run
+// per lane, with which the longest run of a wave set the time, took 256 us for
+// 28,000 queries; this takes 45, the workgroups' kernel after it 13.)
 template <int K>
 __global__ __launch_bounds__(256) void k_dc_knn_wave(int n, const float4* __restrict__ pts,
                                                      const uint32_t* __restrict__ start, uint32_t T, float h, float inv_h,
@@ -394,39 +559,20 @@ __global__ __launch_bounds__(256) void k_dc_knn_wave(int n, const float4* __rest
                                                      uint32_t* __restrict__ far2, uint32_t* __restrict__ far2_n,
                                                      int32_t* __restrict__ nn, float* __restrict__ dnn,
                                                      float* __restrict__ dbar, DcSums* __restrict__ sums) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ uint32_t s_end[8][64], s_at[8][64];   // 7^2 runs, to whole rounds of the lanes
+  const int half = threadIdx.x >> 5;
   const uint32_t count = *far_n;
   double a1 = 0.0, a2 = 0.0;
-  for (uint32_t f = blockIdx.x * 4 + wave; f < count; f += gridDim.x * 4) {
-    const uint32_t slot = __builtin_amdgcn_readfirstlane(far[f]);
+  for (uint32_t f = blockIdx.x * 8 + half; f < count; f += gridDim.x * 8) {
+    const uint32_t slot = far[f];
     const float4 q = pts[slot];
-    const int qi = __float_as_int(q.w);
-    const float fy = dc_floor(q.y, inv_h), fz = dc_floor(q.z, inv_h);
-    const int cx = static_cast<int>(dc_floor(q.x, inv_h)), cy = static_cast<int>(fy), cz = static_cast<int>(fz);
     double b[K];
-    bool done = false;
-    for (int R = 2; R < 8 && !done && n - 1 >= K; R = R == 2 ? 4 : R + 3) {
-#pragma unroll
-      for (int m = 0; m < K; ++m) b[m] = dc_empty();
-      const int side = 2 * R + 1, per = R == 2 ? 2 : 1;
-      for (int t = lane; t < side * side * per; t += 64) {
-        const int u = t / per, dy = u % side - R, dz = u / side - R;
-        const uint2 run = dc_run(start, T, n, cx, cy + dy, cz + dz, R);
-        const float wy = fy + static_cast<float>(dy), wz = fz + static_cast<float>(dz);
-        for (uint32_t p = run.x + t % per; p < run.y; p += per) {
-          const float4 o = dc_at(pts, p, n);
-          const int oi = __float_as_int(o.w);
-          const bool in = dc_floor(o.y, inv_h) == wy && dc_floor(o.z, inv_h) == wz && oi != qi;
-          dc_insert<K>(b, dc_key(in ? dc_d2(q, o) : kDcNone, oi));
-        }
-      }
-      dc_merge64<K>(b);
-      const float g = (static_cast<float>(R) - 0.0625f) * h;
-      done = dc_key_d2(b[K - 1]) <= g * g * 0.9999f;
-    }
-    if (lane == 0) {
+    const bool done =
+        n - 1 >= K && (dc_search<K, 2, 32>(b, n, pts, start, T, h, inv_h, q, s_end[half], s_at[half], nullptr) ||
+                       dc_search<K, 3, 32>(b, n, pts, start, T, h, inv_h, q, s_end[half], s_at[half], nullptr));
+    if ((threadIdx.x & 31) == 0) {
       if (done) {
-        const double d0 = static_cast<double>(dc_finish<K>(b, K, qi, nn, dnn, dbar));
+        const double d0 = static_cast<double>(dc_finish<K>(b, K, __float_as_int(q.w), nn, dnn, dbar));
         a1 += d0;
         a2 += d0 * d0;
       } else {
@@ -434,10 +580,44 @@ __global__ __launch_bounds__(256) void k_dc_knn_wave(int n, const float4* __rest
       }
     }
   }
-  dc_add_sums<false>(0, 0, a1, a2, sums);
+  if ((threadIdx.x & 31) == 0 && a2 != 0.0) {
+    DcSums* d = sums + (blockIdx.x * 8 + half) % kDcSlots;
+    unsafeAtomicAdd(&d->a1, a1);
+    unsafeAtomicAdd(&d->a2, a2);
+  }
 }
 
-// The queries the wave search left (fewer than K other points: every query): a
+// Queries still open, a workgroup each: the cells up to R = 7.  (Half a wave took
+// some 20 us for one of these, and they come in clusters, so that the last of the
+// kernel before doubled its time.)  What is left goes to the scan of every point.
+template <int K>
+__global__ __launch_bounds__(256) void k_dc_knn_wide(int n, const float4* __restrict__ pts,
+                                                     const uint32_t* __restrict__ start, uint32_t T, float h, float inv_h,
+                                                     const uint32_t* __restrict__ far, const uint32_t* __restrict__ far_n,
+                                                     uint32_t* __restrict__ far2, uint32_t* __restrict__ far2_n,
+                                                     int32_t* __restrict__ nn, float* __restrict__ dnn,
+                                                     float* __restrict__ dbar, DcSums* __restrict__ sums) {
+  __shared__ uint32_t s_end[256], s_at[256];   // 15^2 runs
+  __shared__ double s_lists[4 * K];
+  const uint32_t count = *far_n;
+  for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
+    const uint32_t slot = far[f];
+    const float4 q = pts[slot];
+    double b[K];
+    const bool done = n - 1 >= K && dc_search<K, 7, 256>(b, n, pts, start, T, h, inv_h, q, s_end, s_at, s_lists);
+    if (threadIdx.x == 0) {
+      if (done) {
+        const double d0 = static_cast<double>(dc_finish<K>(b, K, __float_as_int(q.w), nn, dnn, dbar));
+        unsafeAtomicAdd(&sums[blockIdx.x % kDcSlots].a1, d0);
+        unsafeAtomicAdd(&sums[blockIdx.x % kDcSlots].a2, d0 * d0);
+      } else {
+        far2[atomicAdd(far2_n, 1u)] = slot;
+      }
+    }
+  }
+}
+
+// The queries the searches left (fewer than K other points: every query): a
 // workgroup per (query, range of points) scans its range (each thread a strided
 // share, its own K best) and merges the 256 lists; with S > 1 ranges the lists
 // go to cand for k_dc_knn_far_merge, with one range the result is written here.
@@ -465,7 +645,7 @@ __global__ __launch_bounds__(256) void k_dc_knn_far(int n, const float4* __restr
     for (int p = p0 + threadIdx.x; p < p1; p += 256) {
       const float4 o = pts[p];
       const int oi = __float_as_int(o.w);
-      dc_insert<K>(b, dc_key(oi != qi ? dc_d2(q, o) : kDcNone, oi));
+      dc_insert<K>(b, dc_key(oi != qi ? dc_d2(q, o) : dc_none(), oi));
     }
     dc_merge64<K>(b);
     if ((threadIdx.x & 63) == 0) {
@@ -583,6 +763,9 @@ constexpr int kDcComps = 12;   // spherical-harmonics planes that a workgroup of
 // Output of every point: its own values, a merged pair's (at the lower index),
 // and a new point next to each sparse point (after all kept points).  Workgroup
 // row 0 writes the geometry, row y > 0 the colour planes 12 (y - 1) to 12 y - 1.
+// HBM bounds it: 190 MB past the L2s (kept points move to where the cache lines no
+// longer match) in 33 us at 200,000 points, 5.7 TB/s; one thread per point, all planes
+// in turn, took 61.
 __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint32_t* __restrict__ pos,
                                                   const int32_t* __restrict__ partner, const float* __restrict__ dbar,
                                                   const float* __restrict__ noise, float spread, float jitter,
@@ -597,23 +780,37 @@ __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint3
   const int64_t q = static_cast<int64_t>(pos[N + i]);
   const int64_t next = i + 1 < n ? static_cast<int64_t>(pos[N + i + 1]) : static_cast<int64_t>(rep->total);
   const bool put = kept && o < cap, spawn = next > q && q < cap;
+  const bool merged = put && j >= 0;
+  float oi = 1.0f, oj = 0.0f, li = 0.0f, lj = 0.0f;
+  if (merged) {
+    li = A.logits[i]; lj = A.logits[j];
+    oi = dc_sigmoid(li); oj = dc_sigmoid(lj);
+  }
+  const float w = oi + oj;
   if (blockIdx.y > 0) {
     const int c0 = (static_cast<int>(blockIdx.y) - 1) * kDcComps, c1 = min(c0 + kDcComps, A.nsh);
-    if (put && j >= 0) {
-      const float oi = dc_sigmoid(A.logits[i]), oj = dc_sigmoid(A.logits[j]);
-      const float w = oi + oj;
-      for (int c = c0; c < c1; ++c) A.o_sh[c * cap + o] = (oi * A.sh[c * N + i] + oj * A.sh[c * N + j]) / w;
+    if (!(put || spawn)) return;
+    // all loads first, so that they are in flight together
+    float v[kDcComps], u[kDcComps];
+#pragma unroll
+    for (int c = 0; c < kDcComps; ++c) v[c] = c0 + c < c1 ? A.sh[(c0 + c) * N + i] : 0.0f;
+    if (merged) {
+#pragma unroll
+      for (int c = 0; c < kDcComps; ++c) u[c] = c0 + c < c1 ? A.sh[(c0 + c) * N + j] : 0.0f;
     }
-    const bool copy = put && j < 0;
-    if (copy || spawn) {
-      float v[kDcComps];
+    if (spawn) {
 #pragma unroll
-      for (int c = 0; c < kDcComps; ++c) v[c] = c0 + c < c1 ? A.sh[(c0 + c) * N + i] : 0.0f;
+      for (int c = 0; c < kDcComps; ++c)
+        if (c0 + c < c1) A.o_sh[(c0 + c) * cap + q] = v[c];
+    }
+    if (merged) {
 #pragma unroll
-      for (int c = 0; c < kDcComps; ++c) {
-        if (copy && c0 + c < c1) A.o_sh[(c0 + c) * cap + o] = v[c];
-        if (spawn && c0 + c < c1) A.o_sh[(c0 + c) * cap + q] = v[c];
-      }
+      for (int c = 0; c < kDcComps; ++c) v[c] = (oi * v[c] + oj * u[c]) / w;
+    }
+    if (put) {
+#pragma unroll
+      for (int c = 0; c < kDcComps; ++c)
+        if (c0 + c < c1) A.o_sh[(c0 + c) * cap + o] = v[c];
     }
     return;
   }
@@ -630,9 +827,6 @@ __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint3
     } else {
       // merge with j (j > i): opacity-weighted position and colour, mean
       // scale, accumulated opacity, the more opaque one's rotation
-      const float li = A.logits[i], lj = A.logits[j];
-      const float oi = dc_sigmoid(li), oj = dc_sigmoid(lj);
-      const float w = oi + oj;
       for (int c = 0; c < 3; ++c) {
         A.o_means[c * cap + o] = (oi * A.means[c * N + i] + oj * A.means[c * N + j]) / w;
         A.o_ls[c * cap + o] = logf(0.5f * (expf(A.ls[c * N + i]) + expf(A.ls[c * N + j])));
@@ -670,7 +864,7 @@ gs_status launch_density_control(const gs_gaussians& g, const gs_density_params&
   DcReport r{};
   if (n > 0) {
     { TimedLaunch t("k_dc_clear", s); k_dc_clear<<<static_cast<unsigned>(ceil_div(T, 256)), 256, 0, s>>>(w.count, T, w.sums, w.rep,
-                                                                                                 w.far_n, w.far2_n); }
+                                                                                                 w.far_n, w.far2_n, w.far3_n); }
     if ((st = check_launch("k_dc_clear")) != GS_OK) return st;
     { TimedLaunch t("k_dc_cells", s); k_dc_cells<<<gn, 256, 0, s>>>(n, g.means, inv_h, T - 1u, w.cell, w.count, w.rep); }
     if ((st = check_launch("k_dc_cells")) != GS_OK) return st;
@@ -680,16 +874,19 @@ gs_status launch_density_control(const gs_gaussians& g, const gs_density_params&
 #define GS_DC_KNN(K)                                                                                              \
   {                                                                                                               \
     { TimedLaunch t("k_dc_near<" #K ">", s);                                                                      \
-      k_dc_near<K><<<static_cast<unsigned>(ceil_div(n, 32)), 256, 0, s>>>(n, w.pts, w.count, T, h, inv_h, r2, w.rho, \
+      k_dc_near<K><<<static_cast<unsigned>(ceil_div(n, 256 / kDcLanes)), 256, 0, s>>>(n, w.pts, w.count, T, h, inv_h, r2, w.rho, \
                                                                           w.nn, w.dnn, w.dbar, w.sums, w.far,     \
                                                                           w.far_n); }                             \
     { TimedLaunch t("k_dc_knn_wave<" #K ">", s);                                                                  \
       k_dc_knn_wave<K><<<2048, 256, 0, s>>>(n, w.pts, w.count, T, h, inv_h, w.far, w.far_n, w.far2, w.far2_n,     \
                                             w.nn, w.dnn, w.dbar, w.sums); }                                       \
+    { TimedLaunch t("k_dc_knn_wide<" #K ">", s);                                                                  \
+      k_dc_knn_wide<K><<<1024, 256, 0, s>>>(n, w.pts, w.count, T, h, inv_h, w.far2, w.far2_n, w.far, w.far3_n,    \
+                                            w.nn, w.dnn, w.dbar, w.sums); }                                       \
     { TimedLaunch t("k_dc_knn_far<" #K ">", s);                                                                   \
-      k_dc_knn_far<K><<<1024, 256, 0, s>>>(n, w.pts, w.far2, w.far2_n, w.nn, w.dnn, w.dbar, w.sums, w.cand); }    \
+      k_dc_knn_far<K><<<1024, 256, 0, s>>>(n, w.pts, w.far, w.far3_n, w.nn, w.dnn, w.dbar, w.sums, w.cand); }     \
     { TimedLaunch t("k_dc_knn_far_merge<" #K ">", s);                                                             \
-      k_dc_knn_far_merge<K><<<256, 64, 0, s>>>(n, w.pts, w.far2, w.far2_n, w.nn, w.dnn, w.dbar, w.sums, w.cand); }  \
+      k_dc_knn_far_merge<K><<<256, 64, 0, s>>>(n, w.pts, w.far, w.far3_n, w.nn, w.dnn, w.dbar, w.sums, w.cand); } \
   }
     switch (prm.knn) {
       case 1: GS_DC_KNN(1); break;
