@@ -132,15 +132,32 @@ __device__ __forceinline__ void split_put2(Split8& s, int e, float a, float b) {
   s.lo[e] = p.lo[0]; s.lo[e + 1] = p.lo[1];
 }
 
-// Read a D-layout pre-activation (4 row-blocks, bias included) back as the
-// split B operands of the next layer, after the ReLU.
-__device__ __forceinline__ void relu_to_b(const floatx4 h[4], Split8& B0, Split8& B1) {
+// D-layout values (4 row-blocks) as the split B operands of the next product.
+__device__ __forceinline__ void d_to_b(const floatx4 h[4], Split8& B0, Split8& B1) {
 #pragma unroll
   for (int e = 0; e < 8; e += 2) {
-    const int b0 = e >> 2, i = e & 3;
-    split_put2(B0, e, fmaxf(h[b0][i], 0.0f), fmaxf(h[b0][i + 1], 0.0f));
-    split_put2(B1, e, fmaxf(h[2 + b0][i], 0.0f), fmaxf(h[2 + b0][i + 1], 0.0f));
+    split_put2(B0, e, h[e >> 2][e & 3], h[e >> 2][(e & 3) + 1]);
+    split_put2(B1, e, h[2 + (e >> 2)][e & 3], h[2 + (e >> 2)][(e & 3) + 1]);
   }
+}
+
+// Where a layer's pre-activations are positive, a wave mask per value (scalar
+// registers: the backward needs them long after the values).
+struct ReluMask {
+  uint64_t m[4][4];
+};
+
+// The split ReLU of a layer's pre-activations (0 for a NaN) and their signs.
+__device__ __forceinline__ void relu_to_b(const floatx4 h[4], Split8& B0, Split8& B1, ReluMask& on) {
+  floatx4 p[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      on.m[b][i] = __builtin_amdgcn_ballot_w64(h[b][i] > 0.0f);
+      p[b][i] = __builtin_amdgcn_inverse_ballot_w64(on.m[b][i]) ? h[b][i] : 0.0f;
+    }
+  d_to_b(p, B0, B1);
 }
 
 // The biases of a hidden layer in the D layout of row-block b: lane (g, r)
@@ -172,30 +189,103 @@ __device__ __forceinline__ Split8 input_operand(int g, bool valid, const uint4& 
   return X;
 }
 
+// N consecutive packed tiles, read together (one wait for all).
+template <int N>
+__device__ __forceinline__ void tiles(const MlpShared& sh, int op, int lane, uint4* w) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) w[k] = sh.ops[(op + k) * 64 + lane];
+}
+
+// Staging of one group ([sample][unit]); plane 0 holds the BF16 value (hi),
+// plane 1 the BF16 rounding of the remainder (lo).  Rows of 64 units are padded
+// to 72 (36 banks): the stores of a quarter's 16 lanes (one per row) and the
+// transposing reads (32 bytes of four rows) then each touch different banks.
+constexpr int kRow = 72, kRowX = 36, kRowG3 = 4;
+struct alignas(16) MlpStage {
+  __bf16 h1[2][16][kRow];
+  __bf16 g1[2][16][kRow];
+  __bf16 hg2[2][16][kRow];   // h2, then g2
+  __bf16 x[2][16][kRowX];
+  __bf16 g3[2][16][kRowG3];
+};
+
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// Orders a wave's LDS accesses: its lanes read what other lanes of it wrote.
+// (The hardware keeps a wave's LDS operations in order; this keeps the compiler.)
+__device__ __forceinline__ void stage_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The split operands of k-chunks 0, 1 of sample r: slots 4 q .. 4 q + 3 of chunk c
+// are units 32 c + 16 q + 4 g and the three after it.
+__device__ __forceinline__ void stage_put(__bf16 (*m)[16][kRow], int g, int r, const Split8& S0, const Split8& S1) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const Split8& S = c ? S1 : S0;
+      const int at = 32 * c + 16 * q + 4 * g;
+      const bf16x4 hi = {S.hi[4 * q], S.hi[4 * q + 1], S.hi[4 * q + 2], S.hi[4 * q + 3]};
+      const bf16x4 lo = {S.lo[4 * q], S.lo[4 * q + 1], S.lo[4 * q + 2], S.lo[4 * q + 3]};
+      __builtin_memcpy(&m[0][r][at], &hi, sizeof(hi));
+      __builtin_memcpy(&m[1][r][at], &lo, sizeof(lo));
+    }
+}
+
+// Samples 4 g .. 4 g + 3 of unit 16 b + r of a staged plane.  The transposing read
+// works on 16 lanes: lane r names row r / 4 (of four), columns 4 (r % 4) .. + 3 (of
+// sixteen), and gets column r of the four rows.  (g3 has four columns: its rows
+// come back four times.)
+template <int ROW>
+__device__ __forceinline__ bf16x4 stage_get(const __bf16 (*p)[ROW], int b, int g, int r) {
+  auto* at = reinterpret_cast<const __attribute__((address_space(3))) shortx4*>(
+      reinterpret_cast<uintptr_t>(&p[4 * g + (r >> 2)][ROW > 4 ? 16 * b + 4 * (r & 3) : 0]));
+  const shortx4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(const_cast<__attribute__((address_space(3))) shortx4*>(at));
+  bf16x4 o;
+  __builtin_memcpy(&o, &v, sizeof(o));
+  return o;
+}
+
+__device__ __forceinline__ bf16x8 join(const bf16x4& a, const bf16x4& b) {
+  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 struct MlpFwdState {
-  floatx4 h1[4], h2[4], o;
+  floatx4 o;
   Split8 X, B0, B1, C0, C1;
+  ReluMask m1, m2;
 };
 
 __device__ __forceinline__ floatx4 mfma2(const uint4& a, const Split8& b, const floatx4& c) {
   return mfma(a, b.lo, mfma(a, b.hi, c));
 }
 
-// h1, h2: pre-activations (biases included); B, C: the split ReLU outputs.
-__device__ __forceinline__ void mlp_forward_group(const MlpShared& sh, int lane, MlpFwdState& st) {
+// B, C: the split ReLU outputs; m1, m2: the signs of the pre-activations.  BWD:
+// the activations also go to sg, as soon as they are there.
+template <bool BWD>
+__device__ __forceinline__ void mlp_forward_group(const MlpShared& sh, int lane, MlpFwdState& st, MlpStage* sg = nullptr) {
   const int g = lane >> 4;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+  floatx4 h[4];
+  uint4 w[8];
+  tiles<4>(sh, kOpW1, lane, w);
 #pragma unroll
-  for (int b = 0; b < 4; ++b) st.h1[b] = mfma2(sh.ops[(kOpW1 + b) * 64 + lane], st.X, bias_d(sh.bias, b, g));
-  relu_to_b(st.h1, st.B0, st.B1);
+  for (int b = 0; b < 4; ++b) h[b] = mfma2(w[b], st.X, bias_d(sh.bias, b, g));
+  tiles<8>(sh, kOpW2, lane, w);
+  relu_to_b(h, st.B0, st.B1, st.m1);
+  if (BWD) stage_put(sg->h1, g, lane & 15, st.B0, st.B1);
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-    floatx4 acc = mfma2(sh.ops[(kOpW2 + 2 * b) * 64 + lane], st.B0, bias_d(sh.bias + 64, b, g));
-    st.h2[b] = mfma2(sh.ops[(kOpW2 + 2 * b + 1) * 64 + lane], st.B1, acc);
+    const floatx4 acc = mfma2(w[2 * b], st.B0, bias_d(sh.bias + 64, b, g));
+    h[b] = mfma2(w[2 * b + 1], st.B1, acc);
   }
-  relu_to_b(st.h2, st.C0, st.C1);
-  floatx4 acc = mfma2(sh.ops[kOpW3 * 64 + lane], st.C0, zero);
-  st.o = mfma2(sh.ops[(kOpW3 + 1) * 64 + lane], st.C1, acc);
+  tiles<2>(sh, kOpW3, lane, w);
+  relu_to_b(h, st.C0, st.C1, st.m2);
+  if (BWD) stage_put(sg->hg2, g, lane & 15, st.C0, st.C1);
+  st.o = mfma2(w[1], st.C1, mfma2(w[0], st.C0, zero));
 }
 
 // The hardware reciprocal (1 ulp) instead of a correctly rounded division:
@@ -291,7 +381,7 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(int S, int per, const uint16_t*
     sample_dir<MODE>(cur, cam, d, len);
     MlpFwdState st;
     st.X = input_operand(g, valid, cur.z, d);
-    mlp_forward_group(sh, lane, st);
+    mlp_forward_group<false>(sh, lane, st);
     cur = nxt;
     if (g == 0 && valid) {
 #pragma unroll
@@ -353,74 +443,43 @@ size_t mlp_packed_bytes() { return kOps * 64 * sizeof(uint4) + kBiasFloats * siz
 // the D layout like the activations.  dx rows 0..15 are dL/dz, rows 16..31
 // dL/dY (the SH encoding), which the basis gradient carries to the direction.
 // The gradients entering the transposed products are hi + lo BF16 pairs as in
-// the forward.  Weight gradients contract over samples: each group's
-// activations and gradients go to LDS transposed ([unit][sample], hi and lo
-// planes) and
+// the forward.  Weight gradients contract over samples:
 //   dW1 += g1 x^T,  dW2 += g2 h1^T,  dW3 += g3 h2^T
-// run as hi.hi + lo.hi + hi.lo (the lo.lo term, about 2^-18 relative, is
-// dropped) on two 16x16x32 products whose K runs over the group's 16 samples
-// twice: [g_hi | g_lo] x [h_hi | h_hi], then [g_hi | g_lo] x [h_lo | 0] (for the
-// latent inputs, whose lo part is zero, the first alone).  Sums stay
-// in registers for the wave's whole share and are written once as a partial
-// vector; a fixed-order two-stage sum over waves makes the result
-// deterministic for a given sample count.
+// as hi.hi + lo.hi + hi.lo (the lo.lo term, about 2^-18 relative, is dropped).
+// A lane of those operands holds four samples of one unit, where the layers
+// above leave four units of one sample: the operands go to LDS as they are
+// ([sample][unit], four units a store) and come back through the transposing LDS
+// read.  Two waves share the sums of dW1 and dW2: after a barrier each takes half
+// of the tiles over both waves' samples (32, a whole K), so that a wave's sums
+// take 64 registers and not 112 and two waves fit a SIMD without spills.  dW3 (3 of
+// 16 rows used) stays with the wave, K running over its 16 samples twice:
+// [g_hi | g_hi] x [h_hi | h_lo], then [g_lo | 0] x [h_hi | h_lo].  Sums stay in
+// registers for the wave's whole share; a workgroup adds its waves' up in LDS and
+// writes one partial vector, and a fixed-order sum over workgroups makes the
+// result deterministic for a given sample count.
 
 constexpr int kPartStride = GS_MLP_PARAMS + 1;  // parameters, then the loss
-constexpr int kBwdWavesMax = 1024;
-constexpr int kReduceChunk = 64;                 // waves per first-stage block
+constexpr int kBwdWaves = 8;                     // waves of a workgroup
+constexpr int kBwdGroupsMax = 256;               // workgroups: one per CU, whose LDS it takes
 
-// Transposed staging of one group ([unit][sample]); plane 0 holds the BF16
-// value (hi), plane 1 the BF16 rounding of the remainder (lo).  Rows are
-// padded to kRow = 20 values (10 banks): the four quarters of a wave, which
-// write rows 4 apart, then land on disjoint LDS banks, and row starts stay
-// 8-byte aligned for the operand reads.
-constexpr int kRow = 20;
-struct alignas(16) MlpStage {
-  __bf16 x[2][32][kRow];
-  __bf16 h1[2][64][kRow];
-  __bf16 h2[2][64][kRow];
-  __bf16 g1[2][64][kRow];
-  __bf16 g2[2][64][kRow];
-  __bf16 g3[2][16][kRow];
+// The hi and lo operands of two groups staged at m0 and m1: slots 0..3 hold the
+// first group's samples, 4..7 the second's.
+struct PairOp {
+  bf16x8 hi, lo;
 };
-
-// unit u of sample r: slot e of a split operand
-__device__ __forceinline__ void stage_put(__bf16 (*plane)[64][kRow], int u, int r, const Split8& v, int e) {
-  plane[0][u][r] = v.hi[e];
-  plane[1][u][r] = v.lo[e];
-}
-
-// A 16x16x32 operand over a group's staged samples: lane (g, r) takes row
-// `row`, samples 8 (g & 1) .. 8 (g & 1) + 7 of plane p (K slots 8 g .. 8 g + 7:
-// samples 0..15, then 0..15 again).
-template <int ROWS>
-__device__ __forceinline__ bf16x8 stage_read8(const __bf16 (*plane)[ROWS][kRow], int p, int row, int g) {
-  bf16x8 v;
-  __builtin_memcpy(&v, &plane[p][row][8 * (g & 1)], sizeof(v));
-  return v;
-}
-// [hi | lo] along K (the gradient side), [hi | hi], and [lo | 0]
-template <int ROWS>
-__device__ __forceinline__ bf16x8 stage_hilo(const __bf16 (*plane)[ROWS][kRow], int row, int g) {
-  return stage_read8<ROWS>(plane, g >> 1, row, g);
-}
-template <int ROWS>
-__device__ __forceinline__ bf16x8 stage_lo0(const __bf16 (*plane)[ROWS][kRow], int row, int g) {
-  bf16x8 v = stage_read8<ROWS>(plane, 1, row, g);
-  return g < 2 ? v : bf16x8{};
+template <int ROW>
+__device__ __forceinline__ PairOp stage_pair(const __bf16 (*m0)[16][ROW], const __bf16 (*m1)[16][ROW], int b, int g, int r) {
+  PairOp o;
+  o.hi = join(stage_get<ROW>(m0[0], b, g, r), stage_get<ROW>(m1[0], b, g, r));
+  o.lo = join(stage_get<ROW>(m0[1], b, g, r), stage_get<ROW>(m1[1], b, g, r));
+  return o;
 }
 
 __device__ __forceinline__ floatx4 mfma32(const bf16x8& a, const bf16x8& b, const floatx4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-
-// D-layout gradients (4 row-blocks) as the split B operands of the next product.
-__device__ __forceinline__ void grad_to_b(const floatx4 h[4], Split8& B0, Split8& B1) {
-#pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    split_put2(B0, e, h[e >> 2][e & 3], h[e >> 2][(e & 3) + 1]);
-    split_put2(B1, e, h[2 + (e >> 2)][e & 3], h[2 + (e >> 2)][(e & 3) + 1]);
-  }
+__device__ __forceinline__ floatx4 mfma_dw(const PairOp& a, const PairOp& b, const floatx4& c) {
+  return mfma32(a.hi, b.lo, mfma32(a.lo, b.hi, mfma32(a.hi, b.hi, c)));
 }
 
 // Sum over the 16 lanes of each DPP row (the 16 samples of one quarter); every
@@ -433,23 +492,44 @@ __device__ __forceinline__ float row_sum16(float v) {
   return v;
 }
 
+// A wave's sums: rows 32 half .. + 31 of dW1 and dW2 over its pair's samples, the
+// rest over its own.
 struct MlpGrads {
-  floatx4 dW1[4][2], dW2[4][4], dW3[4];
+  floatx4 dW1[2][2], dW2[2][4], dW3[4];
   float db1[16], db2[16], db3[3], loss;
 };
 
-// One group: forward, loss gradient, backward, weight-gradient update.
-// Returns dL/dz (dxz) and dL/dY (dxe) of this lane's sample in the D layout.
+// One group: forward, loss gradient, backward, weight-gradient update (every wave
+// of the workgroup at once: it has two barriers).  Returns dL/dz (dxz) and dL/dY
+// (dxe) of this lane's sample in the D layout.
+//
+// Latency bounds it, with LDS (the packed tiles, 30 KB a group, and the staged
+// operands: two fifths of the cycles), VALU issue (530 instructions a group, half)
+// and the matrix cores (98 products, a quarter) all busy: 158 us for 1,048,576
+// samples, 64 to a latent.  One wave per SIMD with all 112 registers of sums and
+// 16-bit transposing stores took 260; two whole waves per SIMD, which spill, 190; a
+// pair of groups in lockstep by one wave per SIMD 220.
 template <int MODE>
-__device__ __forceinline__ void mlp_bwd_group(const MlpShared& sh, MlpStage& sg, MlpGrads& G, int lane,
+__device__ __forceinline__ void mlp_bwd_group(const MlpShared& sh, MlpStage* stage, int wave, MlpGrads& G, int lane,
                                               const SampleIn& x, const float d[3], bool loss_mode, float scale,
                                               floatx4& dxz, floatx4& dxe) {
   const int g = lane >> 4, r = lane & 15;
   const bool valid = x.in;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+  MlpStage& sg = stage[wave];
   MlpFwdState st;
   st.X = input_operand(g, valid, x.z, d);
-  mlp_forward_group(sh, lane, st);
+  lds_barrier();   // the pair's reads of the group before
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const bf16x4 hi = {st.X.hi[4 * q], st.X.hi[4 * q + 1], st.X.hi[4 * q + 2], st.X.hi[4 * q + 3]};
+    const bf16x4 lo = {st.X.lo[4 * q], st.X.lo[4 * q + 1], st.X.lo[4 * q + 2], st.X.lo[4 * q + 3]};
+    __builtin_memcpy(&sg.x[0][r][8 * g + 4 * q], &hi, sizeof(hi));
+    __builtin_memcpy(&sg.x[1][r][8 * g + 4 * q], &lo, sizeof(lo));
+  }
+  mlp_forward_group<true>(sh, lane, st, &sg);
+  uint4 w[8];
+  tiles<4>(sh, kOpW3T, lane, w);
   floatx4 g3 = zero;
   if (g == 0 && valid) {
 #pragma unroll
@@ -471,86 +551,74 @@ __device__ __forceinline__ void mlp_bwd_group(const MlpShared& sh, MlpStage& sg,
 #pragma unroll
   for (int e = 0; e < 8; e += 2)
     split_put2(Bg3, e, (g == 0 && e < 4) ? g3[e & 3] : 0.0f, (g == 0 && e < 4) ? g3[(e & 3) + 1] : 0.0f);
-  floatx4 g2[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const floatx4 t = mfma2(sh.ops[(kOpW3T + b) * 64 + lane], Bg3, zero);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) g2[b][i] = (st.h2[b][i] > 0.0f) ? t[i] : 0.0f;
+  if (g == 0) {
+    const bf16x4 hi = {Bg3.hi[0], Bg3.hi[1], Bg3.hi[2], Bg3.hi[3]}, lo = {Bg3.lo[0], Bg3.lo[1], Bg3.lo[2], Bg3.lo[3]};
+    __builtin_memcpy(&sg.g3[0][r][0], &hi, sizeof(hi));
+    __builtin_memcpy(&sg.g3[1][r][0], &lo, sizeof(lo));
   }
-  Split8 G0, G1;
-  grad_to_b(g2, G0, G1);
-  floatx4 g1[4];
+  stage_fence();
+  {
+    const bf16x4 hi = stage_get<kRowG3>(sg.g3[0], 0, g, r), lo = stage_get<kRowG3>(sg.g3[1], 0, g, r);
+    const bf16x8 hh = join(hi, hi), l0 = join(lo, bf16x4{});
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    floatx4 t = mfma2(sh.ops[(kOpW2T + 2 * b) * 64 + lane], G0, zero);
-    t = mfma2(sh.ops[(kOpW2T + 2 * b + 1) * 64 + lane], G1, t);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) g1[b][i] = (st.h1[b][i] > 0.0f) ? t[i] : 0.0f;
-  }
-  Split8 H0, H1;
-  grad_to_b(g1, H0, H1);
-  dxz = mfma2(sh.ops[(kOpW1T + 0) * 64 + lane], H0, zero);
-  dxz = mfma2(sh.ops[(kOpW1T + 1) * 64 + lane], H1, dxz);
-  dxe = mfma2(sh.ops[(kOpW1T + 2) * 64 + lane], H0, zero);
-  dxe = mfma2(sh.ops[(kOpW1T + 3) * 64 + lane], H1, dxe);
-
-  // transposed staging for the weight gradients: the split operands the
-  // products above used (slot e of B_c carries unit hid(c, g, e))
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int u = hid(c, g, e);
-      stage_put(sg.h1, u, r, c ? st.B1 : st.B0, e);
-      stage_put(sg.h2, u, r, c ? st.C1 : st.C0, e);
-      stage_put(sg.g1, u, r, c ? H1 : H0, e);
-      stage_put(sg.g2, u, r, c ? G1 : G0, e);
+    for (int b = 0; b < 4; ++b) {
+      const bf16x8 h = join(stage_get<kRow>(sg.hg2[0], b, g, r), stage_get<kRow>(sg.hg2[1], b, g, r));
+      G.dW3[b] = mfma32(l0, h, mfma32(hh, h, G.dW3[b]));
     }
+  }
+  floatx4 t2[4];
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < 4; ++b) {
+    const floatx4 t = mfma2(w[b], Bg3, zero);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      G.db1[4 * b + i] += g1[b][i];
-      G.db2[4 * b + i] += g2[b][i];
+      t2[b][i] = __builtin_amdgcn_inverse_ballot_w64(st.m2.m[b][i]) ? t[i] : 0.0f;
+      G.db2[4 * b + i] += t2[b][i];
     }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    sg.x[0][8 * g + e][r] = st.X.hi[e];
-    sg.x[1][8 * g + e][r] = st.X.lo[e];
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float v = g == 0 ? g3[i] : 0.0f;
-    const __bf16 h = static_cast<__bf16>(v);
-    sg.g3[0][4 * g + i][r] = h;
-    sg.g3[1][4 * g + i][r] = static_cast<__bf16>(v - static_cast<float>(h));
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  bf16x8 bH1[4], bH1l[4], bH2[4], bH2l[4];
+  tiles<8>(sh, kOpW2T, lane, w);
+  Split8 G0, G1;
+  d_to_b(t2, G0, G1);
+  stage_fence();
+  stage_put(sg.hg2, g, r, G0, G1);
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-    bH1[b] = stage_read8<64>(sg.h1, 0, 16 * b + r, g);
-    bH1l[b] = stage_lo0<64>(sg.h1, 16 * b + r, g);
-    bH2[b] = stage_read8<64>(sg.h2, 0, 16 * b + r, g);
-    bH2l[b] = stage_lo0<64>(sg.h2, 16 * b + r, g);
-  }
-  const bf16x8 bX0 = stage_read8<32>(sg.x, 0, r, g);
-  const bf16x8 bX1 = stage_read8<32>(sg.x, 0, 16 + r, g), bX1l = stage_lo0<32>(sg.x, 16 + r, g);
-  const bf16x8 aG3 = stage_hilo<16>(sg.g3, r, g);
+    const floatx4 t = mfma2(w[2 * b + 1], G1, mfma2(w[2 * b], G0, zero));
 #pragma unroll
-  for (int bo = 0; bo < 4; ++bo) {
-    const bf16x8 aG2 = stage_hilo<64>(sg.g2, 16 * bo + r, g);
-    const bf16x8 aG1 = stage_hilo<64>(sg.g1, 16 * bo + r, g);
-#pragma unroll
-    for (int bi = 0; bi < 4; ++bi) G.dW2[bo][bi] = mfma32(aG2, bH1l[bi], mfma32(aG2, bH1[bi], G.dW2[bo][bi]));
-    G.dW1[bo][0] = mfma32(aG1, bX0, G.dW1[bo][0]);
-    G.dW1[bo][1] = mfma32(aG1, bX1l, mfma32(aG1, bX1, G.dW1[bo][1]));
-    G.dW3[bo] = mfma32(aG3, bH2l[bo], mfma32(aG3, bH2[bo], G.dW3[bo]));
+    for (int i = 0; i < 4; ++i) {
+      t2[b][i] = __builtin_amdgcn_inverse_ballot_w64(st.m1.m[b][i]) ? t[i] : 0.0f;
+      G.db1[4 * b + i] += t2[b][i];
+    }
   }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  tiles<MODE == 1 ? 4 : 2>(sh, kOpW1T, lane, w);
+  Split8 H0, H1;
+  d_to_b(t2, H0, H1);
+  stage_put(sg.g1, g, r, H0, H1);
+  dxz = mfma2(w[1], H1, mfma2(w[0], H0, zero));
+  if (MODE == 1) dxe = mfma2(w[3], H1, mfma2(w[2], H0, zero));
+  lds_barrier();
+  const MlpStage &s0 = stage[wave & ~1], &s1 = stage[wave | 1];
+  const int half = 2 * (wave & 1);
+  {
+    PairOp h[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) h[b] = stage_pair<kRow>(s0.h1, s1.h1, b, g, r);
+#pragma unroll
+    for (int bo = 0; bo < 2; ++bo) {
+      const PairOp a = stage_pair<kRow>(s0.hg2, s1.hg2, half + bo, g, r);
+#pragma unroll
+      for (int bi = 0; bi < 4; ++bi) G.dW2[bo][bi] = mfma_dw(a, h[bi], G.dW2[bo][bi]);
+    }
+  }
+  // the latent inputs are BF16: their lo part is zero
+  const PairOp x1 = stage_pair<kRowX>(s0.x, s1.x, 1, g, r);
+  const bf16x8 x0 = join(stage_get<kRowX>(s0.x[0], 0, g, r), stage_get<kRowX>(s1.x[0], 0, g, r));
+#pragma unroll
+  for (int bo = 0; bo < 2; ++bo) {
+    const PairOp a = stage_pair<kRow>(s0.g1, s1.g1, half + bo, g, r);
+    G.dW1[bo][0] = mfma32(a.lo, x0, mfma32(a.hi, x0, G.dW1[bo][0]));
+    G.dW1[bo][1] = mfma_dw(a, x1, G.dW1[bo][1]);
+  }
 }
 
 // MODE 0: sample s has direction dirs[s] and latent s / per (per a power of
@@ -562,7 +630,7 @@ __device__ __forceinline__ void mlp_bwd_group(const MlpShared& sh, MlpStage& sg,
 //         see load_sample); dlat[s] and the direction's share of dL/dmean are
 //         written for live Gaussians (dmean is added to), zeros elsewhere.
 template <int MODE>
-__global__ __launch_bounds__(256) void k_mlp_bwd(int S, int per, const uint16_t* __restrict__ latents,
+__global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(int S, int per, const uint16_t* __restrict__ latents,
                                                  const float* __restrict__ dirs, const float* __restrict__ means,
                                                  const int* __restrict__ radius, DevCam cam,
                                                  const uint4* __restrict__ ops, const float* __restrict__ bias,
@@ -570,25 +638,25 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(int S, int per, const uint16_t*
                                                  float scale, float* __restrict__ dlat, float* __restrict__ dmean,
                                                  float* __restrict__ partial, int64_t cs, int64_t ss) {
   __shared__ MlpShared sh;
-  __shared__ MlpStage stage[4];
+  __shared__ union {
+    MlpStage stage[kBwdWaves];
+    float part[2][kPartStride];
+  } u;
   load_packed(sh, ops, bias);
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-  MlpStage& sg = stage[wave];
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
   MlpGrads G;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    G.dW1[a][0] = zero; G.dW1[a][1] = zero; G.dW3[a] = zero;
+  for (int b = 0; b < 4; ++b) { G.dW2[0][b] = zero; G.dW2[1][b] = zero; G.dW3[b] = zero; }
 #pragma unroll
-    for (int b = 0; b < 4; ++b) G.dW2[a][b] = zero;
-  }
+  for (int b = 0; b < 2; ++b) { G.dW1[0][b] = zero; G.dW1[1][b] = zero; }
 #pragma unroll
   for (int k = 0; k < 16; ++k) { G.db1[k] = 0.f; G.db2[k] = 0.f; }
   G.db3[0] = G.db3[1] = G.db3[2] = 0.f;
   G.loss = 0.f;
 
-  const int wave_id = blockIdx.x * 4 + wave, nwaves = gridDim.x * 4;
+  const int wave_id = blockIdx.x * kBwdWaves + wave, nwaves = gridDim.x * kBwdWaves;
   const int ngroups = (S + 15) / 16;
   // per >= 16: a wave owns whole latents (per / 16 consecutive groups each)
   const int gpl = per >= 16 ? per / 16 : 1;
@@ -600,10 +668,11 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(int S, int per, const uint16_t*
   auto group_of = [&](int unit, int q) { return (static_cast<int64_t>(unit) * gpl + q) * 16 + r; };
   SampleIn cur = load_sample<MODE, true>(group_of(wave_id, 0), wave_id < nunits ? S : 0, per, g, latents, dirs,
                                          means, radius, cin, dmean, cs, ss);
-  for (int unit = wave_id; unit < nunits; unit += nwaves) {
+  // (every wave of a workgroup takes as many steps as its first)
+  for (int unit = wave_id; unit - wave < nunits; unit += nwaves) {
     floatx4 zacc = zero;
     for (int q = 0; q < gpl; ++q) {
-      const int s = static_cast<int>(group_of(unit, q));
+      const int64_t s = group_of(unit, q);
       const int nunit = (q + 1 < gpl) ? unit : unit + nwaves;
       const int nq = (q + 1 < gpl) ? q + 1 : 0;
       const SampleIn nxt = load_sample<MODE, true>(group_of(nunit, nq), nunit < nunits ? S : 0, per, g, latents,
@@ -612,7 +681,7 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(int S, int per, const uint16_t*
       float d[3], len;
       sample_dir<MODE>(cur, cam, d, len);
       floatx4 dxz, dxe;
-      mlp_bwd_group<MODE>(sh, sg, G, lane, cur, d, loss_mode, scale, dxz, dxe);
+      mlp_bwd_group<MODE>(sh, u.stage, wave, G, lane, cur, d, loss_mode, scale, dxz, dxe);
       if (per >= 16) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) zacc[i] += row_sum16(dxz[i]);
@@ -621,7 +690,7 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(int S, int per, const uint16_t*
         for (int i = 0; i < 4; ++i) {
           float v = dxz[i];
           for (int w = 1; w < per; w <<= 1) v += __shfl_xor(v, w, 16);
-          if ((r & (per - 1)) == 0) dlat[static_cast<int64_t>(s / per) * 16 + 4 * g + i] = valid ? v : 0.0f;
+          if ((r & (per - 1)) == 0) dlat[s / per * 16 + 4 * g + i] = valid ? v : 0.0f;
         }
       }
       if (MODE == 1) {
@@ -646,127 +715,128 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(int S, int per, const uint16_t*
       }
       cur = nxt;
     }
-    if (per >= 16 && r == 0) {
+    if (per >= 16 && r == 0 && unit < nunits) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) dlat[static_cast<int64_t>(unit) * 16 + 4 * g + i] = zacc[i];
     }
   }
 
-  // partial vector of this wave (D layout: row 4g + i of a 16-row block, column r)
-  float* out = partial + static_cast<int64_t>(wave_id) * kPartStride;
-#pragma unroll
-  for (int bo = 0; bo < 4; ++bo)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int o = 16 * bo + 4 * g + i;
-#pragma unroll
-      for (int bi = 0; bi < 4; ++bi) out[P_W2 + o * kMlpH + 16 * bi + r] = G.dW2[bo][bi][i];
-      out[P_W1 + o * kMlpIn + r] = G.dW1[bo][0][i];
-      out[P_W1 + o * kMlpIn + 16 + r] = G.dW1[bo][1][i];
-    }
-#pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int o = 4 * g + i;
-      if (o < kMlpOut) out[P_W3 + o * kMlpH + 16 * bi + r] = G.dW3[bi][i];
-    }
+  // the workgroup's partial vector (D layout: row 4g + i of a 16-row block,
+  // column r): waves 0..3 and 4..7 add up in turn, each half in its own copy
+  float* const out = u.part[wave >> 2];
 #pragma unroll
   for (int b = 0; b < 4; ++b)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float s1 = row_sum16(G.db1[4 * b + i]);
-      const float s2 = row_sum16(G.db2[4 * b + i]);
-      if (r == 0) {
-        out[P_B1 + 16 * b + 4 * g + i] = s1;
-        out[P_B2 + 16 * b + 4 * g + i] = s2;
-      }
+      G.db1[4 * b + i] = row_sum16(G.db1[4 * b + i]);
+      G.db2[4 * b + i] = row_sum16(G.db2[4 * b + i]);
     }
 #pragma unroll
-  for (int i = 0; i < kMlpOut; ++i) {
-    const float s3 = row_sum16(G.db3[i]);
-    if (lane == 0) out[P_B3 + i] = s3;
+  for (int i = 0; i < kMlpOut; ++i) G.db3[i] = row_sum16(G.db3[i]);
+  G.loss = row_sum16(G.loss);
+  for (int w = 0; w < 4; ++w) {
+    __syncthreads();
+    if ((wave & 3) != w) continue;
+    auto add = [&](int p, float v) { out[p] = w ? out[p] + v : v; };
+    auto add_half = [&](int p, float v) { out[p] = w > 1 ? out[p] + v : v; };   // rows that every other wave has
+#pragma unroll
+    for (int bo = 0; bo < 2; ++bo)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = 32 * (wave & 1) + 16 * bo + 4 * g + i;
+#pragma unroll
+        for (int bi = 0; bi < 4; ++bi) add_half(P_W2 + o * kMlpH + 16 * bi + r, G.dW2[bo][bi][i]);
+        add_half(P_W1 + o * kMlpIn + r, G.dW1[bo][0][i]);
+        add_half(P_W1 + o * kMlpIn + 16 + r, G.dW1[bo][1][i]);
+      }
+#pragma unroll
+    for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = 4 * g + i;
+        if (o < kMlpOut) add(P_W3 + o * kMlpH + 16 * bi + r, G.dW3[bi][i]);
+      }
+    if (r == 0) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          add(P_B1 + 16 * b + 4 * g + i, G.db1[4 * b + i]);
+          add(P_B2 + 16 * b + 4 * g + i, G.db2[4 * b + i]);
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < kMlpOut; ++i) add(P_B3 + i, G.db3[i]);
+      add(GS_MLP_PARAMS, G.loss);
+    }
   }
-  const float sl = row_sum16(G.loss);
-  if (lane == 0) out[GS_MLP_PARAMS] = sl;
-}
-
-// First stage: block (x, y) sums waves [64 y, 64 y + 64) of 64 parameters,
-// four interleaved sub-sums per parameter combined in a fixed order.
-__global__ __launch_bounds__(256) void k_mlp_reduce1(const float* __restrict__ partial, int nwaves,
-                                                     float* __restrict__ stage2) {
-  __shared__ float part[4][64];
-  const int p = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
-  const int w0 = blockIdx.y * kReduceChunk, w1 = min(nwaves, w0 + kReduceChunk);
-  float acc = 0.f;
-  if (p < kPartStride)
-    for (int w = w0 + q; w < w1; w += 4) acc += partial[static_cast<int64_t>(w) * kPartStride + p];
-  part[q][threadIdx.x & 63] = acc;
   __syncthreads();
-  if (q == 0 && p < kPartStride) {
-    const int t = threadIdx.x;
-    stage2[static_cast<int64_t>(blockIdx.y) * kPartStride + p] = ((part[0][t] + part[1][t]) + part[2][t]) + part[3][t];
-  }
+  for (int p = threadIdx.x; p < kPartStride; p += 64 * kBwdWaves)
+    partial[static_cast<int64_t>(blockIdx.x) * kPartStride + p] = u.part[0][p] + u.part[1][p];
 }
 
-__global__ __launch_bounds__(256) void k_mlp_reduce2(const float* __restrict__ stage2, int nchunks,
-                                                     float* __restrict__ dparams, float* __restrict__ loss) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= kPartStride) return;
+// Sum of the workgroups' partial vectors: a block takes 64 parameters, eight
+// interleaved sub-sums each, combined in a fixed order.
+__global__ __launch_bounds__(512) void k_mlp_reduce(const float* __restrict__ partial, int count,
+                                                    float* __restrict__ dparams, float* __restrict__ loss) {
+  __shared__ float part[8][64];
+  const int t = threadIdx.x & 63, q = threadIdx.x >> 6, p = blockIdx.x * 64 + t;
   float acc = 0.f;
-  for (int c = 0; c < nchunks; ++c) acc += stage2[static_cast<int64_t>(c) * kPartStride + p];
+  if (p < kPartStride) {
+#pragma unroll 8
+    for (int w = q; w < count; w += 8) acc += partial[static_cast<int64_t>(w) * kPartStride + p];
+  }
+  part[q][t] = acc;
+  __syncthreads();
+  if (q != 0 || p >= kPartStride) return;
+#pragma unroll
+  for (int k = 1; k < 8; ++k) acc += part[k][t];
   if (p < GS_MLP_PARAMS) dparams[p] = acc;
   else if (loss) *loss = acc;
 }
 
-// Waves of the backward for S samples: about 8 groups of 16 per wave, a
-// multiple of 4 (one block), at most kBwdWavesMax.
-static int mlp_bwd_waves(int64_t S, int per) {
+// Workgroups of the backward for S samples: a unit (a group of 16 samples, or
+// the groups of one latent) per wave, up to one workgroup per CU.
+static int mlp_bwd_groups(int64_t S, int per) {
   const int64_t groups = std::max<int64_t>(1, ceil_div(S, 16));
   const int64_t units = per >= 16 ? std::max<int64_t>(1, groups / (per / 16)) : groups;
-  int64_t w = ceil_div(units, 8);
-  w = std::min<int64_t>(kBwdWavesMax, std::max<int64_t>(4, ceil_div(w, 4) * 4));
-  return static_cast<int>(w);
+  return static_cast<int>(std::min<int64_t>(kBwdGroupsMax, ceil_div(units, kBwdWaves)));
 }
 
 size_t mlp_bwd_workspace(int64_t S, int per) {
-  const int w = mlp_bwd_waves(S, per);
-  const int chunks = static_cast<int>(ceil_div(w, kReduceChunk));
-  return static_cast<size_t>(w + chunks) * kPartStride * sizeof(float);
+  return static_cast<size_t>(mlp_bwd_groups(S, per)) * kPartStride * sizeof(float);
 }
 
-static gs_status reduce_partials(float* ws, int nwaves, float* dparams, float* loss, hipStream_t s) {
-  const int chunks = static_cast<int>(ceil_div(nwaves, kReduceChunk));
-  float* stage2 = ws + static_cast<size_t>(nwaves) * kPartStride;
-  { TimedLaunch gs_tl("k_mlp_reduce1", s); k_mlp_reduce1<<<dim3(static_cast<unsigned>(ceil_div(kPartStride, 64)), chunks), 256, 0, s>>>(ws, nwaves, stage2); }
-  { TimedLaunch gs_tl("k_mlp_reduce2", s); k_mlp_reduce2<<<static_cast<unsigned>(ceil_div(kPartStride, 256)), 256, 0, s>>>(stage2, chunks, dparams, loss); }
+static gs_status reduce_partials(const float* ws, int count, float* dparams, float* loss, hipStream_t s) {
+  { TimedLaunch gs_tl("k_mlp_reduce", s); k_mlp_reduce<<<static_cast<unsigned>(ceil_div(kPartStride, 64)), 512, 0, s>>>(ws, count, dparams, loss); }
   return check_launch("k_mlp_reduce");
 }
 
 gs_status launch_mlp_bwd(int64_t S, int per, const uint16_t* latents, const float* dirs, const void* packed,
                          const float* dL_drgb, const float* target, float scale, float* dlat, float* dparams,
                          float* loss, void* ws, hipStream_t s) {
-  const int waves = mlp_bwd_waves(S, per);
+  const int groups = mlp_bwd_groups(S, per);
   DevCam dummy{};
-  { TimedLaunch gs_tl("k_mlp_bwd<0>", s); k_mlp_bwd<0><<<waves / 4, 256, 0, s>>>(static_cast<int>(S), per, latents, dirs, nullptr, nullptr, dummy,
+  { TimedLaunch gs_tl("k_mlp_bwd<0>", s); k_mlp_bwd<0><<<groups, 64 * kBwdWaves, 0, s>>>(static_cast<int>(S), per, latents, dirs, nullptr, nullptr, dummy,
                                          packed_ops(packed), packed_bias(packed), dL_drgb, target, scale, dlat,
                                          nullptr, static_cast<float*>(ws), 1, 3); }
   gs_status st = check_launch("k_mlp_bwd");
   if (st != GS_OK) return st;
-  return reduce_partials(static_cast<float*>(ws), waves, dparams, loss, s);
+  return reduce_partials(static_cast<float*>(ws), groups, dparams, loss, s);
 }
 
 gs_status launch_mlp_render_bwd(int64_t n, const uint16_t* latents, const float* means, const int* radius,
                                 const DevCam& cam, const void* packed, const float* g2d, bool rows, float* dlat,
                                 float* dmeans, float* dparams, void* ws, hipStream_t s) {
-  const int waves = mlp_bwd_waves(n, 1);
+  const int groups = mlp_bwd_groups(n, 1);
   const int64_t cs = rows ? 1 : n, ss = rows ? kAccStride : 1;
-  { TimedLaunch gs_tl("k_mlp_bwd<1>", s); k_mlp_bwd<1><<<waves / 4, 256, 0, s>>>(static_cast<int>(n), 1, latents, nullptr, means, radius, cam,
+  { TimedLaunch gs_tl("k_mlp_bwd<1>", s); k_mlp_bwd<1><<<groups, 64 * kBwdWaves, 0, s>>>(static_cast<int>(n), 1, latents, nullptr, means, radius, cam,
                                          packed_ops(packed), packed_bias(packed), g2d, nullptr, 0.0f, dlat, dmeans,
                                          static_cast<float*>(ws), cs, ss); }
   gs_status st = check_launch("k_mlp_render_bwd");
   if (st != GS_OK) return st;
-  return reduce_partials(static_cast<float*>(ws), waves, dparams, nullptr, s);
+  return reduce_partials(static_cast<float*>(ws), groups, dparams, nullptr, s);
 }
 
 // ------------------------------------------------------------------ training support

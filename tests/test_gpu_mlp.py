@@ -150,6 +150,42 @@ def test_mlp_backward_matches_oracle_within_bound(gs, n, per):
     _check_grads(f"n={n} per={per}", got_P, want_P, bP, got_z, want_z, bz, massP)
 
 
+# shares that end inside a group of 16, a pair of waves, a workgroup of eight and
+# after a full round of the card's 2,048 waves
+@pytest.mark.parametrize("n,per", [(15, 1), (17, 1), (129, 1), (32785, 1), (9, 2), (3, 16), (2049, 16), (9, 128)])
+def test_mlp_backward_shares_that_end_anywhere(gs, n, per):
+    """A sample's latent gradient has the same bits in whichever wave and place it
+    is taken, and the weights' gradient is the sum of two parts' gradients up to
+    the FP32 rounding of the sums (as many terms as a wave and the workgroups add)."""
+    say(f"[mlp bwd shares] n={n} per={per}")
+    Pbits = kaiming_params(30 + n)
+    z = scenes.bf16_bits(np.random.default_rng(n + 1).normal(0, 0.5, (n, 16)).astype(np.float32))
+    d = _dirs(n, per, 40 + n)
+    G = np.random.default_rng(n + 2).normal(size=(n * per, 3)).astype(np.float32)
+    packed = _packed(gs, Pbits)
+
+    def grads(lo, hi):
+        dlat = torch.empty((hi - lo, 16), dtype=torch.float32, device=DEV)
+        dP = torch.empty(oracle.MLP_PARAMS, dtype=torch.float32, device=DEV)
+        S = (hi - lo) * per
+        gs.mlp_bwd(S, per, to_dev(z[lo:hi].view(np.int16)), to_dev(d[lo:hi].reshape(S, 3)), packed, dlat, dP,
+                   _bwd_workspace(gs, S, per), dL_drgb=to_dev(G[lo * per:hi * per]))
+        torch.cuda.synchronize()
+        return dlat.cpu().numpy(), dP.cpu().numpy().astype(np.float64)
+
+    cut = n // 3 + 1 if n > 1 else 1
+    whole_z, whole_P = grads(0, n)
+    parts = [grads(0, cut), grads(cut, n)]
+    assert np.array_equal(whole_z, np.concatenate([p[0] for p in parts]))
+    P = scenes.bf16_to_f32(Pbits).astype(np.float64)
+    x = oracle.mlp_inputs(scenes.bf16_to_f32(z).astype(np.float64), d.astype(np.float64))
+    mass = bwd_bounds(x, P, G.astype(np.float64))[2]
+    # both sides round each sum of at most S / 16 + 256 terms; a bounded share of the
+    # mass may come from gates that the exact network has closed
+    tol = 2 * (n * per / 16 + 256) * F32 * (mass + 1e-2 * mass.max()) + 1e-7
+    assert (np.abs(whole_P - parts[0][1] - parts[1][1]) <= tol).all()
+
+
 def test_mlp_distillation_loss_and_gradient(gs):
     """Loss mode: L = scale * sum |c - target|^2 with the gradient taken from
     the kernel's own colours."""
