@@ -334,7 +334,7 @@ __device__ __forceinline__ SampleIn load_sample(int64_t s64, int S, int per, int
 #pragma unroll
     for (int i = 0; i < kMlpOut; ++i) {
       x.c[i] = dL_dc[(MODE == 1 ? 6 + i : i) * cs + s * ss];
-      if (MODE == 1 && dmean && x.in) x.m[i] = dmean[static_cast<int64_t>(i) * S + s];
+      if (MODE == 1 && dmean) x.m[i] = dmean[static_cast<int64_t>(i) * S + s];
     }
   }
   return x;
@@ -505,14 +505,14 @@ struct MlpGrads {
 //
 // Latency bounds it, with LDS (the packed tiles, 30 KB a group, and the staged
 // operands: two fifths of the cycles), VALU issue (530 instructions a group, half)
-// and the matrix cores (98 products, a quarter) all busy: 158 us for 1,048,576
+// and the matrix cores (98 products, a quarter) all busy: 150 us for 1,048,576
 // samples, 64 to a latent.  One wave per SIMD with all 112 registers of sums and
 // 16-bit transposing stores took 260; two whole waves per SIMD, which spill, 190; a
 // pair of groups in lockstep by one wave per SIMD 220.
-template <int MODE>
+template <int MODE, class Prefetch>
 __device__ __forceinline__ void mlp_bwd_group(const MlpShared& sh, MlpStage* stage, int wave, MlpGrads& G, int lane,
                                               const SampleIn& x, const float d[3], bool loss_mode, float scale,
-                                              floatx4& dxz, floatx4& dxe) {
+                                              floatx4& dxz, floatx4& dxe, const Prefetch& prefetch) {
   const int g = lane >> 4, r = lane & 15;
   const bool valid = x.in;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -596,6 +596,7 @@ __device__ __forceinline__ void mlp_bwd_group(const MlpShared& sh, MlpStage* sta
   stage_put(sg.g1, g, r, H0, H1);
   dxz = mfma2(w[1], H1, mfma2(w[0], H0, zero));
   if (MODE == 1) dxe = mfma2(w[3], H1, mfma2(w[2], H0, zero));
+  prefetch();   // the next group's inputs
   lds_barrier();
   const MlpStage &s0 = stage[wave & ~1], &s1 = stage[wave | 1];
   const int half = 2 * (wave & 1);
@@ -672,16 +673,25 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(int S, int per, cons
   for (int unit = wave_id; unit - wave < nunits; unit += nwaves) {
     floatx4 zacc = zero;
     for (int q = 0; q < gpl; ++q) {
+      // MODE 1: addresses that depend on the lane are worked out anew each time;
+      // kept across the loop they spill, and a reload waits for the prefetched
+      // inputs (70 us against 58 for 200,000 Gaussians)
+      int lane = threadIdx.x & 63;
+      if constexpr (MODE == 1) asm volatile("" : "+v"(lane));
+      const int g = lane >> 4, r = lane & 15;
+      auto group_of = [&](int unit, int q) { return (static_cast<int64_t>(unit) * gpl + q) * 16 + r; };
       const int64_t s = group_of(unit, q);
       const int nunit = (q + 1 < gpl) ? unit : unit + nwaves;
       const int nq = (q + 1 < gpl) ? q + 1 : 0;
-      const SampleIn nxt = load_sample<MODE, true>(group_of(nunit, nq), nunit < nunits ? S : 0, per, g, latents,
-                                                   dirs, means, radius, cin, dmean, cs, ss);
+      SampleIn nxt;
       const bool valid = cur.in;
       float d[3], len;
       sample_dir<MODE>(cur, cam, d, len);
       floatx4 dxz, dxe;
-      mlp_bwd_group<MODE>(sh, u.stage, wave, G, lane, cur, d, loss_mode, scale, dxz, dxe);
+      mlp_bwd_group<MODE>(sh, u.stage, wave, G, lane, cur, d, loss_mode, scale, dxz, dxe, [&] {
+        nxt = load_sample<MODE, true>(group_of(nunit, nq), nunit < nunits ? S : 0, per, g, latents, dirs, means, radius,
+                                      cin, dmean, cs, ss);
+      });
       if (per >= 16) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) zacc[i] += row_sum16(dxz[i]);
