@@ -81,7 +81,7 @@ STAGE_KERNELS = {
     "project": ("k_project<", "k_mlp_fwd<1>"),
     "bin_sort": ("k_depth_keys", "k_os_", "k_rs_hist", "k_rs_scatter", "k_scan_", "k_chunk_",
                  "k_coarse_parts", "k_fine_", "k_small_", "k_tile_starts", "k_emit", "k_ranges", "k_put_zero_k"),
-    "render_fwd": ("k_render_fwd_light", "k_render_fwd<false", "k_tile_plan"),
+    "render_fwd": ("k_render_fwd_light", "k_render_fwd_few", "k_render_fwd<false", "k_tile_plan"),
     "l1_loss": ("k_l1_",),
     "render_bwd": ("k_render_bwd", "k_acc_to_g2d", "k_det_", "k_zero4", "k_batch_plan"),
     "colour_hash_table": ("k_chs_table",),
