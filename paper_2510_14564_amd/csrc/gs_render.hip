@@ -1254,11 +1254,12 @@ __global__ __launch_bounds__(256) void k_det_reduce(int n, const uint32_t* __res
 // (So did walking several batches per workgroup, 621 us against 660 at 1.5M
 // stretched Gaussians.)  With the item carrying
 // its list position, 16-bit lists and the shorter support test it runs eight
-// waves per SIMD (63 registers against 71): 265 us against 273 at 1M Gaussians,
-// 622 against 682 at 1.5M stretched ones, and with colour-hash sampling, where
-// four workgroups now share a CU's LDS instead of three, 201 against 270.
+// waves per SIMD (63 registers against 71): 260 us against 273 at 1M Gaussians,
+// 610 against 682 at 1.5M stretched ones (seven waves: 264 and 628), and with
+// colour-hash sampling, where four workgroups now share a CU's LDS instead of
+// three, 201 against 270.
 template <bool DET, bool CHS = false>
-__global__ __launch_bounds__(256) void k_render_bwd(const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ point_list,
                                                     const float4* __restrict__ rec, DevCam cam,
                                                     const float* __restrict__ final_T,
