@@ -1158,6 +1158,11 @@ __global__ __launch_bounds__(256) void k_acc_to_g2d(int n, const float4* __restr
 // rectangle order.  No atomics: the result is the same bit for bit on every
 // run (for a given schedule).  Rows of entries no pixel reaches stay zero.
 constexpr int kDetRow = 9;
+// The sums of a batch wait in LDS for its four waves in two parts of the batch,
+// the entries behind first: 33 KB of LDS and four workgroups per CU instead of 51
+// KB and three (175 us against 193 for 120,001 Gaussians at 1237 x 823; three
+// parts, five workgroups by registers: 176, four parts 183).
+constexpr int kDetPart = kBatch / 2;
 
 __global__ __launch_bounds__(256) void k_det_count(int n, const float4* __restrict__ rec,
                                                    const int* __restrict__ radius, int tiles_x, int tiles_y,
@@ -1275,7 +1280,7 @@ __global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const ui
   __shared__ Stage st;
   __shared__ uint32_t s_max;
   // DET: each wave's nine sums per staged entry, [wave][entry][9]
-  __shared__ float4 s_part4[DET ? 4 * kBatch * kDetRow / 4 : 1];
+  __shared__ float4 s_part4[DET ? kDetPart * kDetRow : 1];   // [wave][entry of the part][sum]
   float* const s_part = reinterpret_cast<float*>(s_part4);
   // CHS: the grouping, and per staged entry the sums of the gradient reaching
   // its group's aggregated opacity and colour (representatives only)
@@ -1394,7 +1399,7 @@ __global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const ui
       id = load_id(bi - 1);
     }
     if constexpr (DET) {
-      for (int i = threadIdx.x; i < 4 * kBatch * kDetRow / 4; i += 256) s_part4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = threadIdx.x; i < kDetPart * kDetRow; i += 256) s_part4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if constexpr (CHS) s_chs4[threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
     lds_barrier();
@@ -1414,41 +1419,74 @@ __global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const ui
     }
     // entry m0 + j reaches this pixel iff j < ncon - m0 (one compare per entry)
     const uint32_t nrel = ncon > m0 ? ncon - m0 : 0u;
-    for (int i = static_cast<int>(uniform(static_cast<uint32_t>(st.len[wave]))) - 1; i >= 0; --i) {
-      const uint32_t j = uniform(st.list[wave][i]);
-      const bool live = j < nrel;
-      const uint64_t reached = __builtin_amdgcn_ballot_w64(live);
-      const float4 p = st.r[j].p;
-      const float4 q = st.r[j].q;
-      const float cb = st.r[j].c.x;
-      float dx, dy, p2, eg, og, nx, ny;
-      eval_pair(p, q, px, py, dx, dy, p2, eg, og, nx, ny);
-      const float alpha = fminf(kAlphaMax, og);
-      const bool ok = live && (p2 <= 0.0f) && (alpha >= kAlphaMin);
-      // the wave's test from the compares' own masks (a ballot of the
-      // combined bool would first turn it into an integer and back)
-      if ((reached & __builtin_amdgcn_ballot_w64(p2 <= 0.0f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin)) == 0)
-        continue;
-      float v[9];
-      bwd_terms(q, cb, ok, nx, ny, alpha, eg, og, G0, G1, G2, T, GS, v);
-      const float red8 = wave_sum8(v, lo8);
-      const float red9 = wave_sum_to_lane63(v[8]);  // dL/db
-      if constexpr (DET) {
-        if (writer) s_part[(wave * kBatch + static_cast<int>(j)) * kDetRow + out_slot] = lane == 63 ? red9 : red8;
-      } else {
-        // CHS: a group's opacity and colour sums wait in LDS for the member pass below
-        bool to_lds = false;
-        if constexpr (CHS) to_lds = out_slot >= 5 && cs.rep[j] != kChsNone;
-        // the Gaussian's row in scalar registers: the atomics take it as
-        // their base and the lane's slot as a 32-bit offset
-        float* const row = acc + static_cast<int64_t>(uniform(st.r[j].gid)) * kAccStride;
-        if (writer) {
-          if (to_lds)
-            atomicAdd(&s_chs[4 * static_cast<int>(j) + out_slot - 5], lane == 63 ? red9 : red8);
-          else
-            unsafeAtomicAdd(row + out_slot, lane == 63 ? red9 : red8);
+    int i = static_cast<int>(uniform(static_cast<uint32_t>(st.len[wave]))) - 1;
+    // the wave's entries back to entry part0 of the batch
+    auto walk = [&](int part0) {
+      for (; i >= 0; --i) {
+        const uint32_t j = uniform(st.list[wave][i]);
+        if (DET && static_cast<int>(j) < part0) break;
+        const bool live = j < nrel;
+        const uint64_t reached = __builtin_amdgcn_ballot_w64(live);
+        const float4 p = st.r[j].p;
+        const float4 q = st.r[j].q;
+        const float cb = st.r[j].c.x;
+        float dx, dy, p2, eg, og, nx, ny;
+        eval_pair(p, q, px, py, dx, dy, p2, eg, og, nx, ny);
+        const float alpha = fminf(kAlphaMax, og);
+        const bool ok = live && (p2 <= 0.0f) && (alpha >= kAlphaMin);
+        // the wave's test from the compares' own masks (a ballot of the
+        // combined bool would first turn it into an integer and back)
+        if ((reached & __builtin_amdgcn_ballot_w64(p2 <= 0.0f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin)) == 0)
+          continue;
+        float v[9];
+        bwd_terms(q, cb, ok, nx, ny, alpha, eg, og, G0, G1, G2, T, GS, v);
+        const float red8 = wave_sum8(v, lo8);
+        const float red9 = wave_sum_to_lane63(v[8]);  // dL/db
+        if constexpr (DET) {
+          if (writer) s_part[(wave * kDetPart + static_cast<int>(j) - part0) * kDetRow + out_slot] = lane == 63 ? red9 : red8;
+        } else {
+          // CHS: a group's opacity and colour sums wait in LDS for the member pass below
+          bool to_lds = false;
+          if constexpr (CHS) to_lds = out_slot >= 5 && cs.rep[j] != kChsNone;
+          // the Gaussian's row in scalar registers: the atomics take it as
+          // their base and the lane's slot as a 32-bit offset
+          float* const row = acc + static_cast<int64_t>(uniform(st.r[j].gid)) * kAccStride;
+          if (writer) {
+            if (to_lds)
+              atomicAdd(&s_chs[4 * static_cast<int>(j) + out_slot - 5], lane == 63 ? red9 : red8);
+            else
+              unsafeAtomicAdd(row + out_slot, lane == 63 ? red9 : red8);
+          }
         }
       }
+    };
+    if constexpr (DET) {
+      for (int part0 = kBatch - kDetPart; part0 >= 0; part0 -= kDetPart) {
+        if (part0 >= static_cast<int>(cnt)) continue;
+        walk(part0);
+        // entry part0 + t's row: its four waves' sums added in wave order
+        lds_barrier();
+        const int t = threadIdx.x;
+        if (t < kDetPart && part0 + t < static_cast<int>(cnt)) {
+          const uint32_t r = det_row(row_of[st.r[part0 + t].gid], tx, ty);
+          float sum[kDetRow];
+#pragma unroll
+          for (int c = 0; c < kDetRow; ++c) {
+            constexpr int kWave = kDetPart * kDetRow;
+            float* const w = s_part + t * kDetRow + c;
+            sum[c] = ((w[0] + w[kWave]) + w[2 * kWave]) + w[3 * kWave];
+            w[0] = w[kWave] = w[2 * kWave] = w[3 * kWave] = 0.0f;   // for the part before it
+          }
+          if (r < rows) {
+            float* const dst = part + static_cast<size_t>(r) * kDetRow;
+#pragma unroll
+            for (int c = 0; c < kDetRow; ++c) dst[c] = sum[c];
+          }
+        }
+        if (part0 > 0) lds_barrier();
+      }
+    } else {
+      walk(0);
     }
     if constexpr (CHS) {
       // every member of a group of two or more (representative included) gets
@@ -1467,21 +1505,6 @@ __global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const ui
             unsafeAtomicAdd(row + 7, tot.z * sn);
             unsafeAtomicAdd(row + 8, tot.w * sn);
           }
-        }
-      }
-    }
-    if constexpr (DET) {
-      // entry t's row: its four waves' sums added in wave order
-      __syncthreads();
-      const int t = threadIdx.x;
-      if (t < cnt) {
-        const uint32_t r = det_row(row_of[st.r[t].gid], tx, ty);
-        if (r < rows) {
-          float* const dst = part + static_cast<size_t>(r) * kDetRow;
-#pragma unroll
-          for (int c = 0; c < kDetRow; ++c)
-            dst[c] = ((s_part[t * kDetRow + c] + s_part[(kBatch + t) * kDetRow + c]) +
-                      s_part[(2 * kBatch + t) * kDetRow + c]) + s_part[(3 * kBatch + t) * kDetRow + c];
         }
       }
     }

@@ -577,6 +577,40 @@ def test_deterministic_backward(gs, name):
         say(f"  schedule {sched}: bit-identical reruns, worst rel err {worst:.2e}")
 
 
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 255, 256, 257, 385])
+def test_deterministic_rows_at_the_edges_of_batches(gs, n):
+    """One tile of n entries (a batch's sums wait for its waves in two parts of 128):
+    with the upstream gradient on one quadrant a row holds that wave's sum alone, so
+    the four such runs add up to the whole run's row, to the rounding of three
+    additions and a scaling per run."""
+    say(f"[deterministic rows] n={n}")
+    scene = scenes.uniform_scene(n, 40 + n, sh_degree=0)
+    scene.means[:] *= 0.05
+    scene.log_scales[:] = np.clip(scene.log_scales, -4.0, -2.0)
+    scene.logits[:] = -3.0                       # thin: every entry is reached
+    cam = scenes.front_camera(16, 16)
+    p, g, out = gpu_project(gs, scene, cam)
+    k, pl, ranges = gpu_bin_sort(gs, scene.n, out, cam)
+    assert k == n
+    image, fT, nc, ck = gpu_render(gs, scene.n, out, pl, ranges, k, cam)
+    G = scenes.upstream_grad(cam, 7)
+
+    def rows(mask):
+        Gd = to_dev((G * mask).astype(np.float32))
+        return gpu_render_bwd(gs, scene.n, out, pl, ranges, k, cam, fT, nc, ck, Gd, deterministic=True,
+                              schedule=gs.SCHEDULE_BALANCED).cpu().numpy().astype(np.float64)
+
+    whole = rows(np.ones((16, 16)))
+    parts = []
+    for q in range(4):
+        m = np.zeros((16, 16))
+        m[8 * (q >> 1):8 * (q >> 1) + 8, 8 * (q & 1):8 * (q & 1) + 8] = 1.0
+        parts.append(rows(m))
+    mass = sum(np.abs(r) for r in parts)
+    assert (mass.max(axis=0) > 0).all() or (mass.max(axis=1) > 0).all()
+    assert (np.abs(whole - sum(parts)) <= 8 * 2.0 ** -24 * mass).all()
+
+
 @pytest.mark.parametrize("width", [2400, 4800])
 def test_bin_sort_wide_frame_fallback(gs, width):
     """Wide frames: 150 x 63 tiles (9,450: the direct emission, 19 x 8 super
