@@ -793,7 +793,7 @@ __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint3
     // all loads first, so that they are in flight together
     float v[kDcComps], u[kDcComps];
 #pragma unroll
-    for (int c = 0; c < kDcComps; ++c) v[c] = c0 + c < c1 ? A.sh[(c0 + c) * N + i] : 0.0f;
+    for (int c = 0; c < kDcComps; ++c) v[c] = c0 + c < c1 ? __builtin_nontemporal_load(&A.sh[(c0 + c) * N + i]) : 0.0f;
     if (merged) {
 #pragma unroll
       for (int c = 0; c < kDcComps; ++c) u[c] = c0 + c < c1 ? A.sh[(c0 + c) * N + j] : 0.0f;
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint3
     if (spawn) {
 #pragma unroll
       for (int c = 0; c < kDcComps; ++c)
-        if (c0 + c < c1) A.o_sh[(c0 + c) * cap + q] = v[c];
+        if (c0 + c < c1) __builtin_nontemporal_store(v[c], &A.o_sh[(c0 + c) * cap + q]);
     }
     if (merged) {
 #pragma unroll
@@ -810,7 +810,7 @@ __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint3
     if (put) {
 #pragma unroll
       for (int c = 0; c < kDcComps; ++c)
-        if (c0 + c < c1) A.o_sh[(c0 + c) * cap + o] = v[c];
+        if (c0 + c < c1) __builtin_nontemporal_store(v[c], &A.o_sh[(c0 + c) * cap + o]);
     }
     return;
   }

@@ -15,6 +15,8 @@ namespace gs {
 
 constexpr int kAdamSegs = 6;
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
 struct AdamSeg {
   float* p;
   const float* g;
@@ -47,17 +49,21 @@ __global__ __launch_bounds__(256) void k_adam_gaussians(AdamArgs a) {
     const AdamSeg& sg = a.seg[s];
     const int64_t e = 4 * (c - sg.chunk0);
     if (sg.vec) {
-      float4 p = reinterpret_cast<const float4*>(sg.p)[e / 4];
-      const float4 g = reinterpret_cast<const float4*>(sg.g)[e / 4];
-      float4 m = reinterpret_cast<const float4*>(sg.m)[e / 4];
-      float4 v = reinterpret_cast<const float4*>(sg.v)[e / 4];
-      adam_one(p.x, g.x, m.x, v.x, sg.lr, a);
-      adam_one(p.y, g.y, m.y, v.y, sg.lr, a);
-      adam_one(p.z, g.z, m.z, v.z, sg.lr, a);
-      adam_one(p.w, g.w, m.w, v.w, sg.lr, a);
-      reinterpret_cast<float4*>(sg.p)[e / 4] = p;
-      reinterpret_cast<float4*>(sg.m)[e / 4] = m;
-      reinterpret_cast<float4*>(sg.v)[e / 4] = v;
+      auto at = [&](const float* q) { return reinterpret_cast<const floatx4*>(q) + e / 4; };
+      floatx4 p = __builtin_nontemporal_load(at(sg.p)), m = __builtin_nontemporal_load(at(sg.m)),
+              v = __builtin_nontemporal_load(at(sg.v));
+      const floatx4 g = __builtin_nontemporal_load(at(sg.g));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float pk = p[k], mk = m[k], vk = v[k];
+        adam_one(pk, g[k], mk, vk, sg.lr, a);
+        p[k] = pk;
+        m[k] = mk;
+        v[k] = vk;
+      }
+      __builtin_nontemporal_store(p, reinterpret_cast<floatx4*>(sg.p) + e / 4);
+      __builtin_nontemporal_store(m, reinterpret_cast<floatx4*>(sg.m) + e / 4);
+      __builtin_nontemporal_store(v, reinterpret_cast<floatx4*>(sg.v) + e / 4);
     } else {
       const int64_t end = min(e + 4, sg.len);
       for (int64_t i = e; i < end; ++i) {
