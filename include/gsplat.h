@@ -304,8 +304,9 @@ gs_status gs_render_bwd_workspace(const gs_gaussians* g, int64_t k, const gs_cam
  *   deterministic = 1: no atomics, one partial per (tile, Gaussian) entry
  *     summed per Gaussian in the row-major order of its tile rectangle: the
  *     same bits on every run for a given schedule; 0: device atomics.
- *   schedule: as for gs_render_fwd (BALANCED plans from the work counts the
- *     forward left in t_ckpt).
+ *   schedule: as for gs_render_fwd, the forward's or another one (BALANCED and
+ *     MERGED plan from the work counts that every split's forward leaves in
+ *     t_ckpt).
  *   ws: gs_render_bwd_workspace bytes, 256-byte aligned, caller-owned.
  * Errors: INVALID_ARG for NULL arrays, bad sizes, an unknown schedule or a
  * small workspace (before any device work); HIP for launch failures. */

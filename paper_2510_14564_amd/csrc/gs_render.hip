@@ -652,10 +652,8 @@ __global__ __launch_bounds__(256) void k_render_fwd_light(const uint2* __restric
                                       con[k], done[k]);
   }
   const int64_t HW = static_cast<int64_t>(cam.width) * cam.height;
-  uint32_t mx = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    mx = max(mx, con[k]);
     if (pxi[k] < cam.width && pyi[k] < cam.height) {
       const int64_t pix = static_cast<int64_t>(pyi[k]) * cam.width + pxi[k];
       image[pix] = fmaf(T[k], cam.bg[0], a0[k]);
@@ -665,8 +663,14 @@ __global__ __launch_bounds__(256) void k_render_fwd_light(const uint2* __restric
       n_contrib[pix] = con[k];
     }
   }
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), o, 64)));
-  if (lane < 4) tile_work[4 * tile + lane] = lane == 0 ? mx : 0u;   // the tile's, in its first quadrant's place
+  // each quadrant's backward work count: a backward of another split cuts its
+  // waves' lists by them
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t mx = con[k];
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), o, 64)));
+    if (lane == 0) tile_work[4 * tile + k] = mx;
+  }
 }
 
 // Forward of frames of few tiles.  With fewer tiles than the chip holds

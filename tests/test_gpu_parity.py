@@ -577,6 +577,38 @@ def test_deterministic_backward(gs, name):
         say(f"  schedule {sched}: bit-identical reruns, worst rel err {worst:.2e}")
 
 
+@pytest.mark.parametrize("n,width,height", [(700, 320, 240), (4000, 800, 640)])
+def test_every_forward_split_serves_every_backward_split(gs, n, width, height):
+    """The backward's split need not be the forward's: for all nine pairs, both
+    reductions, the record gradients meet the staged tolerance.  Most tiles have
+    1 to 64 entries (MERGED's light tiles), some more; the frames have fewer
+    and more tiles than the forward of few tiles takes."""
+    say(f"[splits crossed] n={n} {width}x{height}")
+    scene = scenes.uniform_scene(n, 41, log_scale_mean=-3.2, log_scale_std=0.5, sh_degree=0)
+    cam = scenes.front_camera(width, height)
+    p, g, out = gpu_project(gs, scene, cam)
+    h = proj_host(out)
+    k, pl, ranges = gpu_bin_sort(gs, scene.n, out, cam)
+    o_pl, o_ranges, _, _ = oracle.bin_sort(h["u"], h["v"], h["radius"], h["depth"], width, height)
+    nt = (o_ranges[:, 1] - o_ranges[:, 0]).astype(np.int64)
+    assert ((nt > 0) & (nt <= 64)).sum() > 100 and (nt > 64).any()
+    G = scenes.upstream_grad(cam, 1001)
+    image, fT, nc, _ = gpu_render(gs, scene.n, out, pl, ranges, k, cam)
+    _, _, _, flips, amb, _ = check_render(image, fT, nc, h["rec"][:, :9], o_pl, o_ranges, cam)
+    G[:, amb] = 0.0
+    _, o_g2d, o_mass = oracle_render_bwd_sigma(h["rec"][:, :9], o_pl, o_ranges, cam, G, flips=flips)
+    splits = (gs.SCHEDULE_PLAIN, gs.SCHEDULE_BALANCED, gs.SCHEDULE_MERGED)
+    for fwd in splits:
+        image, fT, nc, ck = gpu_render(gs, scene.n, out, pl, ranges, k, cam, schedule=fwd)
+        for bwd in splits:
+            for det in (False, True):
+                g2d = gpu_render_bwd(gs, scene.n, out, pl, ranges, k, cam, fT, nc, ck, to_dev(G), deterministic=det,
+                                     schedule=bwd).cpu().numpy().T
+                for j, nm in enumerate("u v Sxx Sxy Syy o r g b".split()):
+                    grad_close(g2d[:, j], o_g2d[:, j], name=f"forward {fwd} backward {bwd} det {det} g2d.{nm}",
+                               mass=o_mass[:, j])
+
+
 @pytest.mark.parametrize("n", [1, 127, 128, 129, 255, 256, 257, 385])
 def test_deterministic_rows_at_the_edges_of_batches(gs, n):
     """One tile of n entries (a batch's sums wait for its waves in two parts of 128):
