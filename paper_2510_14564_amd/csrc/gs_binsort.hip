@@ -1016,6 +1016,16 @@ static int64_t direct_max_parts(int64_t n, int64_t cap, int ns) {
   return ceil_div(std::max<int64_t>(cap, 1), part_entries(n)) + ns;
 }
 
+// The workspace never shrinks as n grows, so that one sized for a run's largest
+// set serves the smaller ones: where the chunks or the parts get coarser with n, the
+// pieces that depend on them keep the largest size of any smaller set.
+static int64_t ws_chunks(int64_t n) { return std::min<int64_t>(kDirectChunks, ceil_div(std::max<int64_t>(n, 1), 64)); }
+static int64_t ws_parts(int64_t cap, int ns) { return ceil_div(std::max<int64_t>(cap, 1), kPartSmall) + ns; }
+static size_t ws_sort_state(int64_t n) {
+  const size_t fine = os_state_words(std::min(n, kOsSmallN), kOsThreads * kOsItemsSmall, kOsMaxPasses);
+  return n <= kOsSmallN ? fine : std::max(fine, os_state_words(n, kOsThreads * kOsItemsN, kOsMaxPasses));
+}
+
 // In-place inclusive prefix sums of `len` ints at p[0], p[stride], ... by one wave.
 __device__ __forceinline__ void wave_prefix_lds(int* p, int len, int stride, int lane) {
   int carry = 0;
@@ -1738,20 +1748,20 @@ static BinWs carve_bin(void* ws, int64_t n, int64_t cap, int tiles_x, int tiles_
   b.scan.total = b.readback;
   b.os.ghist = b.zero;
   b.os.err = reinterpret_cast<uint32_t*>(b.readback + 1);
-  b.os.state = c.take<uint32_t>(os_state_words(n, kOsThreads * (n <= kOsSmallN ? kOsItemsSmall : kOsItemsN), kOsMaxPasses));
+  b.os.state = c.take<uint32_t>(ws_sort_state(n));
   b.os.counters = c.take<uint32_t>(kOsMaxPasses);
   if (direct) {
     const size_t nt = static_cast<size_t>(tiles_x) * tiles_y;
     const int ns = super_dim(tiles_x) * super_dim(tiles_y);
-    const size_t chunks = static_cast<size_t>(direct_chunks(n));
-    const size_t parts = static_cast<size_t>(direct_max_parts(n, cap, ns));
+    const size_t chunks = static_cast<size_t>(ws_chunks(n));
+    const size_t parts = static_cast<size_t>(ws_parts(cap, ns));
     b.table = c.take<uint32_t>(chunks * ns);
     b.kfine = c.take<unsigned long long>(chunks);
     b.ctotal = c.take<uint32_t>(ns);
     b.cstart = c.take<uint32_t>(ns);
     b.total = c.take<uint32_t>(nt);
     b.start = c.take<uint32_t>(nt);
-    b.qcnt = c.take<uint32_t>(small_frame(n, static_cast<int64_t>(nt)) ? 4 * nt : 1);
+    b.qcnt = c.take<uint32_t>(small_frame(1, static_cast<int64_t>(nt)) ? 4 * nt : 1);
     b.pbase = c.take<uint32_t>(ns + 1);
     b.fits = c.take<uint32_t>(1);
     b.ftab = c.take<uint32_t>(parts * 64);

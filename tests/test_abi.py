@@ -268,3 +268,19 @@ def test_density_control_rejects_bad_arguments(gs, case):
 def test_density_control_workspace_grows_with_n(gs):
     a, b = gs.density_control_workspace(1000), gs.density_control_workspace(100000)
     assert b > a > 0 and b - a >= 60 * 99000
+
+
+@pytest.mark.parametrize("width,height", [(64, 64), (1600, 1064), (3840, 2160), (12000, 12000)])
+def test_bin_sort_workspace_serves_smaller_sets(gs, width, height):
+    """A buffer sized for a run's largest set and capacity serves every smaller
+    one: the workspace never shrinks as n or the capacity grows, also where the
+    number of chunks and the sizes of the sort's chunks and parts change."""
+    cs = gs.camera_struct(scenes.front_camera(width, height))
+    ns = [0, 1, 64, 4096, 16384, 16385, 65536, 65537, 131072, 131073, 1 << 18, (1 << 18) + 1, 300_000, 1 << 20, 3_000_000]
+    caps = [0, 1, 255, 256, 1024, 1 << 20, 8_000_000]
+    for cap in caps:
+        sizes = [gs.bin_sort_workspace(n, cap, cs) for n in ns]
+        assert sizes == sorted(sizes), (cap, list(zip(ns, sizes)))
+    for n in ns:
+        sizes = [gs.bin_sort_workspace(n, cap, cs) for cap in caps]
+        assert sizes == sorted(sizes), (n, list(zip(caps, sizes)))
