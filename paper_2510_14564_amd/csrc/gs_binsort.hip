@@ -19,10 +19,9 @@
 // Both keep the (depth, index) order inside each tile, so the result equals
 // the full sort bit for bit.
 #include "gs_internal.h"
+#include "gs_slots.h"
 
-#include <mutex>
 #include <optional>
-#include <vector>
 
 namespace gs {
 
@@ -1790,45 +1789,19 @@ __global__ void k_put_zero_k(unsigned long long* __restrict__ k_dev) {
 // Where the waiting call reads K: two words of pinned host memory that
 // k_tile_starts writes itself, so that no copy to pageable memory is queued
 // behind the lists (the call at 4,096 Gaussians: 70 -> 49 us of host time,
-// with the caller's cheaper stream lookup).  A slot
-// belongs to one call at a time and goes back to the free list when the call
-// returns; there are as many as calls ever ran at once (16 bytes each, kept
-// until the process ends).
-class KSlot {
- public:
-  KSlot() {
-    {
-      std::lock_guard<std::mutex> lock(mu());
-      if (!pool().empty()) {
-        p_ = pool().back();
-        pool().pop_back();
-      }
-    }
-    void* q = nullptr;
-    if (!p_ && hipHostMalloc(&q, 2 * sizeof(unsigned long long), hipHostMallocPortable) == hipSuccess)
-      p_ = static_cast<unsigned long long*>(q);
-    if (!p_) (void)hipGetLastError();   // no pinned memory: the caller copies instead
-  }
-  ~KSlot() {
-    if (!p_) return;
-    std::lock_guard<std::mutex> lock(mu());
-    pool().push_back(p_);
-  }
-  KSlot(const KSlot&) = delete;
-  KSlot& operator=(const KSlot&) = delete;
-  unsigned long long* get() const { return p_; }
-
- private:
-  static std::mutex& mu() {
-    static std::mutex* const m = new std::mutex;
-    return *m;
-  }
-  static std::vector<unsigned long long*>& pool() {
-    static std::vector<unsigned long long*>* const v = new std::vector<unsigned long long*>;
-    return *v;
-  }
-  unsigned long long* p_ = nullptr;
-};
+// with the caller's cheaper stream lookup).
+static SlotPool& k_slots() {
+  static SlotPool* const pool = new SlotPool(
+      []() -> unsigned long long* {
+        void* q = nullptr;
+        if (hipHostMalloc(&q, 2 * sizeof(unsigned long long), hipHostMallocPortable) == hipSuccess)
+          return static_cast<unsigned long long*>(q);
+        (void)hipGetLastError();   // no pinned memory: the caller copies instead
+        return nullptr;
+      },
+      [](unsigned long long* p) { (void)hipHostFree(p); }, 64);
+  return *pool;
+}
 
 gs_status run_bin_sort(int64_t n64, const gs_projected& proj, const DevCam& cam, void* ws, size_t ws_bytes,
                        uint32_t* point_list, int64_t capacity, uint32_t* ranges, int64_t* k_out,
@@ -1860,14 +1833,14 @@ gs_status run_bin_sort(int64_t n64, const gs_projected& proj, const DevCam& cam,
     }
     const uint32_t* order = b.order;
     unsigned long long rb[2] = {0ull, 0ull};
-    std::optional<KSlot> slot;
+    std::optional<Slot> slot;
     unsigned long long* k_put = k_dev;
     if (b.table) {
       // direct emission: no host wait between the depth sort and the
       // placement; K (and the look-back flag) are read once at the end
       const int tx = cam.tiles_x, ty = cam.tiles_y;
       const bool small = small_frame(n, ntiles);
-      if (!k_dev) k_put = slot.emplace().get();
+      if (!k_dev) k_put = slot.emplace(k_slots()).get();
       const StartArgs sa{ntiles, b.start, reinterpret_cast<uint2*>(ranges), static_cast<unsigned long long>(capacity),
                          small ? 0 : direct_chunks(n), b.kfine, b.readback, k_put, b.fits};
       const unsigned sgrid = static_cast<unsigned>(ceil_div(ntiles, 1024));
@@ -1915,6 +1888,7 @@ gs_status run_bin_sort(int64_t n64, const gs_projected& proj, const DevCam& cam,
     if (!k_put && (st = check_hip(hipMemcpyAsync(rb, b.readback, sizeof(rb), hipMemcpyDeviceToHost, s),
                                   "hipMemcpyAsync(K)")) != GS_OK) return st;
     if ((st = check_hip(hipStreamSynchronize(s), "hipStreamSynchronize")) != GS_OK) return st;
+    if (slot) slot->work_done();
     if (k_put) {
       rb[0] = k_put[0];
       rb[1] = k_put[1];

@@ -3,6 +3,7 @@ include/gsplat.h declares, and rejects bad arguments before any HIP call."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -284,3 +285,55 @@ def test_bin_sort_workspace_serves_smaller_sets(gs, width, height):
     for n in ns:
         sizes = [gs.bin_sort_workspace(n, cap, cs) for cap in caps]
         assert sizes == sorted(sizes), (n, list(zip(caps, sizes)))
+
+
+def test_pinned_slots_of_failed_calls_stay_out_of_the_pool(tmp_path):
+    """The pinned words that the waiting binning call reads K from: a slot goes
+    to another call only after the work that writes it has ended; a call that
+    fails with work queued keeps its slot out of the pool.  Threads never share a
+    slot, and the pool keeps a bounded number of them."""
+    src = tmp_path / "slots.cpp"
+    src.write_text(r"""
+#include <atomic>
+#include <set>
+#include <thread>
+#include "gs_slots.h"
+static std::atomic<int> made{0}, freed{0};
+static unsigned long long* make() { ++made; return new unsigned long long[2]; }
+static void drop(unsigned long long* p) { ++freed; delete[] p; }
+#define CHECK(c) do { if (!(c)) return __LINE__ % 250 + 1; } while (0)
+int main() {
+  gs::SlotPool pool(make, drop, 3);
+  unsigned long long *failed, *good;
+  { gs::Slot s(pool); failed = s.get(); }                     // error return: work may still write it
+  { gs::Slot s(pool); good = s.get(); CHECK(good != failed); s.work_done(); }
+  { gs::Slot s(pool); CHECK(s.get() == good); s.work_done(); }   // reused
+  for (int i = 0; i < 100; ++i) { gs::Slot s(pool); CHECK(s.get() != failed); s.work_done(); }
+  CHECK(made == 2 && freed == 0);
+  {   // six calls at once: six slots, of which three are kept
+    gs::Slot a(pool), b(pool), c(pool), d(pool), e(pool), f(pool);
+    CHECK((std::set<void*>{a.get(), b.get(), c.get(), d.get(), e.get(), f.get()}.size() == 6));
+    a.work_done(); b.work_done(); c.work_done(); d.work_done(); e.work_done(); f.work_done();
+  }
+  CHECK(made == 7 && freed == 3);
+  std::atomic<int> shared{0};
+  std::vector<std::thread> t;
+  for (int k = 1; k <= 8; ++k)
+    t.emplace_back([&, k] {
+      for (int i = 0; i < 2000; ++i) {
+        gs::Slot s(pool);
+        s.get()[0] = k;
+        std::this_thread::yield();
+        if (s.get()[0] != static_cast<unsigned long long>(k)) ++shared;
+        s.work_done();
+      }
+    });
+  for (auto& x : t) x.join();
+  CHECK(shared == 0 && made - freed <= 1 + 3);   // the failed call's, and those kept
+  return 0;
+}
+""")
+    exe = tmp_path / "slots"
+    csrc = os.path.join(ROOT, "paper_2510_14564_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", f"-I{csrc}", str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], timeout=60).returncode == 0
