@@ -373,6 +373,15 @@ __device__ __forceinline__ uint2 rect_at(uint2 rc, int shift) {
   return make_uint2(x0 | (xe << 16), y0 | (ye << 16));
 }
 
+// A rectangle's part in columns (by_x) or rows [b0, b1); empty where they do not meet.
+__device__ __forceinline__ uint2 band_of(uint2 rc, bool by_x, uint32_t b0, uint32_t b1) {
+  const uint32_t v = by_x ? rc.x : rc.y;
+  const uint32_t lo = max(v & 0xFFFFu, b0), hi = min(v >> 16, b1);
+  if (lo >= hi) return make_uint2(0u, 0u);
+  const uint32_t w = lo | (hi << 16);
+  return by_x ? make_uint2(w, rc.y) : make_uint2(rc.x, w);
+}
+
 // ------------------------------------------------------------ onesweep sort
 // Stable LSD radix sort of (key, value) pairs in passes of up to 8 bits, one
 // sweep per pass:
@@ -940,18 +949,21 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 // Coarse: the ranks are cut into up to 1024 chunks of equally many consecutive
 // ranks (a rank has one coarse entry per super tile its rectangle touches).
 // More chunks than the chip holds at once even out their different entry
-// counts; cutting at equal entry counts needs a scan of the counts first (two
-// launches) and gave fewer, longer chunks: 35.5 -> 10.9 us for the coarse
-// emission at 200k Gaussians, 40.2 -> 30.8 at 1M, besides the scan's 17-19.
+// counts, and chunks far above the mean are cut again (k_coarse_parts); cutting
+// at equal entry counts needs a scan of the counts first (two launches) and gave
+// fewer, longer chunks: 33.3 -> 12.2 us for the coarse emission at 200k Gaussians,
+// 35.2 -> 33.8 at 1M, besides the scan's 17-19.
 //  1. k_chunk_count: per chunk, the coarse entries of every super tile, from
 //     a 2D difference array of the chunk's super-tile rectangles in LDS (four
 //     LDS atomics per Gaussian, then prefix sums along rows and columns) --
 //     table[c][s]; it also adds up the tile counts (K).
 //  2. k_chunk_colscan: per super tile, the exclusive prefix over chunks (in
 //     place) and the total; k_coarse_parts: the super tiles' starts in the
-//     coarse list and the cut of each super tile's run into parts of at most
-//     1024 (small sets: 256) entries (numbered over the super tiles in turn).
-//  3. k_emit_coarse: one workgroup per chunk walks its ranks 256 at a time.
+//     coarse list, the cut of each super tile's run into parts of at most
+//     1024 (small sets: 256) entries (numbered over the super tiles in turn),
+//     and the cut of chunks with many entries into bands of super tiles.
+//  3. k_emit_coarse: one workgroup per chunk (or band of one) walks its ranks
+//     256 at a time.
 //     Rank 64 w + l of a group comes before rank 64 w' + l' on a super tile
 //     that both rectangles contain iff (w, l) < (w', l'); with per-wave 64-bit
 //     masks col[w][x] (lanes whose rectangle spans column x) and row[w][y],
@@ -980,6 +992,7 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 constexpr int kSuperShift = 3;            // super tiles of 8 x 8 tiles
 constexpr int kSuper = 1 << kSuperShift;
 constexpr int kDirectChunks = 1024;       // chunks at most
+constexpr unsigned long long kBandEntries = 4096;   // entries below which a chunk is not cut into bands
 constexpr size_t kLdsBudget = 65536;      // bytes of LDS per workgroup
 constexpr size_t kEmitStaticLds = 11776;  // k_emit_coarse's fixed arrays, rounded up
 // Coarse entries per part of the fine passes: sets of up to kSmallPartN
@@ -1010,6 +1023,8 @@ static bool direct_ok(int tiles_x, int tiles_y) {
 // Ranks per chunk: a whole number of waves, at most kDirectChunks chunks.
 static int direct_ranks(int64_t n) { return static_cast<int>(ceil_div(std::max<int64_t>(n, 1), 64 * kDirectChunks) * 64); }
 static int direct_chunks(int64_t n) { return static_cast<int>(ceil_div(std::max<int64_t>(n, 1), direct_ranks(n))); }
+// Workgroups of the coarse emission at most (k_coarse_parts).
+static int direct_items(int chunks) { return chunks + chunks / 2; }
 // parts at most: every super tile's run of at most `cap` coarse entries in total
 static int64_t direct_max_parts(int64_t n, int64_t cap, int ns) {
   return ceil_div(std::max<int64_t>(cap, 1), part_entries(n)) + ns;
@@ -1039,27 +1054,29 @@ __device__ __forceinline__ void wave_prefix_lds(int* p, int len, int stride, int
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectWaves = kDirectThreads / 64;
 
-// Per chunk: table[c][s] over the sx x sy super tiles, and the sum of the
+// Per chunk: table[c][s] over the sx x sy super tiles, the sum of the
 // chunk's tile counts in kfine[c] (added up by k_tile_starts: a thousand
 // atomics on one word queue for longer than the kernel runs, 21 us against
-// 15 at 1M Gaussians).
+// 15 at 1M Gaussians), and its coarse entries in kcoarse[c].
 constexpr int kCountThreads = 256;
 constexpr int kCountWaves = kCountThreads / 64;
 __global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks, const uint2* __restrict__ rect_rank,
                                                                int sx, int sy, uint32_t* __restrict__ table,
-                                                               unsigned long long* __restrict__ kfine) {
+                                                               unsigned long long* __restrict__ kfine,
+                                                               unsigned long long* __restrict__ kcoarse) {
   extern __shared__ int s_diff[];   // (sy + 1) rows of (sx + 1)
-  __shared__ unsigned long long s_k[kCountWaves];
+  __shared__ unsigned long long s_k[kCountWaves], s_kc[kCountWaves];
   const int c = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int pitch = sx + 1, cells = pitch * (sy + 1);
   for (int i = tid; i < cells; i += kCountThreads) s_diff[i] = 0;
   __syncthreads();
   const int r0 = c * ranks, r1 = min(n, r0 + ranks);
-  unsigned long long fine = 0;
+  unsigned long long fine = 0, coarse = 0;
   for (int r = r0 + tid; r < r1; r += kCountThreads) {
     const uint2 rc = rect_rank[r];
     fine += rect_count(rc);
     const uint2 sr = rect_at(rc, kSuperShift);
+    coarse += rect_count(sr);
     if (rect_count(sr) == 0) continue;
     const int x0 = static_cast<int>(sr.x & 0xFFFFu), xe = static_cast<int>(sr.x >> 16);
     const int y0 = static_cast<int>(sr.y & 0xFFFFu), ye = static_cast<int>(sr.y >> 16);
@@ -1068,13 +1085,17 @@ __global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks,
     atomicAdd(&s_diff[ye * pitch + x0], -1);
     atomicAdd(&s_diff[ye * pitch + xe], 1);
   }
-  for (int o = 32; o > 0; o >>= 1) fine += __shfl_xor(fine, o, 64);
-  if (lane == 0) s_k[wave] = fine;
+  for (int o = 32; o > 0; o >>= 1) {
+    fine += __shfl_xor(fine, o, 64);
+    coarse += __shfl_xor(coarse, o, 64);
+  }
+  if (lane == 0) { s_k[wave] = fine; s_kc[wave] = coarse; }
   __syncthreads();
   if (tid == 0) {
-    unsigned long long k = 0;
-    for (int w = 0; w < kCountWaves; ++w) k += s_k[w];
+    unsigned long long k = 0, kc = 0;
+    for (int w = 0; w < kCountWaves; ++w) { k += s_k[w]; kc += s_kc[w]; }
     kfine[c] = k;
+    kcoarse[c] = kc;
   }
   for (int y = wave; y < sy; y += kCountWaves) wave_prefix_lds(s_diff + y * pitch, sx, 1, lane);
   __syncthreads();
@@ -1219,11 +1240,41 @@ __global__ __launch_bounds__(1024) void k_tile_starts(const uint32_t* __restrict
 // super tiles in turn: parts pbase[s] .. pbase[s+1]-1 (pbase[ns]: all parts).
 // A coarse list longer than its buffer (capacity) gives no parts: K is at
 // least as large, so the frame is reported as not fitting.
+//
+// The second workgroup cuts the coarse emission's items: a chunk with more
+// than twice the mean of the chunks' coarse entries (kcoarse[c]) becomes bands of
+// super-tile columns or rows (the longer side, `side` of them), a workgroup
+// each.  Item i is (chunk, first | end << 16), nitems[0] their number, at most
+// direct_items: the cuts add at most the total over twice the mean, half the
+// chunks.  Equal ranks are not equal entries: near the camera consecutive ranks
+// cover most of the frame.  With 4,000 such Gaussians of 1M the emission takes
+// 43 us at 1600 x 1064 and 61 at 3840 x 2160, against 143 and 542 with a
+// workgroup per chunk; where no chunk is cut, the items cost it 1 us.
+struct ChunkItems {
+  int chunks, side;
+  const unsigned long long* kcoarse;
+  uint2* items;
+  uint32_t* nitems;
+};
 __global__ __launch_bounds__(1024) void k_coarse_parts(int ns, int part, const uint32_t* __restrict__ ctotal,
                                                        uint32_t* __restrict__ cstart, unsigned long long capacity,
-                                                       uint32_t* __restrict__ pbase) {
+                                                       uint32_t* __restrict__ pbase, ChunkItems a) {
   __shared__ unsigned long long s_w[16];
   const int tid = threadIdx.x;
+  if (blockIdx.x == 1) {
+    // chunk tid's bands (kDirectChunks = 1024 threads)
+    const unsigned long long mine = tid < a.chunks ? a.kcoarse[tid] : 0ull, chunks = static_cast<unsigned long long>(a.chunks);
+    unsigned long long all, nall;
+    block_exclusive_u64<1024>(mine, s_w, all);
+    const unsigned long long most = max(kBandEntries, 2ull * ((all + chunks - 1ull) / chunks));
+    const uint32_t side = static_cast<uint32_t>(a.side);
+    const uint32_t bands = tid < a.chunks ? static_cast<uint32_t>(min(static_cast<unsigned long long>(side), max(1ull, (mine + most - 1ull) / most))) : 0u;
+    const uint32_t at = static_cast<uint32_t>(block_exclusive_u64<1024>(bands, s_w, nall));
+    for (uint32_t b = 0; b < bands; ++b)
+      a.items[at + b] = make_uint2(static_cast<uint32_t>(tid), (b * side / bands) | (((b + 1u) * side / bands) << 16));
+    if (tid == 0) a.nitems[0] = static_cast<uint32_t>(nall);
+    return;
+  }
   const int per = (ns + 1023) / 1024;
   const int t0 = min(ns, tid * per), t1 = min(ns, t0 + per);
   const uint32_t upart = static_cast<uint32_t>(part);
@@ -1348,7 +1399,10 @@ __device__ __forceinline__ void place_entry(int rw, uint32_t e, int lo, const ui
   if (later == 0ull) s_delta[t] = static_cast<uint16_t>(within + 1u);   // at most 256
 }
 
-// Coarse emission over the sx x sy super tiles (tiles_x, tiles_y below).
+// Coarse emission over the sx x sy super tiles (tiles_x, tiles_y below): one
+// item (a chunk, or a band of one) per workgroup.  A band's workgroup sees every
+// rank's rectangle clipped to its columns or rows, and with it only its own
+// super tiles: their positions depend on no other band.
 // Groups of 256 ranks.  Waves 0-3 hold the group's ranks (64 each, a
 // rank-wave), loaded while the group before was placed, and build their
 // coverage masks; then the group's runs of 64 entries (rank-wave 0's, then
@@ -1368,7 +1422,10 @@ __global__ __launch_bounds__(kDirectThreads) __attribute__((amdgpu_waves_per_eu(
                                                                 const uint32_t* __restrict__ table,
                                                                 const uint32_t* __restrict__ start, int tiles_x,
                                                                 int tiles_y, unsigned long long* __restrict__ coarse,
-                                                                uint32_t capacity) {
+                                                                uint32_t capacity, const uint2* __restrict__ items,
+                                                                const uint32_t* __restrict__ nitems) {
+  const uint2 item = items[blockIdx.x];   // (both loads at once; past the items, what was there before)
+  if (blockIdx.x >= nitems[0]) return;
   // dynamic: col[4][tiles_x] row[4][tiles_y] (u64), then pos[ntiles] (u32), delta[ntiles] (u16)
   extern __shared__ unsigned long long s_dyn[];
   __shared__ uint32_t s_pre[4][65];   // per rank-wave: exclusive entry offsets, then the total
@@ -1381,7 +1438,9 @@ __global__ __launch_bounds__(kDirectThreads) __attribute__((amdgpu_waves_per_eu(
   const int edge = tiles_x + tiles_y;
   uint32_t* const s_pos = reinterpret_cast<uint32_t*>(s_dyn + 4 * edge);
   uint16_t* const s_delta = reinterpret_cast<uint16_t*>(s_pos + ntiles);
-  const int c = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int c = static_cast<int>(item.x), tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const uint32_t band0 = item.y & 0xFFFFu, band1 = item.y >> 16;
+  const bool by_x = tiles_x >= tiles_y;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t R0 = static_cast<uint32_t>(c) * static_cast<uint32_t>(ranks);
   const uint32_t R1 = min(static_cast<uint32_t>(n), R0 + static_cast<uint32_t>(ranks));
@@ -1409,7 +1468,7 @@ __global__ __launch_bounds__(kDirectThreads) __attribute__((amdgpu_waves_per_eu(
       const uint32_t rl = min(r0 + 256u + static_cast<uint32_t>(tid), R1 - 1u);
       nfr = rect_rank[rl];
       ngid = order[rl];
-      const uint2 rc = rect_at(fr, kSuperShift);
+      const uint2 rc = band_of(rect_at(fr, kSuperShift), by_x, band0, band1);
       const uint32_t cnt = rect_count(rc);
       s_rect[tid] = rc;
       s_frect[tid] = fr;
@@ -1713,7 +1772,9 @@ struct BinWs {
   OsWs os;                        // depth sort state
   uint32_t* zero;                 // its digit counts, K and the error flag, cleared by k_depth_keys
   unsigned long long* readback;   // [0] K, [1] the error flag
-  unsigned long long* kfine;      // direct emission: the tile counts' sum per chunk
+  unsigned long long *kfine, *kcoarse;   // direct emission: per chunk, the tile counts' sum and the coarse entries
+  uint2* items;                   // direct emission: the coarse emission's items and their number
+  uint32_t* nitems;
   // direct emission: chunk x super-tile table, super-tile totals and starts,
   // tile totals and starts (and quarter counts, small frames), the parts, per
   // part x tile counts, and the coarse list
@@ -1756,6 +1817,9 @@ static BinWs carve_bin(void* ws, int64_t n, int64_t cap, int tiles_x, int tiles_
     const size_t parts = static_cast<size_t>(ws_parts(cap, ns));
     b.table = c.take<uint32_t>(chunks * ns);
     b.kfine = c.take<unsigned long long>(chunks);
+    b.kcoarse = c.take<unsigned long long>(chunks);
+    b.items = c.take<uint2>(static_cast<size_t>(direct_items(static_cast<int>(chunks))));
+    b.nitems = c.take<uint32_t>(1);
     b.ctotal = c.take<uint32_t>(ns);
     b.cstart = c.take<uint32_t>(ns);
     b.total = c.take<uint32_t>(nt);
@@ -1858,15 +1922,15 @@ gs_status run_bin_sort(int64_t n64, const gs_projected& proj, const DevCam& cam,
         const unsigned fgrid = static_cast<unsigned>(std::min<int64_t>(direct_max_parts(n, capacity, ns), kFineGrid));
         const uint32_t cap32 = static_cast<uint32_t>(std::min<int64_t>(capacity, UINT32_MAX));
         { TimedLaunch gs_tl("k_chunk_count", s); k_chunk_count<<<chunks, kCountThreads, sizeof(int) * (sx + 1) * (sy + 1), s>>>(
-            n, ranks, b.rect_rank, sx, sy, b.table, b.kfine); }
+            n, ranks, b.rect_rank, sx, sy, b.table, b.kfine, b.kcoarse); }
         if ((st = check_launch("k_chunk_count")) != GS_OK) return st;
         { TimedLaunch gs_tl("k_chunk_colscan", s); k_chunk_colscan<<<static_cast<unsigned>(ceil_div(ns, 16)), 1024, 0, s>>>(chunks, ns, b.table, b.ctotal); }
         if ((st = check_launch("k_chunk_colscan")) != GS_OK) return st;
-        { TimedLaunch gs_tl("k_coarse_parts", s); k_coarse_parts<<<1, 1024, 0, s>>>(ns, part_entries(n), b.ctotal, b.cstart, static_cast<unsigned long long>(capacity),
-                                                                                    b.pbase); }
+        { TimedLaunch gs_tl("k_coarse_parts", s); k_coarse_parts<<<2, 1024, 0, s>>>(ns, part_entries(n), b.ctotal, b.cstart, static_cast<unsigned long long>(capacity),
+                                                                                    b.pbase, ChunkItems{chunks, std::max(sx, sy), b.kcoarse, b.items, b.nitems}); }
         if ((st = check_launch("k_coarse_parts")) != GS_OK) return st;
-        { TimedLaunch gs_tl("k_emit_coarse", s); k_emit_coarse<<<chunks, kDirectThreads, emit_dyn_lds(sx, sy), s>>>(
-            n, ranks, order, b.rect_rank, b.table, b.cstart, sx, sy, b.coarse, cap32); }
+        { TimedLaunch gs_tl("k_emit_coarse", s); k_emit_coarse<<<direct_items(chunks), kDirectThreads, emit_dyn_lds(sx, sy), s>>>(
+            n, ranks, order, b.rect_rank, b.table, b.cstart, sx, sy, b.coarse, cap32, b.items, b.nitems); }
         if ((st = check_launch("k_emit_coarse")) != GS_OK) return st;
         const size_t pb_lds = sizeof(uint32_t) * (static_cast<size_t>(ns) + 1);
         const bool fine = part_entries(n) == kPartSmall;

@@ -784,6 +784,63 @@ def test_bin_sort_many_tiles_per_group(gs):
     say(f"  K={k}, {sum(wide)} of {len(wide)} aligned rank groups wide, bit-exact")
 
 
+def _near_camera_scene(n, n_near, seed):
+    """Small Gaussians everywhere and n_near large ones right before the camera,
+    each covering the whole frame: the first depth ranks hold most of the entries."""
+    sc = scenes.uniform_scene(n, seed, log_scale_mean=-4.5, log_scale_std=0.3, sh_degree=0)
+    means, ls = sc.means.copy(), sc.log_scales.copy()
+    means[:2, :n_near] *= np.float32(0.3)
+    means[2, :n_near] = np.float32(-2.2) + np.float32(0.01) * np.abs(means[2, :n_near])
+    ls[:, :n_near] = np.float32(-0.9)
+    return dataclasses.replace(sc, means=means, log_scales=ls)
+
+
+@pytest.mark.parametrize("n,n_near,width,height", [(140000, 1000, 1600, 1064), (140000, 1000, 1064, 1600),
+                                                   (70000, 3000, 900, 40), (20000, 300, 2000, 1500)])
+def test_bin_sort_near_camera_lists(gs, n, n_near, width, height):
+    """Chunks of depth ranks with many times the mean of entries, which the
+    coarse emission cuts into bands of super-tile columns (wide frames) or rows
+    (tall ones): the oracle's lists bit for bit."""
+    scene = _near_camera_scene(n, n_near, 96)
+    cam = scenes.front_camera(width, height)
+    say(f"[bin/sort near camera] n={n} {width}x{height}")
+    p, g, out = gpu_project(gs, scene, cam)
+    h = proj_host(out)
+    k, pl, ranges = gpu_bin_sort(gs, n, out, cam)
+    o_pl, o_ranges, _, _ = oracle.bin_sort(h["u"], h["v"], h["radius"], h["depth"], width, height)
+    assert k == len(o_pl) and k > n_near * gs.n_tiles(gs.camera_struct(cam)) // 2
+    assert np.array_equal(pl[:k].cpu().numpy().view(np.uint32), o_pl), "point_list"
+    assert np.array_equal(ranges.cpu().numpy().view(np.uint32), o_ranges), "ranges"
+
+
+def test_bin_sort_near_camera_is_balanced(gs):
+    """The coarse emission takes about as long with the widest Gaussians first in
+    depth as with the same Gaussians at shuffled depths (a workgroup per chunk of
+    ranks: 4 times as long)."""
+    n = 600_000
+    cam = scenes.front_camera(1600, 1064)
+    cs = gs.camera_struct(cam)
+    p, g, out = gpu_project(gs, _near_camera_scene(n, 4000, 97), cam)
+    k, _, ranges = gpu_bin_sort(gs, n, out, cam)
+    ws = torch.empty(gs.bin_sort_workspace(n, k, cs), dtype=torch.uint8, device=DEV)
+    pl = torch.empty(k, dtype=torch.int32, device=DEV)
+
+    def emission():
+        best = float("inf")
+        for _ in range(8):
+            gs.kernel_timer_start()
+            assert gs.bin_sort(n, out, cs, ws, pl, ranges) == k
+            torch.cuda.synchronize()
+            best = min(best, gs.kernel_timer_stop()["k_emit_coarse"][1])
+        return best
+
+    near = emission()
+    out.depth.copy_(out.depth[torch.randperm(n, generator=torch.Generator().manual_seed(3)).to(DEV)])
+    mixed = emission()
+    say(f"  K={k}: emission {near * 1e3:.0f} us in depth order, {mixed * 1e3:.0f} us shuffled")
+    assert near < 2 * mixed
+
+
 def _depth_case_scene(kind, n=20000, seed=95):
     """Scenes whose depth keys exercise the depth sort's digit structure
     (camera at distance 3 on the z axis: depth = z + 3)."""
