@@ -1305,8 +1305,9 @@ __global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const ui
     first = static_cast<uint32_t>(it.z);
     len = static_cast<uint32_t>(it.w);
   } else {
-    tile = tile_of_block(plan, blockIdx.x);
-    if (tile < 0) return;
+    // neighbouring tiles on one XCD: a Gaussian's atomics meet in its L2 (in tile
+    // order over all eight 1054 us against 656 for 1,000 wide Gaussians at 7680 x 4320)
+    tile = xcd_remap(blockIdx.x, gridDim.x);
     const uint2 rg = ranges[tile];
     first = rg.x;
     len = rg.y - rg.x;
