@@ -686,18 +686,27 @@ __global__ __launch_bounds__(256) void k_render_fwd_light(const uint2* __restric
 //    16 pixels instead of 64);
 //  - entries are tested against the box of the wave's pixels that have not
 //    stopped: one that only reaches stopped pixels changes nothing;
-//  - kFewBatches batches are staged at a time, and the next ones' records are
-//    gathered while these are walked.
+//  - a batch (kFewBatches) is staged at a time, and the next one's records are
+//    gathered while it is walked.
 // Every pixel takes the same steps in the same order as in k_render_fwd: the
 // outputs are the same bits.
-// Measured (forward, us; this against k_render_fwd): 256 tiles, 500k Gaussians
-// on a 203 x 131 frame 360 : 2094; 64 tiles, 4,096 Gaussians 23 : 40; 1,200
-// tiles 56 : 67, 122 : 176 and 194 : 290 at 20k, 200k and 1M Gaussians; 1,900
-// tiles 72 : 56, 146 : 147 and 207 : 210; 2,500 tiles 80 : 59, 182 : 139 and
-// 259 : 232 (each quadrant stages the tile's list for itself, which costs
-// once the chip is full).  The line lies between 1,200 and 1,900.
-constexpr int kFewTiles = 1280;
-constexpr int kFewBatches = 2;
+// One batch at a time takes 17 KB of LDS and 71 registers, seven workgroups to a
+// CU, where two took 33 KB and 107, four to a CU, and were no faster where the chip
+// is not full: 625 tiles, 100k clustered Gaussians 76 us against 89, uniform ones 50
+// against 58; 117 tiles the same.
+// Measured (forward, us; this against k_render_fwd): 16 tiles, 20k clustered Gaussians
+// 130 : 539, uniform ones 47 : 123; 256 tiles 42 : 104 and 33 : 52; 400 tiles 43 : 92 and
+// 35 : 45, and no set on up to 400 tiles is slower by more than 0.5 us.  The chip holds
+// the quadrants of 448 tiles; beyond that they queue, and each stages its tile's list for
+// itself.  625 tiles, 20 to 1,500 uniform Gaussians (up to 25 entries a tile) 9 : 7 to
+// 16 : 12, 20k (330 entries, all tiles alike) 45 : 41, clustered ones 43 : 76, 400k 55 : 57 and
+// 113 : 217; 900 tiles, 100k 56 : 41 and 85 : 113; 1,225 tiles 68 : 42 and 87 : 96.  So up
+// to 400 tiles any set, up to 640 those with 64 entries a tile and more.
+constexpr int kFewTiles = 400, kFewLongTiles = 640, kFewLongMean = 64;
+static bool few_tiles(int ntiles, int64_t k) {
+  return ntiles <= kFewTiles || (ntiles <= kFewLongTiles && k >= static_cast<int64_t>(kFewLongMean) * ntiles);
+}
+constexpr int kFewBatches = 1;
 constexpr int kFewChunk = kFewBatches * kBatch;
 
 struct FewRec {
@@ -1021,7 +1030,7 @@ gs_status launch_render_fwd(const gs_projected& proj, const uint32_t* point_list
                                                       reinterpret_cast<const float4*>(proj.records), cam, image,
                                                       final_T, n_contrib, t_ckpt, nullptr, plan, tile_work, c_ckpt,
                                                       cplane);
-  } else if (ntiles <= kFewTiles && !plan) {
+  } else if (few_tiles(ntiles, k) && !plan) {
     TimedLaunch gs_tl("k_render_fwd_few", s);
     k_render_fwd_few<<<4 * ntiles, 256, 0, s>>>(reinterpret_cast<const uint2*>(ranges), point_list,
                                                 reinterpret_cast<const float4*>(proj.records), cam, image, final_T,

@@ -743,6 +743,26 @@ def test_few_tiles_forward_is_the_same_bits(gs, n, width, height):
     say(f"  {n} on {width}x{height}: K={k}, longest list {int((ranges[:, 1] - ranges[:, 0]).max())}")
 
 
+@pytest.mark.parametrize("n,width,height,few", [(50, 320, 320, True), (20000, 320, 320, True),
+                                                (50, 336, 320, False), (20000, 336, 320, True),
+                                                (20000, 512, 320, True), (500, 512, 320, False),
+                                                (20000, 528, 320, False)])
+def test_few_tiles_forward_where_it_is_chosen(gs, n, width, height, few):
+    """The forward of few tiles runs up to 400 tiles, and up to 640 of at least 64
+    entries each on average; on either side of both lines the image, final_T and
+    n_contrib are MERGED's, bit for bit."""
+    scene = scenes.uniform_scene(n, 99, log_scale_mean=-3.4, log_scale_std=0.5, sh_degree=0)
+    cam = scenes.front_camera(width, height)
+    p, g, out = gpu_project(gs, scene, cam)
+    k, pl, ranges = gpu_bin_sort(gs, n, out, cam)
+    want = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=gs.SCHEDULE_MERGED)[:3]
+    for sched in (gs.SCHEDULE_PLAIN, gs.SCHEDULE_BALANCED):
+        gs.kernel_timer_start()
+        got = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=sched)[:3]
+        assert ("k_render_fwd_few" in gs.kernel_timer_stop()) == few
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), f"schedule {sched}"
+
+
 def _slab_scene(n_small=20000, n_big=700, seed=93):
     """Small Gaussians everywhere plus large ones in a thin depth slab: rank
     groups inside the slab touch thousands of tiles, the others a few hundred."""
