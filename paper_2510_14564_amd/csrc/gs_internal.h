@@ -137,6 +137,21 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Passes over arrays that nothing reads again soon go past the caches
+// (non-temporal) where the arrays are too large to wait there for their next
+// reader: element i at p, read or written once.
+template <bool NT, class P>
+__device__ __forceinline__ auto load_once(P p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, class P, class V>
+__device__ __forceinline__ void store_once(V v, P p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+constexpr double kCacheBytes = 268435456.0;   // the last-level cache
+
 // Per-Gaussian gradient accumulator rows of the compositing backward (atomic
 // mode): nine sums padded to 48 bytes (three float4s; a row lies within one
 // 128-byte L2 line for six Gaussians in eight and straddles two for the

@@ -40,6 +40,11 @@ __device__ __forceinline__ void adam_one(float& p, float g, float& m, float& v, 
   p = p - lr * (m / a.bc1) / (sqrtf(v / a.bc2) + a.eps);
 }
 
+// NT: the four arrays go past the caches, which cannot hold them until the
+// next step.  us a call, kept in the caches against past them: 150k Gaussians of degree 3 (142
+// MB in the four arrays) 41 : 46; 250k (236 MB) 67 : 74; 700k of degree 1 (258 MB) 71 : 77; 300k of
+// degree 3 (283 MB) 78 : 76; 500k (472 MB) 151 : 135; 1M (944 MB) 324 : 277.
+template <bool NT>
 __global__ __launch_bounds__(256) void k_adam_gaussians(AdamArgs a) {
   for (int64_t c = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; c < a.chunks;
        c += static_cast<int64_t>(gridDim.x) * 256) {
@@ -50,9 +55,8 @@ __global__ __launch_bounds__(256) void k_adam_gaussians(AdamArgs a) {
     const int64_t e = 4 * (c - sg.chunk0);
     if (sg.vec) {
       auto at = [&](const float* q) { return reinterpret_cast<const floatx4*>(q) + e / 4; };
-      floatx4 p = __builtin_nontemporal_load(at(sg.p)), m = __builtin_nontemporal_load(at(sg.m)),
-              v = __builtin_nontemporal_load(at(sg.v));
-      const floatx4 g = __builtin_nontemporal_load(at(sg.g));
+      floatx4 p = load_once<NT>(at(sg.p)), m = load_once<NT>(at(sg.m)), v = load_once<NT>(at(sg.v));
+      const floatx4 g = load_once<NT>(at(sg.g));
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float pk = p[k], mk = m[k], vk = v[k];
@@ -61,9 +65,9 @@ __global__ __launch_bounds__(256) void k_adam_gaussians(AdamArgs a) {
         m[k] = mk;
         v[k] = vk;
       }
-      __builtin_nontemporal_store(p, reinterpret_cast<floatx4*>(sg.p) + e / 4);
-      __builtin_nontemporal_store(m, reinterpret_cast<floatx4*>(sg.m) + e / 4);
-      __builtin_nontemporal_store(v, reinterpret_cast<floatx4*>(sg.v) + e / 4);
+      store_once<NT>(p, reinterpret_cast<floatx4*>(sg.p) + e / 4);
+      store_once<NT>(m, reinterpret_cast<floatx4*>(sg.m) + e / 4);
+      store_once<NT>(v, reinterpret_cast<floatx4*>(sg.v) + e / 4);
     } else {
       const int64_t end = min(e + 4, sg.len);
       for (int64_t i = e; i < end; ++i) {
@@ -121,7 +125,13 @@ gs_status launch_adam_gaussians(int64_t n, int sh_degree, const gs_param_arrays&
   a.bc2 = static_cast<float>(1.0 - std::pow(static_cast<double>(cfg.beta2), cfg.step));
   if (chunks == 0) return GS_OK;
   const unsigned grid = static_cast<unsigned>(std::min<int64_t>(ceil_div(chunks, 256), 1 << 20));
-  { TimedLaunch gs_tl("k_adam_gaussians", s); k_adam_gaussians<<<grid, 256, 0, s>>>(a); }
+  if (4.0 * 16.0 * static_cast<double>(chunks) > kCacheBytes) {
+    TimedLaunch gs_tl("k_adam_gaussians<true>", s);
+    k_adam_gaussians<true><<<grid, 256, 0, s>>>(a);
+  } else {
+    TimedLaunch gs_tl("k_adam_gaussians<false>", s);
+    k_adam_gaussians<false><<<grid, 256, 0, s>>>(a);
+  }
   return check_launch("k_adam_gaussians");
 }
 

@@ -128,13 +128,22 @@ __device__ __forceinline__ void alpha_support(const Geo& g, float& ex, float& ey
 
 constexpr int kProjThreads = 256;
 
-// Every input is read once a call and none of the parameters' gradients is read
-// before the next optimiser step: they go past the caches (non-temporal), which
-// then keep what the step does read again.  Written the ordinary way, the
-// gradients' 236 bytes per Gaussian leave the caches during the next call's
-// projection: 88 us for it against 61 at 1M Gaussians, 118 against 86 at 1.5M (the
-// backward 67 and 66, 93 and 98).
-template <int DEG>
+// NT: every input is read once a call, and the parameters' gradients (but the
+// learned colour's dL/dmean) not before the optimiser's step: they go past the
+// caches, which then keep what the step does read again.  That pays once the
+// parameters and their gradients leave little room there (project_streams).
+// This kernel, the backward's and a following optimiser step together, us, kept in
+// the caches against past them: degree 3, 150k Gaussians (71 MB of parameters and
+// gradients) 72 : 77; 400k (189 MB) 160 : 170; 500k (236 MB) 205 : 206; 1M 405 : 405; degree 1,
+// 1M (184 MB) 184 : 189; without an optimiser, 250k (118 MB) 36 : 44; 500k 77 : 68; 1M 157 : 126 (the
+// projection alone 90 : 61: the gradients, 236 bytes per Gaussian, leave the caches
+// during it).  So the line is at 200 MB.
+static bool project_streams(int64_t n, int degree) {
+  const double floats = 11.0 + (degree < 0 ? 0.0 : 3.0 * (degree + 1) * (degree + 1));
+  return 2.0 * 4.0 * floats * static_cast<double>(n) > 200e6;
+}
+
+template <int DEG, bool NT>
 __global__ __launch_bounds__(kProjThreads) void k_project(int n, const float* __restrict__ means,
                                                  const float* __restrict__ log_scales,
                                                  const float* __restrict__ quats, const float* __restrict__ logits,
@@ -147,10 +156,8 @@ __global__ __launch_bounds__(kProjThreads) void k_project(int n, const float* __
   const unsigned l = threadIdx.x;
   // element i of row k of a [rows][n] field
   auto at = [&](auto* p, int k) -> auto& { return soa_row<kProjThreads>(p, k, n)[l]; };
-  // the same for what no later kernel finds in a cache: loaded, or stored, without
-  // keeping it there (see the measurements above k_project)
-  auto once = [&](auto* p, int k) { return __builtin_nontemporal_load(&soa_row<kProjThreads>(p, k, n)[l]); };
-  auto put = [&](auto* p, int k, float v) { __builtin_nontemporal_store(v, &soa_row<kProjThreads>(p, k, n)[l]); };
+  auto once = [&](auto* p, int k) { return load_once<NT>(&soa_row<kProjThreads>(p, k, n)[l]); };
+  auto put = [&](auto* p, int k, float v) { store_once<NT>(v, &soa_row<kProjThreads>(p, k, n)[l]); };
   constexpr int NC = DEG < 0 ? 0 : (DEG + 1) * (DEG + 1);
   float m[3], s[3], q[4];
 #pragma unroll
@@ -245,22 +252,26 @@ gs_status launch_project(const gs_gaussians& g, const DevCam& cam, gs_projected&
   if (n == 0) return GS_OK;
   const dim3 block(kProjThreads), grid(static_cast<unsigned>(ceil_div(n, kProjThreads)));
   float4* rec = reinterpret_cast<float4*>(out.records);
-  if (g.colour_mode == 1) {
-    { TimedLaunch gs_tl("k_project<-1>", s); k_project<-1><<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, nullptr, cam, rec, out.depth,
-                                         out.radius, out.tiles_touched, nullptr); }
+  const bool mlp = g.colour_mode == 1;
+  const int degree = mlp ? -1 : std::min(std::max(g.sh_degree, 0), 3);
+  const bool nt = project_streams(n, degree);
+  {
+    // the kernel's own template name, as profilers report it
+    static const char* const kNames[2][5] = {
+        {"k_project<-1, false>", "k_project<0, false>", "k_project<1, false>", "k_project<2, false>", "k_project<3, false>"},
+        {"k_project<-1, true>", "k_project<0, true>", "k_project<1, true>", "k_project<2, true>", "k_project<3, true>"}};
+    static decltype(&k_project<0, false>) const kKernels[2][5] = {
+        {k_project<-1, false>, k_project<0, false>, k_project<1, false>, k_project<2, false>, k_project<3, false>},
+        {k_project<-1, true>, k_project<0, true>, k_project<1, true>, k_project<2, true>, k_project<3, true>}};
+    TimedLaunch gs_tl(kNames[nt][degree + 1], s);
+    kKernels[nt][degree + 1]<<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, mlp ? nullptr : g.sh, cam, rec,
+                                                    out.depth, out.radius, out.tiles_touched,
+                                                    mlp ? nullptr : out.colour_grad);
+  }
+  if (mlp) {
     gs_status st = check_launch("k_project");
     if (st != GS_OK) return st;
     return launch_mlp_render(n, g.latents, g.means, out.radius, cam, g.mlp, out.records, s);
-  }
-  switch (g.sh_degree) {
-    case 0: { TimedLaunch gs_tl("k_project<0>", s); k_project<0><<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, g.sh, cam, rec,
-                                                 out.depth, out.radius, out.tiles_touched, out.colour_grad); } break;
-    case 1: { TimedLaunch gs_tl("k_project<1>", s); k_project<1><<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, g.sh, cam, rec,
-                                                 out.depth, out.radius, out.tiles_touched, out.colour_grad); } break;
-    case 2: { TimedLaunch gs_tl("k_project<2>", s); k_project<2><<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, g.sh, cam, rec,
-                                                 out.depth, out.radius, out.tiles_touched, out.colour_grad); } break;
-    default: { TimedLaunch gs_tl("k_project<3>", s); k_project<3><<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, g.sh, cam, rec,
-                                                  out.depth, out.radius, out.tiles_touched, out.colour_grad); } break;
   }
   return check_launch("k_project");
 }
@@ -282,7 +293,7 @@ gs_status launch_project(const gs_gaussians& g, const DevCam& cam, gs_projected&
 // non-NULL, the densification statistics of the view are accumulated:
 // stat_grad[i] += |(dL/du, dL/dv)| (pixel units) and stat_count[i] += 1 for
 // every Gaussian whose footprint meets a tile.
-template <int DEG, bool ROWS>
+template <int DEG, bool ROWS, bool NT>
 __global__ __launch_bounds__(kProjThreads) void k_project_bwd(int n, const float* __restrict__ means,
                                                      const float* __restrict__ log_scales,
                                                      const float* __restrict__ quats,
@@ -300,10 +311,8 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd(int n, const float
   const unsigned l = threadIdx.x;
   // element i of row k of a [rows][n] field
   auto at = [&](auto* p, int k) -> auto& { return soa_row<kProjThreads>(p, k, n)[l]; };
-  // the same for what no later kernel finds in a cache: loaded, or stored, without
-  // keeping it there (see k_project)
-  auto once = [&](auto* p, int k) { return __builtin_nontemporal_load(&soa_row<kProjThreads>(p, k, n)[l]); };
-  auto put = [&](auto* p, int k, float v) { __builtin_nontemporal_store(v, &soa_row<kProjThreads>(p, k, n)[l]); };
+  auto once = [&](auto* p, int k) { return load_once<NT>(&soa_row<kProjThreads>(p, k, n)[l]); };   // NT: see k_project
+  auto put = [&](auto* p, int k, float v) { store_once<NT>(v, &soa_row<kProjThreads>(p, k, n)[l]); };
   // DEG < 0: colour comes from the learned decoder, whose backward adds its
   // share to dL/dmean afterwards; only the geometry is differentiated here.
   // cgrad (from the projection): d colour / d direction and the clamp
@@ -503,37 +512,23 @@ gs_status launch_project_bwd(const gs_gaussians& g, const DevCam& cam, const int
   const dim3 block(kProjThreads), grid(static_cast<unsigned>(ceil_div(n, kProjThreads)));
   float* sg = stats ? stats->grad_norm_sum : nullptr;
   uint32_t* sc = stats ? stats->visible_count : nullptr;
-#define GS_PB(D, R)                                                                                               \
-  k_project_bwd<D, R><<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, g.sh, cam, g2d,          \
-                                             gr.means, gr.log_scales, gr.quats, gr.logits, gr.sh, tiles_touched, \
-                                             sg, sc, cgrad)
+  const int degree = g.colour_mode == 1 ? -1 : std::min(std::max(g.sh_degree, 0), 3);
+  const bool nt = project_streams(n, degree);
   {
     // the kernel's own template name, as profilers report it
-    static const char* const kNames[2][4] = {
-        {"k_project_bwd<0, false>", "k_project_bwd<1, false>", "k_project_bwd<2, false>", "k_project_bwd<3, false>"},
-        {"k_project_bwd<0, true>", "k_project_bwd<1, true>", "k_project_bwd<2, true>", "k_project_bwd<3, true>"}};
-    TimedLaunch gs_tl(g.colour_mode == 1 ? (rows ? "k_project_bwd<-1, true>" : "k_project_bwd<-1, false>")
-                                         : kNames[rows ? 1 : 0][std::min(std::max(g.sh_degree, 0), 3)], s);
-    if (g.colour_mode == 1) {
-      if (rows) GS_PB(-1, true);
-      else GS_PB(-1, false);
-    } else if (rows) {
-      switch (g.sh_degree) {
-        case 0: GS_PB(0, true); break;
-        case 1: GS_PB(1, true); break;
-        case 2: GS_PB(2, true); break;
-        default: GS_PB(3, true); break;
-      }
-    } else {
-      switch (g.sh_degree) {
-        case 0: GS_PB(0, false); break;
-        case 1: GS_PB(1, false); break;
-        case 2: GS_PB(2, false); break;
-        default: GS_PB(3, false); break;
-      }
-    }
-  }
+#define GS_PB(D, R) {{"k_project_bwd<" #D ", " #R ", false>", k_project_bwd<D, R, false>}, \
+                     {"k_project_bwd<" #D ", " #R ", true>", k_project_bwd<D, R, true>}}
+    static const struct {
+      const char* name;
+      decltype(&k_project_bwd<0, false, false>) kernel;
+    } kForms[2][5][2] = {{GS_PB(-1, false), GS_PB(0, false), GS_PB(1, false), GS_PB(2, false), GS_PB(3, false)},
+                         {GS_PB(-1, true), GS_PB(0, true), GS_PB(1, true), GS_PB(2, true), GS_PB(3, true)}};
 #undef GS_PB
+    const auto& form = kForms[rows][degree + 1][nt];
+    TimedLaunch gs_tl(form.name, s);
+    form.kernel<<<grid, block, 0, s>>>(n, g.means, g.log_scales, g.quats, g.logits, g.sh, cam, g2d, gr.means,
+                                       gr.log_scales, gr.quats, gr.logits, gr.sh, tiles_touched, sg, sc, cgrad);
+  }
   gs_status st = check_launch("k_project_bwd");
   if (st != GS_OK || g.colour_mode != 1) return st;
   return launch_mlp_render_bwd(n, g.latents, g.means, radius, cam, g.mlp, g2d, rows, gr.latents, gr.means, gr.mlp, ws,

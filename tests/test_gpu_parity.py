@@ -763,6 +763,71 @@ def test_few_tiles_forward_where_it_is_chosen(gs, n, width, height, few):
         assert all(torch.equal(a, b) for a, b in zip(got, want)), f"schedule {sched}"
 
 
+def _gpu_scene(n, degree, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    r = lambda *shape: torch.randn(shape, generator=g, device=DEV)
+    return dict(means=r(3, n) * 0.5, log_scales=r(3, n) * 0.5 - 4.0, quats=r(4, n), logits=r(n),
+                sh=r((degree + 1) ** 2, 3, n) * 0.1)
+
+
+@pytest.mark.parametrize("n,degree", [(450_000, 3), (1_150_000, 1), (423_000, 3)])
+def test_projection_of_large_sets_is_the_same_bits(gs, n, degree):
+    """Sets whose parameters and gradients pass 200 MB are projected, forward and
+    backward, past the caches (423,000 of degree 3 lie just below).  Each Gaussian
+    gets the bits that it gets in a small set."""
+    cam = scenes.front_camera(640, 480)
+    cs = gs.camera_struct(cam)
+    p, m = _gpu_scene(n, degree, 11), 1003
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    g2d = torch.randn((gs.G2D, n), generator=gen, device=DEV)
+
+    def both(q, d2):
+        k = q["means"].shape[1]
+        g = gs.gaussians_struct(*(q[x] for x in ("means", "log_scales", "quats", "logits", "sh")), degree)
+        out = gs.ProjectedBuffers(k, DEV)
+        gs.kernel_timer_start()
+        gs.project(g, cs, out)
+        res = {}
+        for cg in (True, False):
+            grads = {x: torch.empty_like(v) for x, v in q.items()}
+            gs.project_bwd(g, cs, d2, grads, proj=out if cg else None)
+            res.update({f"grad {x} {cg}": v for x, v in grads.items()})
+        names = set(gs.kernel_timer_stop())
+        res.update(records=out.records.t(), depth=out.depth, radius=out.radius, tiles=out.tiles_touched,
+                   cgrad=out.colour_grad)
+        return res, names
+
+    whole, names = both(p, g2d)
+    part, small = both({x: v[..., :m].contiguous() for x, v in p.items()}, g2d[:, :m].contiguous())
+    large = 2 * 4 * (11 + 3 * (degree + 1) ** 2) * n > 200e6
+    assert large == (n != 423_000)
+    assert (f"k_project<{degree}, true>" in names) == large and f"k_project<{degree}, false>" in small
+    assert (f"k_project_bwd<{degree}, false, true>" in names) == large
+    for x, v in part.items():
+        assert torch.equal(whole[x][..., :m].contiguous().view(torch.int32), v.contiguous().view(torch.int32)), x
+
+
+@pytest.mark.parametrize("n,degree", [(300_000, 3), (280_000, 3), (750_002, 1)])
+def test_optimiser_of_large_sets_is_the_same_bits(gs, n, degree):
+    """One Adam step past the caches (four arrays of more than 256 MiB; 280,000 of
+    degree 3 lie just below): each Gaussian gets the bits that it gets in a small set."""
+    m_ = 1001
+    p, gr, mo, vo = (_gpu_scene(n, degree, 20 + k) for k in range(4))
+    vo = {x: v.square() for x, v in vo.items()}
+    small = [{x: v[..., :m_].contiguous() for x, v in d.items()} for d in (p, gr, mo, vo)]
+    lrs = dict(means=1e-3, log_scales=2e-3, quats=3e-3, logits=4e-3, sh_dc=5e-3, sh_rest=6e-3)
+    large = 16 * (11 + 3 * (degree + 1) ** 2) * n > 256 * 2 ** 20
+    assert large == (n != 280_000)
+    gs.kernel_timer_start()
+    gs.adam_gaussians(n, degree, p, gr, mo, vo, lrs, 7)
+    assert (f"k_adam_gaussians<{'true' if large else 'false'}>") in gs.kernel_timer_stop()
+    gs.adam_gaussians(m_, degree, *small, lrs, 7)
+    torch.cuda.synchronize()
+    for a, b in zip((p, mo, vo), (small[0], small[2], small[3])):
+        for x in a:
+            assert torch.equal(a[x][..., :m_].contiguous().view(torch.int32), b[x].view(torch.int32)), x
+
+
 def _slab_scene(n_small=20000, n_big=700, seed=93):
     """Small Gaussians everywhere plus large ones in a thin depth slab: rank
     groups inside the slab touch thousands of tiles, the others a few hundred."""
