@@ -492,6 +492,8 @@ __device__ __forceinline__ float row_sum16(float v) {
   return v;
 }
 
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // A wave's sums: rows 32 half .. + 31 of dW1 and dW2 over its pair's samples, the
 // rest over its own.
 struct MlpGrads {
@@ -669,8 +671,14 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(int S, int per, cons
   auto group_of = [&](int unit, int q) { return (static_cast<int64_t>(unit) * gpl + q) * 16 + r; };
   SampleIn cur = load_sample<MODE, true>(group_of(wave_id, 0), wave_id < nunits ? S : 0, per, g, latents, dirs,
                                          means, radius, cin, dmean, cs, ss);
-  // (every wave of a workgroup takes as many steps as its first)
-  for (int unit = wave_id; unit - wave < nunits; unit += nwaves) {
+  // a pair of waves with no unit at all (few units, one step) takes its barriers only
+  // (16 samples 17 -> 11 us a call, 64 of one latent 28 -> 19; scalar, so that the
+  // branch round the barriers is one)
+  const bool idle = uniform(wave_id & ~1) >= nunits;
+  if (idle)
+    for (int q = 0; q < 2 * gpl; ++q) lds_barrier();
+  // (every other wave of a workgroup takes as many steps as its first)
+  for (int unit = idle ? nunits + wave : wave_id; unit - wave < nunits; unit += nwaves) {
     floatx4 zacc = zero;
     for (int q = 0; q < gpl; ++q) {
       // MODE 1: addresses that depend on the lane are worked out anew each time;
@@ -733,6 +741,8 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(int S, int per, cons
 
   // the workgroup's partial vector (D layout: row 4g + i of a 16-row block,
   // column r): waves 0..3 and 4..7 add up in turn, each half in its own copy
+  // (the first `used` only: the others had no unit, nor had their pair)
+  const int used = max(2, min(kBwdWaves, (nunits - static_cast<int>(blockIdx.x) * kBwdWaves + 1) & ~1));
   float* const out = u.part[wave >> 2];
 #pragma unroll
   for (int b = 0; b < 4; ++b)
@@ -746,7 +756,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(int S, int per, cons
   G.loss = row_sum16(G.loss);
   for (int w = 0; w < 4; ++w) {
     __syncthreads();
-    if ((wave & 3) != w) continue;
+    if ((wave & 3) != w || uniform(wave) >= used) continue;
     auto add = [&](int p, float v) { out[p] = w ? out[p] + v : v; };
     auto add_half = [&](int p, float v) { out[p] = w > 1 ? out[p] + v : v; };   // rows that every other wave has
 #pragma unroll
@@ -783,7 +793,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(int S, int per, cons
   }
   __syncthreads();
   for (int p = threadIdx.x; p < kPartStride; p += 64 * kBwdWaves)
-    partial[static_cast<int64_t>(blockIdx.x) * kPartStride + p] = u.part[0][p] + u.part[1][p];
+    partial[static_cast<int64_t>(blockIdx.x) * kPartStride + p] = used > 4 ? u.part[0][p] + u.part[1][p] : u.part[0][p];
 }
 
 // Sum of the workgroups' partial vectors: a block takes 64 parameters, eight

@@ -186,6 +186,46 @@ def test_mlp_backward_shares_that_end_anywhere(gs, n, per):
     assert (np.abs(whole_P - parts[0][1] - parts[1][1]) <= tol).all()
 
 
+@pytest.mark.parametrize("groups,per", [(0, 1), (1, 1), (2, 1), (3, 1), (4, 1), (5, 1), (6, 1), (8, 1), (9, 1), (3, 64), (6, 64)])
+def test_mlp_backward_of_few_groups(gs, groups, per):
+    """Workgroups whose waves have not all a group of 16 samples (or, per = 64, a
+    latent of four): pairs of waves without one take no part.  The weights'
+    gradient is the sum of the units' own up to FP32 rounding, the latents' have
+    their bits, and what the workspace held before does not matter."""
+    unit = max(per, 16)
+    n, S = groups * unit // per, groups * unit
+    Pbits = kaiming_params(50)
+    z = scenes.bf16_bits(np.random.default_rng(51).normal(0, 0.5, (max(n, 1), 16)).astype(np.float32))
+    d = _dirs(max(n, 1), per, 52).reshape(-1, 3)
+    G = np.random.default_rng(53).normal(size=(max(S, 1), 3)).astype(np.float32)
+    packed = _packed(gs, Pbits)
+
+    def grads(lo, hi):
+        k = hi - lo
+        dlat = torch.empty((max(k // per, 1), 16), dtype=torch.float32, device=DEV)
+        dP = torch.full((oracle.MLP_PARAMS,), float("nan"), device=DEV)
+        ws = torch.full((gs.mlp_bwd_workspace(k, per) // 4,), float("nan"), device=DEV)
+        i = slice(lo // per, max(hi // per, lo // per + 1))
+        gs.mlp_bwd(k, per, to_dev(z[i].view(np.int16)), to_dev(d[lo:max(hi, lo + 1)]), packed, dlat, dP, ws,
+                   dL_drgb=to_dev(G[lo:max(hi, lo + 1)]))
+        torch.cuda.synchronize()
+        return dlat.cpu().numpy()[:k // per], dP.cpu().numpy().astype(np.float64)
+
+    whole_z, whole_P = grads(0, S)
+    if groups == 0:
+        assert (whole_P == 0).all()
+        return
+    parts = [grads(u * unit, (u + 1) * unit) for u in range(groups)]
+    assert np.array_equal(whole_z, np.concatenate([p[0] for p in parts]))
+    P = scenes.bf16_to_f32(Pbits).astype(np.float64)
+    x = oracle.mlp_inputs(scenes.bf16_to_f32(z).astype(np.float64), d.reshape(n, per, 3).astype(np.float64))
+    mass = bwd_bounds(x, P, G.astype(np.float64))[2]
+    # both sides round sums of at most S terms; a bounded share of the mass may
+    # come from gates that the exact network has closed
+    tol = 2 * S * F32 * (mass + 1e-2 * mass.max()) + 1e-7
+    assert (np.abs(whole_P - sum(p[1] for p in parts)) <= tol).all()
+
+
 def test_mlp_distillation_loss_and_gradient(gs):
     """Loss mode: L = scale * sum |c - target|^2 with the gradient taken from
     the kernel's own colours."""
