@@ -643,6 +643,36 @@ def test_deterministic_rows_at_the_edges_of_batches(gs, n):
     assert (np.abs(whole - sum(parts)) <= 8 * 2.0 ** -24 * mass).all()
 
 
+@pytest.mark.parametrize("n", [1, 128, 129, 256, 257, 385])
+def test_deterministic_rows_reach_every_entry(gs, n):
+    """One tile of n entries, all of them reached (checked): every Gaussian has a
+    row, on either side of the parts of 128 and the batches of 256, and the rows
+    are the oracle's."""
+    scene = scenes.uniform_scene(n, 60 + n, sh_degree=0)
+    scene.means[:] *= 0.05
+    scene.log_scales[:] = np.clip(scene.log_scales, -4.0, -2.0)
+    scene.logits[:] = -4.0
+    cam = scenes.front_camera(16, 16)
+    p, g, out = gpu_project(gs, scene, cam)
+    h = proj_host(out)
+    k, pl, ranges = gpu_bin_sort(gs, n, out, cam)
+    o_pl, o_ranges, _, _ = oracle.bin_sort(h["u"], h["v"], h["radius"], h["depth"], 16, 16)
+    assert k == n
+    G = scenes.upstream_grad(cam, 8)
+    names = "u v Sxx Sxy Syy o r g b".split()
+    for sched in (gs.SCHEDULE_PLAIN, gs.SCHEDULE_BALANCED):
+        image, fT, nc, ck = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=sched)
+        assert int(nc.max()) == n and float(fT.min()) > 1e-4
+        _, _, _, flips, amb, _ = check_render(image, fT, nc, h["rec"][:, :9], o_pl, o_ranges, cam)
+        G[:, amb] = 0.0
+        _, o_g2d, o_mass = oracle_render_bwd_sigma(h["rec"][:, :9], o_pl, o_ranges, cam, G, flips=flips)
+        rows = gpu_render_bwd(gs, n, out, pl, ranges, k, cam, fT, nc, ck, to_dev(G), deterministic=True,
+                              schedule=sched).cpu().numpy().T
+        assert (o_mass[:, 6] > 0).all() and (rows[:, 5:9] != 0).any(axis=1).all()
+        for j, nm in enumerate(names):
+            grad_close(rows[:, j], o_g2d[:, j], name=f"schedule {sched} g2d.{nm}", mass=o_mass[:, j])
+
+
 @pytest.mark.parametrize("width", [2400, 4800])
 def test_bin_sort_wide_frame_fallback(gs, width):
     """Wide frames: 150 x 63 tiles (9,450: the direct emission, 19 x 8 super
