@@ -764,7 +764,7 @@ constexpr int kDcComps = 12;   // spherical-harmonics planes that a workgroup of
 // and a new point next to each sparse point (after all kept points).  Workgroup
 // row 0 writes the geometry, row y > 0 the colour planes 12 (y - 1) to 12 y - 1.
 // HBM bounds it: 190 MB past the L2s (kept points move to where the cache lines no
-// longer match) in 33 us at 200,000 points, 5.7 TB/s; one thread per point, all planes
+// longer match) in 40 us at 200,000 points, 4.8 TB/s; one thread per point, all planes
 // in turn, took 61.
 __global__ __launch_bounds__(256) void k_dc_write(int n, DcArrays A, const uint32_t* __restrict__ pos,
                                                   const int32_t* __restrict__ partner, const float* __restrict__ dbar,

@@ -11,9 +11,10 @@
 // LDS (one 48-byte record per thread, three 16-byte loads) and every lane
 // reads them back as broadcasts.  The per-pair body is branch-free; a wave
 // leaves a batch as soon as all its lanes are done (ballot), and the workgroup
-// leaves the tile when all 256 pixels are done.  Tiles are mapped so that
-// neighbouring tiles run on the same XCD and share its L2.  Frames of few
-// tiles take a forward that spreads each tile over four CUs.
+// leaves the tile when all 256 pixels are done.  The forward takes the tiles row
+// by row over all eight XCDs; the backward gives each XCD a contiguous part of
+// the frame, so that a Gaussian's atomics meet in one L2.  Frames of few tiles
+// take a forward that spreads each tile over four CUs.
 //
 // This file is compiled with -ffp-contract=off: the forward and the backward
 // evaluate alpha through the same inline function with explicit fmaf, so the
@@ -161,8 +162,9 @@ constexpr float kHeavyFactorFwd = 3.0e38f;
 // Tile of workgroup `bid`.  Plain form: row by row, so that neighbouring tiles,
 // which share Gaussians, are walked at the same time on all eight XCDs.  (A
 // contiguous eighth of the frame to each XCD, for its L2's sake, leaves the
-// XCD with the densest part to finish alone: forward 162 us against 145 on the
-// 1M-Gaussian 1600 x 1064 workload, 447 against 362 at 1M on 3840 x 2160.)
+// XCD with the densest part to finish alone: forward 165 us against 146 on the
+// 1M-Gaussian 1600 x 1064 workload, 413 against 370 at 1M on 3840 x 2160, 328
+// against 320 for 1.5M stretched ones on 1920 x 1080; 200k on 800 x 800 106 against 108.)
 // With a plan (balanced form): heavy tiles first, largest first, then the
 // others in tile order.
 // Light tiles (no more than kLightMax entries to walk) go to the merged
@@ -1270,12 +1272,16 @@ __global__ __launch_bounds__(256) void k_det_reduce(int n, const uint32_t* __res
 // the quadrant, on exact BF16 splits, 266 us against 273), moved the largest
 // scale gradients of stretched Gaussians by up to 8e-3 of the gradients' rms.
 // (So did walking several batches per workgroup, 621 us against 660 at 1.5M
-// stretched Gaussians.)  With the item carrying
-// its list position, 16-bit lists and the shorter support test it runs eight
-// waves per SIMD (63 registers against 71): 260 us against 273 at 1M Gaussians,
-// 610 against 682 at 1.5M stretched ones (seven waves: 264 and 628), and with
-// colour-hash sampling, where four workgroups now share a CU's LDS instead of
-// three, 201 against 270.
+// stretched Gaussians.)  The atomics' order alone moves the largest of them by
+// 1e-3 of the rms between two runs, at times by 2e-2; adding up the four waves'
+// sums in LDS first (one atomic per entry and component) halves the distance
+// from the sums in 64 bits but costs 258 us against 271 and 609 against 641.
+// With the item carrying its list position, 16-bit lists and the shorter support
+// test: 260 us against 273 at 1M Gaussians, 610 against 682 at 1.5M stretched
+// ones, and with colour-hash sampling, where four workgroups now share a CU's LDS
+// instead of three, 201 against 270.  The launch bound holds it to 63 registers,
+// eight waves per SIMD; the 68 that the compiler takes by itself leave seven: 270
+// against 267 and 632 against 612.
 template <bool DET, bool CHS = false>
 __global__ __launch_bounds__(256, DET || CHS ? 1 : 8) void k_render_bwd(const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ point_list,
