@@ -187,8 +187,8 @@ gs_status gs_bin_sort_async(int64_t n, const gs_projected* proj, const gs_camera
 /* Work split of the compositing kernels (Sec. IV: workload imbalance between
  * dense and sparse tiles, adaptive merging of thread blocks).  PLAIN: one
  * workgroup per tile, in the backward with neighbouring tiles on one XCD (the
- * exact forward spreads a tile over four workgroups where the frame has few
- * tiles: up to 400, or up to 640 where k is at least 64 a tile).
+ * exact forward spreads a tile over four workgroups in frames of up to 448
+ * tiles, and one with a long list in frames of up to 1280).
  * BALANCED: the backward gives every 256-entry batch of a tile's walk its
  * own workgroup -- (tile, batch) items planned on the device from the
  * largest n_contrib of each tile, which the forward leaves in t_ckpt -- and

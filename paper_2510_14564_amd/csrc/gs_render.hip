@@ -14,7 +14,7 @@
 // leaves the tile when all 256 pixels are done.  The forward takes the tiles row
 // by row over all eight XCDs; the backward gives each XCD a contiguous part of
 // the frame, so that a Gaussian's atomics meet in one L2.  Frames of few tiles
-// take a forward that spreads each tile over four CUs.
+// take a forward that spreads each tile, or each with a long list, over four CUs.
 //
 // This file is compiled with -ffp-contract=off: the forward and the backward
 // evaluate alpha through the same inline function with explicit fmaf, so the
@@ -490,21 +490,15 @@ __device__ __forceinline__ bool fwd_pair(const float4& p, const float4& q, float
 // COUNT = true runs the same decisions on every entry (no culling) but only
 // counts, per pixel, the pairs examined (alpha evaluated before the walk ends)
 // and the pairs blended, and adds them to counts[0], counts[1].
-template <bool COUNT, bool CHS = false>
-__global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ranges,
-                                                    const uint32_t* __restrict__ point_list,
-                                                    const float4* __restrict__ rec, DevCam cam,
-                                                    float* __restrict__ image, float* __restrict__ final_T,
-                                                    uint32_t* __restrict__ n_contrib, float* __restrict__ t_ckpt,
-                                                    unsigned long long* __restrict__ counts,
-                                                    const int32_t* __restrict__ plan,
-                                                    uint32_t* __restrict__ tile_work,
-                                                    float* __restrict__ c_ckpt, size_t cplane) {
-  __shared__ Stage st;
-  __shared__ typename std::conditional<CHS, ChsStage, char>::type cs;
-  __shared__ alignas(16) uint32_t table[CHS ? kChsBuckets : 1];
-  const int tile = tile_of_block(plan, blockIdx.x);
-  if (tile < 0) return;
+// (cs, table: the colour hash's, else unused.)
+template <bool COUNT, bool CHS, class ChsLds>
+__device__ __forceinline__ void fwd_tile(int tile, Stage& st, ChsLds& cs, uint32_t* table,
+                                         const uint2* __restrict__ ranges, const uint32_t* __restrict__ point_list,
+                                         const float4* __restrict__ rec, const DevCam& cam,
+                                         float* __restrict__ image, float* __restrict__ final_T,
+                                         uint32_t* __restrict__ n_contrib, float* __restrict__ t_ckpt,
+                                         unsigned long long* __restrict__ counts, uint32_t* __restrict__ tile_work,
+                                         float* __restrict__ c_ckpt, size_t cplane) {
   if constexpr (CHS) chs_clear(table);
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   int lx, ly;
@@ -606,6 +600,25 @@ __global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ra
   }
 }
 
+template <bool COUNT, bool CHS = false>
+__global__ __launch_bounds__(256) void k_render_fwd(const uint2* __restrict__ ranges,
+                                                    const uint32_t* __restrict__ point_list,
+                                                    const float4* __restrict__ rec, DevCam cam,
+                                                    float* __restrict__ image, float* __restrict__ final_T,
+                                                    uint32_t* __restrict__ n_contrib, float* __restrict__ t_ckpt,
+                                                    unsigned long long* __restrict__ counts,
+                                                    const int32_t* __restrict__ plan,
+                                                    uint32_t* __restrict__ tile_work,
+                                                    float* __restrict__ c_ckpt, size_t cplane) {
+  __shared__ Stage st;
+  __shared__ typename std::conditional<CHS, ChsStage, char>::type cs;
+  __shared__ alignas(16) uint32_t table[CHS ? kChsBuckets : 1];
+  const int tile = tile_of_block(plan, blockIdx.x);
+  if (tile < 0) return;
+  fwd_tile<COUNT, CHS>(tile, st, cs, table, ranges, point_list, rec, cam, image, final_T, n_contrib, t_ckpt, counts,
+                       tile_work, c_ckpt, cplane);
+}
+
 
 // Forward of light tiles, merged four to a workgroup: one wave per tile, each
 // lane four pixels (the same lane position in each 8x8 quadrant).  The
@@ -698,16 +711,25 @@ __global__ __launch_bounds__(256) void k_render_fwd_light(const uint2* __restric
 // against 58; 117 tiles the same.
 // Measured (forward, us; this against k_render_fwd): 16 tiles, 20k clustered Gaussians
 // 130 : 539, uniform ones 47 : 123; 256 tiles 42 : 104 and 33 : 52; 400 tiles 43 : 92 and
-// 35 : 45, and no set on up to 400 tiles is slower by more than 0.5 us.  The chip holds
-// the quadrants of 448 tiles; beyond that they queue, and each stages its tile's list for
-// itself.  625 tiles, 20 to 1,500 uniform Gaussians (up to 25 entries a tile) 9 : 7 to
-// 16 : 12, 20k (330 entries, all tiles alike) 45 : 41, clustered ones 43 : 76, 400k 55 : 57 and
-// 113 : 217; 900 tiles, 100k 56 : 41 and 85 : 113; 1,225 tiles 68 : 42 and 87 : 96.  So up
-// to 400 tiles any set, up to 640 those with 64 entries a tile and more.
-constexpr int kFewTiles = 400, kFewLongTiles = 640, kFewLongMean = 64;
-static bool few_tiles(int ntiles, int64_t k) {
-  return ntiles <= kFewTiles || (ntiles <= kFewLongTiles && k >= static_cast<int64_t>(kFewLongMean) * ntiles);
-}
+// 35 : 45; 441 tiles, 100k, 76 : 160 and 39 : 45.
+// The chip holds the quadrants of 448 tiles.  In larger frames they queue, and each
+// stages its tile's list for itself, so there (ALL = false) only long lists get four
+// workgroups; the others' first workgroup walks the whole tile as k_render_fwd does, and
+// the other three end at once.  All first workgroups come first, row by row: the chip
+// holds those of 1,280 tiles and leaves the rest of its places to the long lists' others.
+// (Tiles in contiguous eighths, each with its four: 112 against 66 us.)  A list is long
+// above 2,048 entries, above 512 if it is longer than the mean, and above three times the mean:
+//                                     k_render_fwd  all in four  this
+//   900 tiles, uniform, 20k / 100k         39 / 42      53 / 56    40 / 45
+//     clustered, 20k / 100k / 400k    60 / 114 / 165  48 / 84 / 105  33 / 58 / 114
+//   1,225 tiles, uniform, 20k / 100k       39 / 43      62 / 67    41 / 49
+//     clustered, 20k / 100k / 400k     55 / 97 / 133  50 / 87 / 115  34 / 60 / 106
+//   1,056 tiles (192 x 1408), clustered   139 / 375      55 / 111   49 / 100
+//   984 tiles of an orbit, 194k clustered     1277          213        212
+// Lists of fewer than two entries on average are left to k_render_fwd (100 Gaussians
+// on 900 tiles 8 : 12).
+constexpr int kFewTiles = 448, kFewLongTiles = 1280, kFewLeastMean = 2;
+__device__ __forceinline__ uint32_t few_long(uint32_t mean) { return min(3u * mean, min(max(mean, 512u), 2048u)); }
 constexpr int kFewBatches = 1;
 constexpr int kFewChunk = kFewBatches * kBatch;
 
@@ -748,6 +770,7 @@ __device__ __forceinline__ void rows_to_all(float x, float (&v)[4]) {
   v[3] = __uint_as_float(b[1]);
 }
 
+template <bool ALL>
 __global__ __launch_bounds__(256) void k_render_fwd_few(const uint2* __restrict__ ranges,
                                                         const uint32_t* __restrict__ point_list,
                                                         const float4* __restrict__ rec, DevCam cam,
@@ -755,10 +778,29 @@ __global__ __launch_bounds__(256) void k_render_fwd_few(const uint2* __restrict_
                                                         uint32_t* __restrict__ n_contrib, float* __restrict__ t_ckpt,
                                                         uint32_t* __restrict__ tile_work,
                                                         float* __restrict__ c_ckpt, size_t cplane) {
-  __shared__ FewStage st;
+  __shared__ alignas(16) char lds[ALL || sizeof(FewStage) > sizeof(Stage) ? sizeof(FewStage) : sizeof(Stage)];
+  FewStage& st = *reinterpret_cast<FewStage*>(lds);
   const int t = threadIdx.x, lane = t & 63, phase = lane >> 4;
   const int wave = static_cast<int>(uniform(static_cast<uint32_t>(t >> 6)));
-  const int item = xcd_remap(blockIdx.x, gridDim.x), tile = item >> 2, quad = item & 3;
+  const int ntiles = static_cast<int>(gridDim.x) >> 2;
+  int tile, quad;
+  if constexpr (ALL) {
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    tile = item >> 2;
+    quad = item & 3;
+  } else {
+    quad = static_cast<int>(blockIdx.x) / ntiles;
+    tile = static_cast<int>(blockIdx.x) - quad * ntiles;
+    const uint2 all = ranges[tile];
+    // the last tile's list ends at the frame's number of entries
+    if (all.y - all.x <= few_long(ranges[ntiles - 1].y / static_cast<uint32_t>(ntiles))) {
+      char none;
+      if (quad == 0)
+        fwd_tile<false, false>(tile, *reinterpret_cast<Stage*>(lds), none, nullptr, ranges, point_list, rec, cam,
+                               image, final_T, n_contrib, t_ckpt, nullptr, tile_work, c_ckpt, cplane);
+      return;
+    }
+  }
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   const int lx = ((quad & 1) << 3) + ((wave & 1) << 2), ly = ((quad >> 1) << 3) + ((wave >> 1) << 2);   // the block's first pixel
   const int px_i = tx * kTile + lx + (lane & 3), py_i = ty * kTile + ly + ((lane >> 2) & 3);
@@ -908,7 +950,7 @@ __global__ __launch_bounds__(256) void k_render_fwd_few(const uint2* __restrict_
     __syncthreads();                            // st.act is no longer read
     if (lane == 0) st.act[wave] = mx;
     __syncthreads();
-    if (t == 0) tile_work[item] = max(max(st.act[0], st.act[1]), max(st.act[2], st.act[3]));
+    if (t == 0) tile_work[4 * tile + quad] = max(max(st.act[0], st.act[1]), max(st.act[2], st.act[3]));
   }
 }
 
@@ -1032,11 +1074,12 @@ gs_status launch_render_fwd(const gs_projected& proj, const uint32_t* point_list
                                                       reinterpret_cast<const float4*>(proj.records), cam, image,
                                                       final_T, n_contrib, t_ckpt, nullptr, plan, tile_work, c_ckpt,
                                                       cplane);
-  } else if (few_tiles(ntiles, k) && !plan) {
-    TimedLaunch gs_tl("k_render_fwd_few", s);
-    k_render_fwd_few<<<4 * ntiles, 256, 0, s>>>(reinterpret_cast<const uint2*>(ranges), point_list,
-                                                reinterpret_cast<const float4*>(proj.records), cam, image, final_T,
-                                                n_contrib, t_ckpt, tile_work, c_ckpt, cplane);
+  } else if (!plan && (ntiles <= kFewTiles || (ntiles <= kFewLongTiles && k >= kFewLeastMean * ntiles))) {
+    const bool all = ntiles <= kFewTiles;
+    TimedLaunch gs_tl(all ? "k_render_fwd_few<true>" : "k_render_fwd_few<false>", s);
+    (all ? k_render_fwd_few<true> : k_render_fwd_few<false>)<<<4 * ntiles, 256, 0, s>>>(
+        reinterpret_cast<const uint2*>(ranges), point_list, reinterpret_cast<const float4*>(proj.records), cam, image,
+        final_T, n_contrib, t_ckpt, tile_work, c_ckpt, cplane);
   } else {
     TimedLaunch gs_tl("k_render_fwd<false, false>", s);
     k_render_fwd<false><<<ntiles, 256, 0, s>>>(reinterpret_cast<const uint2*>(ranges), point_list,

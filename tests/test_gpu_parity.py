@@ -773,24 +773,50 @@ def test_few_tiles_forward_is_the_same_bits(gs, n, width, height):
     say(f"  {n} on {width}x{height}: K={k}, longest list {int((ranges[:, 1] - ranges[:, 0]).max())}")
 
 
-@pytest.mark.parametrize("n,width,height,few", [(50, 320, 320, True), (20000, 320, 320, True),
-                                                (50, 336, 320, False), (20000, 336, 320, True),
-                                                (20000, 512, 320, True), (500, 512, 320, False),
-                                                (20000, 528, 320, False)])
-def test_few_tiles_forward_where_it_is_chosen(gs, n, width, height, few):
-    """The forward of few tiles runs up to 400 tiles, and up to 640 of at least 64
-    entries each on average; on either side of both lines the image, final_T and
-    n_contrib are MERGED's, bit for bit."""
+@pytest.mark.parametrize("n,width,height,longs", [(50, 320, 320, None), (20000, 448, 256, None), (20, 464, 256, False),
+                                                  (600, 464, 256, True), (20000, 464, 250, True), (100000, 400, 400, True),
+                                                  (200000, 400, 400, True), (400000, 399, 401, True), (20000, 16, 20480, True),
+                                                  (20, 640, 512, False), (20000, 640, 512, True), (20000, 656, 512, False)])
+def test_few_tiles_forward_where_it_is_chosen(gs, n, width, height, longs):
+    """Up to 448 tiles every tile is walked by four workgroups, up to 1,280 (two
+    entries each and more on average) the long lists are: longer than three times the mean,
+    than the mean and 512, or than 2,048.  On either side of every line the image,
+    final_T, n_contrib and a deterministic backward from the checkpoints are those of
+    MERGED, which never takes these kernels, bit for bit."""
     scene = scenes.uniform_scene(n, 99, log_scale_mean=-3.4, log_scale_std=0.5, sh_degree=0)
+    scene.means[:, n // 2:] *= 0.2     # half of them in the middle: lists of very different lengths
     cam = scenes.front_camera(width, height)
     p, g, out = gpu_project(gs, scene, cam)
     k, pl, ranges = gpu_bin_sort(gs, n, out, cam)
-    want = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=gs.SCHEDULE_MERGED)[:3]
+    ntiles = ranges.shape[0]
+    want_few = None
+    if ntiles <= 448 or (ntiles <= 1280 and k >= 2 * ntiles):
+        want_few = "k_render_fwd_few<true>" if ntiles <= 448 else "k_render_fwd_few<false>"
+    length, mean = ranges[:, 1].long() - ranges[:, 0].long(), k // ntiles
+    n_long = int((length > min(3 * mean, min(max(mean, 512), 2048))).sum())
+    say(f"  {n} on {width}x{height}: {ntiles} tiles, K={k}, mean {mean}, {n_long} long lists, {want_few}")
+    if longs is not None:
+        assert (want_few == "k_render_fwd_few<false>" and 0 < n_long < ntiles) == longs
+    G, cs = to_dev(scenes.upstream_grad(cam, 2003)), gs.camera_struct(cam)
+
+    def backward(fT, nc, ck):
+        g2d = torch.empty((gs.G2D, n), dtype=torch.float32, device=DEV)
+        ws = torch.empty(gs.render_bwd_2d_workspace(n, k, cs, True), dtype=torch.uint8, device=DEV)
+        gs.render_bwd_2d(n, out, pl, ranges, k, cs, fT, nc, ck, G, g2d, ws, deterministic=True)
+        return g2d
+
+    *want, ck = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=gs.SCHEDULE_MERGED)
+    want.append(backward(want[1], want[2], ck))
     for sched in (gs.SCHEDULE_PLAIN, gs.SCHEDULE_BALANCED):
         gs.kernel_timer_start()
-        got = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=sched)[:3]
-        assert ("k_render_fwd_few" in gs.kernel_timer_stop()) == few
+        *got, ck = gpu_render(gs, n, out, pl, ranges, k, cam, schedule=sched)
+        names = [x for x in gs.kernel_timer_stop() if x.startswith("k_render_fwd")]
+        assert names == [want_few or "k_render_fwd<false, false>"]
+        got.append(backward(got[1], got[2], ck))
         assert all(torch.equal(a, b) for a, b in zip(got, want)), f"schedule {sched}"
+    image, fT, nc = (torch.empty_like(x) for x in want[:3])   # a frame without a backward
+    gs.render_fwd(n, out, pl, ranges, k, cs, image, fT, nc, None, schedule=gs.SCHEDULE_PLAIN)
+    assert all(torch.equal(a, b) for a, b in zip((image, fT, nc), want))
 
 
 def _gpu_scene(n, degree, seed):
