@@ -949,7 +949,7 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 // Coarse: the ranks are cut into up to 1024 chunks of equally many consecutive
 // ranks (a rank has one coarse entry per super tile its rectangle touches).
 // More chunks than the chip holds at once even out their different entry
-// counts, and chunks far above the mean are cut again (k_coarse_parts); cutting
+// counts, and chunks far above the mean are cut again (k_chunk_colscan); cutting
 // at equal entry counts needs a scan of the counts first (two launches) and gave
 // fewer, longer chunks: 33.3 -> 12.2 us for the coarse emission at 200k Gaussians,
 // 35.2 -> 33.8 at 1M, besides the scan's 17-19.
@@ -958,10 +958,10 @@ __global__ __launch_bounds__(256) void k_ranges(int ntiles, const uint32_t* __re
 //     LDS atomics per Gaussian, then prefix sums along rows and columns) --
 //     table[c][s]; it also adds up the tile counts (K).
 //  2. k_chunk_colscan: per super tile, the exclusive prefix over chunks (in
-//     place) and the total; k_coarse_parts: the super tiles' starts in the
-//     coarse list, the cut of each super tile's run into parts of at most
-//     1024 (small sets: 256) entries (numbered over the super tiles in turn),
-//     and the cut of chunks with many entries into bands of super tiles.
+//     place) and the total, and the cut of chunks with many entries into bands of
+//     super tiles; k_coarse_parts: the super tiles' starts in the coarse list
+//     and the cut of each super tile's run into parts of at most 1024 (small
+//     sets: 256) entries (numbered over the super tiles in turn).
 //  3. k_emit_coarse: one workgroup per chunk (or band of one) walks its ranks
 //     256 at a time.
 //     Rank 64 w + l of a group comes before rank 64 w' + l' on a super tile
@@ -1023,7 +1023,7 @@ static bool direct_ok(int tiles_x, int tiles_y) {
 // Ranks per chunk: a whole number of waves, at most kDirectChunks chunks.
 static int direct_ranks(int64_t n) { return static_cast<int>(ceil_div(std::max<int64_t>(n, 1), 64 * kDirectChunks) * 64); }
 static int direct_chunks(int64_t n) { return static_cast<int>(ceil_div(std::max<int64_t>(n, 1), direct_ranks(n))); }
-// Workgroups of the coarse emission at most (k_coarse_parts).
+// Workgroups of the coarse emission at most (k_chunk_colscan).
 static int direct_items(int chunks) { return chunks + chunks / 2; }
 // parts at most: every super tile's run of at most `cap` coarse entries in total
 static int64_t direct_max_parts(int64_t n, int64_t cap, int ns) {
@@ -1065,19 +1065,22 @@ __global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks,
                                                                unsigned long long* __restrict__ kfine,
                                                                unsigned long long* __restrict__ kcoarse) {
   extern __shared__ int s_diff[];   // (sy + 1) rows of (sx + 1)
-  __shared__ unsigned long long s_k[kCountWaves], s_kc[kCountWaves];
+  __shared__ unsigned long long s_k[kCountWaves];
+  __shared__ uint32_t s_kc[kCountWaves];
   const int c = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int pitch = sx + 1, cells = pitch * (sy + 1);
   for (int i = tid; i < cells; i += kCountThreads) s_diff[i] = 0;
   __syncthreads();
   const int r0 = c * ranks, r1 = min(n, r0 + ranks);
-  unsigned long long fine = 0, coarse = 0;
+  unsigned long long fine = 0;
+  uint32_t coarse = 0;
   for (int r = r0 + tid; r < r1; r += kCountThreads) {
     const uint2 rc = rect_rank[r];
     fine += rect_count(rc);
     const uint2 sr = rect_at(rc, kSuperShift);
-    coarse += rect_count(sr);
-    if (rect_count(sr) == 0) continue;
+    const uint32_t supers = rect_count(sr);
+    coarse += supers;
+    if (supers == 0) continue;
     const int x0 = static_cast<int>(sr.x & 0xFFFFu), xe = static_cast<int>(sr.x >> 16);
     const int y0 = static_cast<int>(sr.y & 0xFFFFu), ye = static_cast<int>(sr.y >> 16);
     atomicAdd(&s_diff[y0 * pitch + x0], 1);
@@ -1085,11 +1088,10 @@ __global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks,
     atomicAdd(&s_diff[ye * pitch + x0], -1);
     atomicAdd(&s_diff[ye * pitch + xe], 1);
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    fine += __shfl_xor(fine, o, 64);
-    coarse += __shfl_xor(coarse, o, 64);
-  }
-  if (lane == 0) { s_k[wave] = fine; s_kc[wave] = coarse; }
+  for (int o = 32; o > 0; o >>= 1) fine += __shfl_xor(fine, o, 64);
+  if (lane == 0) s_k[wave] = fine;
+  coarse = static_cast<uint32_t>(wave_incl_scan(static_cast<int>(coarse)));
+  if (lane == 63) s_kc[wave] = coarse;
   __syncthreads();
   if (tid == 0) {
     unsigned long long k = 0, kc = 0;
@@ -1106,6 +1108,32 @@ __global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks,
     for (int x = lane; x < sx; x += 64) out[y * sx + x] = static_cast<uint32_t>(s_diff[y * pitch + x]);
 }
 
+// Exclusive prefix of one 64-bit value per thread over a workgroup of
+// THREADS threads (s_w: THREADS / 64 words of LDS, free again on return);
+// `all` is the sum.
+template <int THREADS>
+__device__ __forceinline__ unsigned long long block_exclusive_u64(unsigned long long v, unsigned long long* s_w,
+                                                                  unsigned long long& all) {
+  constexpr int W = THREADS / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned long long incl = v;
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned long long u = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += u;
+  }
+  if (lane == 63) s_w[wave] = incl;
+  __syncthreads();
+  unsigned long long before = incl - v;
+  all = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    all += s_w[w];
+    before += (w < wave) ? s_w[w] : 0ull;
+  }
+  __syncthreads();
+  return before;
+}
+
 // One workgroup per 16 super tiles: thread (g, x) = (tid / 16, tid % 16) owns
 // a contiguous 64th of the chunks of super tile x, whose counts it holds in
 // registers (one read of the table, all loads in flight at once); the 64
@@ -1114,10 +1142,47 @@ __global__ __launch_bounds__(kCountThreads) void k_chunk_count(int n, int ranks,
 // trip to memory: a few hundred super tiles make only a handful of
 // workgroups, and 16 columns to each (64 bytes of a table row) take
 // 7.3 us for 977 chunks at 1M Gaussians, 64 columns 28.7 us.
+//
+// A workgroup of its own cuts the coarse emission's items: a chunk with more
+// than twice the mean of the chunks' coarse entries (kcoarse[c]) becomes bands of
+// super-tile columns or rows (the longer side, `side` of them), a workgroup
+// each.  Item i is (chunk, first | end << 16), in chunk order, nitems[0] their
+// number, at most direct_items: the cuts add at most the total over twice the mean,
+// half the chunks.  Equal ranks are not equal entries: near the camera
+// consecutive ranks cover most of the frame.  With 4,000 such Gaussians of 1M the
+// emission takes 43 us at 1600 x 1064 and 61 at 3840 x 2160, against 143 and 542
+// with a workgroup per chunk; where no chunk is cut, the items cost it 1 us.  (Cut
+// beside k_coarse_parts' one workgroup, they took that from 3.1 us to 4.5; the
+// other bands after all chunks, 54 and 81 us, or by the chunks' own workgroups, 71
+// and 105.)
+struct ChunkItems {
+  int side;
+  const unsigned long long* kcoarse;
+  uint2* items;
+  uint32_t* nitems;
+};
 constexpr int kColPer = kDirectChunks / 64;
 __global__ __launch_bounds__(1024) void k_chunk_colscan(int C, int ntiles, uint32_t* __restrict__ table,
-                                                        uint32_t* __restrict__ total) {
+                                                        uint32_t* __restrict__ total, ChunkItems a) {
   __shared__ uint32_t s_part[64][17];
+  if (blockIdx.x == gridDim.x - 1) {
+    // chunk tid's bands (kDirectChunks = 1024 threads)
+    __shared__ unsigned long long s_w[16];
+    const int tid = threadIdx.x;
+    const unsigned long long mine = tid < C ? a.kcoarse[tid] : 0ull, chunks = static_cast<unsigned long long>(C);
+    unsigned long long all;
+    block_exclusive_u64<1024>(mine, s_w, all);
+    const unsigned long long most = max(kBandEntries, 2ull * ((all + chunks - 1ull) / chunks));
+    const uint32_t side = static_cast<uint32_t>(a.side);
+    const uint32_t bands = mine <= most ? 1u : static_cast<uint32_t>(min(static_cast<unsigned long long>(side), (mine + most - 1ull) / most));
+    unsigned long long more = 0;
+    uint32_t at = static_cast<uint32_t>(tid);
+    if (__syncthreads_or(bands > 1u)) at += static_cast<uint32_t>(block_exclusive_u64<1024>(bands - 1u, s_w, more));
+    for (uint32_t b = 0; tid < C && b < bands; ++b)
+      a.items[at + b] = make_uint2(static_cast<uint32_t>(tid), (b * side / bands) | (((b + 1u) * side / bands) << 16));
+    if (tid == 0) a.nitems[0] = static_cast<uint32_t>(C) + static_cast<uint32_t>(more);
+    return;
+  }
   const int g = threadIdx.x >> 4, x = threadIdx.x & 15;
   const int t = blockIdx.x * 16 + x;
   const int per = (C + 63) / 64;   // at most kColPer (C <= kDirectChunks)
@@ -1145,32 +1210,6 @@ __global__ __launch_bounds__(1024) void k_chunk_colscan(int C, int ntiles, uint3
     if (c0 + k < c1) table[static_cast<size_t>(c0 + k) * ntiles + t] = run;
     run += v[k];
   }
-}
-
-// Exclusive prefix of one 64-bit value per thread over a workgroup of
-// THREADS threads (s_w: THREADS / 64 words of LDS, free again on return);
-// `all` is the sum.
-template <int THREADS>
-__device__ __forceinline__ unsigned long long block_exclusive_u64(unsigned long long v, unsigned long long* s_w,
-                                                                  unsigned long long& all) {
-  constexpr int W = THREADS / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  unsigned long long incl = v;
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned long long u = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += u;
-  }
-  if (lane == 63) s_w[wave] = incl;
-  __syncthreads();
-  unsigned long long before = incl - v;
-  all = 0;
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    all += s_w[w];
-    before += (w < wave) ? s_w[w] : 0ull;
-  }
-  __syncthreads();
-  return before;
 }
 
 // start[t] = exclusive prefix of total over the tiles, ranges[t] = (start,
@@ -1240,41 +1279,11 @@ __global__ __launch_bounds__(1024) void k_tile_starts(const uint32_t* __restrict
 // super tiles in turn: parts pbase[s] .. pbase[s+1]-1 (pbase[ns]: all parts).
 // A coarse list longer than its buffer (capacity) gives no parts: K is at
 // least as large, so the frame is reported as not fitting.
-//
-// The second workgroup cuts the coarse emission's items: a chunk with more
-// than twice the mean of the chunks' coarse entries (kcoarse[c]) becomes bands of
-// super-tile columns or rows (the longer side, `side` of them), a workgroup
-// each.  Item i is (chunk, first | end << 16), nitems[0] their number, at most
-// direct_items: the cuts add at most the total over twice the mean, half the
-// chunks.  Equal ranks are not equal entries: near the camera consecutive ranks
-// cover most of the frame.  With 4,000 such Gaussians of 1M the emission takes
-// 43 us at 1600 x 1064 and 61 at 3840 x 2160, against 143 and 542 with a
-// workgroup per chunk; where no chunk is cut, the items cost it 1 us.
-struct ChunkItems {
-  int chunks, side;
-  const unsigned long long* kcoarse;
-  uint2* items;
-  uint32_t* nitems;
-};
 __global__ __launch_bounds__(1024) void k_coarse_parts(int ns, int part, const uint32_t* __restrict__ ctotal,
                                                        uint32_t* __restrict__ cstart, unsigned long long capacity,
-                                                       uint32_t* __restrict__ pbase, ChunkItems a) {
+                                                       uint32_t* __restrict__ pbase) {
   __shared__ unsigned long long s_w[16];
   const int tid = threadIdx.x;
-  if (blockIdx.x == 1) {
-    // chunk tid's bands (kDirectChunks = 1024 threads)
-    const unsigned long long mine = tid < a.chunks ? a.kcoarse[tid] : 0ull, chunks = static_cast<unsigned long long>(a.chunks);
-    unsigned long long all, nall;
-    block_exclusive_u64<1024>(mine, s_w, all);
-    const unsigned long long most = max(kBandEntries, 2ull * ((all + chunks - 1ull) / chunks));
-    const uint32_t side = static_cast<uint32_t>(a.side);
-    const uint32_t bands = tid < a.chunks ? static_cast<uint32_t>(min(static_cast<unsigned long long>(side), max(1ull, (mine + most - 1ull) / most))) : 0u;
-    const uint32_t at = static_cast<uint32_t>(block_exclusive_u64<1024>(bands, s_w, nall));
-    for (uint32_t b = 0; b < bands; ++b)
-      a.items[at + b] = make_uint2(static_cast<uint32_t>(tid), (b * side / bands) | (((b + 1u) * side / bands) << 16));
-    if (tid == 0) a.nitems[0] = static_cast<uint32_t>(nall);
-    return;
-  }
   const int per = (ns + 1023) / 1024;
   const int t0 = min(ns, tid * per), t1 = min(ns, t0 + per);
   const uint32_t upart = static_cast<uint32_t>(part);
@@ -1924,10 +1933,11 @@ gs_status run_bin_sort(int64_t n64, const gs_projected& proj, const DevCam& cam,
         { TimedLaunch gs_tl("k_chunk_count", s); k_chunk_count<<<chunks, kCountThreads, sizeof(int) * (sx + 1) * (sy + 1), s>>>(
             n, ranks, b.rect_rank, sx, sy, b.table, b.kfine, b.kcoarse); }
         if ((st = check_launch("k_chunk_count")) != GS_OK) return st;
-        { TimedLaunch gs_tl("k_chunk_colscan", s); k_chunk_colscan<<<static_cast<unsigned>(ceil_div(ns, 16)), 1024, 0, s>>>(chunks, ns, b.table, b.ctotal); }
+        { TimedLaunch gs_tl("k_chunk_colscan", s); k_chunk_colscan<<<static_cast<unsigned>(ceil_div(ns, 16)) + 1, 1024, 0, s>>>(
+            chunks, ns, b.table, b.ctotal, ChunkItems{std::max(sx, sy), b.kcoarse, b.items, b.nitems}); }
         if ((st = check_launch("k_chunk_colscan")) != GS_OK) return st;
-        { TimedLaunch gs_tl("k_coarse_parts", s); k_coarse_parts<<<2, 1024, 0, s>>>(ns, part_entries(n), b.ctotal, b.cstart, static_cast<unsigned long long>(capacity),
-                                                                                    b.pbase, ChunkItems{chunks, std::max(sx, sy), b.kcoarse, b.items, b.nitems}); }
+        { TimedLaunch gs_tl("k_coarse_parts", s); k_coarse_parts<<<1, 1024, 0, s>>>(ns, part_entries(n), b.ctotal, b.cstart, static_cast<unsigned long long>(capacity),
+                                                                                    b.pbase); }
         if ((st = check_launch("k_coarse_parts")) != GS_OK) return st;
         { TimedLaunch gs_tl("k_emit_coarse", s); k_emit_coarse<<<direct_items(chunks), kDirectThreads, emit_dyn_lds(sx, sy), s>>>(
             n, ranks, order, b.rect_rank, b.table, b.cstart, sx, sy, b.coarse, cap32, b.items, b.nitems); }
